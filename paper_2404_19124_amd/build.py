@@ -24,6 +24,7 @@ SOURCES = [
     "kernels_verify.hip",
     "kernels_f32.hip",
     "kernels_head_skinny.hip",
+    "kernels_head_skinny32.hip",
     "kernels_head_gemm.hip",
     "kernels_tree_meta.hip",
 ]

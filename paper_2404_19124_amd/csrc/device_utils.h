@@ -53,6 +53,17 @@ __device__ __forceinline__ bool before(float v1, int32_t i1, float v2, int32_t i
   return (v1 > v2) || (v1 == v2 && i1 < i2);
 }
 
+// ---- weights as a bounds-checked buffer --------------------------------------
+// A wave-uniform stretch of `bytes` at `base`: a load at or past the end returns zero and touches no memory.
+// Streaming kernels request "the tile after next" through it without asking whether there is one.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_buffer(const void* base, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+// 16 bytes at byte offset `at`, non-temporal (every weight is read once per launch)
+__device__ __forceinline__ __attribute__((__vector_size__(16))) uint32_t load_weight(__amdgpu_buffer_rsrc_t b, int at) {
+  return __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, 2);
+}
+
 // ---- wave reductions ---------------------------------------------------------
 // Within a row of 16 lanes the exchange runs on DPP (quad permutes, then the
 // half-row and row mirrors): four steps of a few cycles each instead of LDS

@@ -409,9 +409,9 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
   if (n_cu < 1) return fail(SPEC_EINVAL, "n_cu = %d must be >= 1", n_cu);
   memset(out, 0, sizeof(*out));
   const int kt = k / 32;
-  if (skinny_fits(rows, kt)) {
+  if (skinny_fits(rows, kt) || skinny32_fits(rows, kt, n_head)) {
     out->kernel = 0;
-    out->block_rows = 16;
+    out->block_rows = rows <= 16 ? 16 : 32;
     out->tile_rows = 16;
     out->row_blocks = 1;
     out->ranges = skinny_grid(n_cu);
@@ -419,7 +419,7 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
     out->parts = skinny_grid(n_cu);
     out->k_split = 1;
     out->workgroups = skinny_grid(n_cu);
-    out->lds_bytes = (int32_t)skinny_lds_bytes(rows, kt);
+    out->lds_bytes = (int32_t)(rows <= 16 ? skinny_lds_bytes(rows, kt) : skinny32_lds_bytes());
     return SPEC_OK;
   }
   GemmPlan pl = plan_gemm(rows, n_head > 0 ? k_top : 0, n_head, n_proj, kt, n_cu);
@@ -502,11 +502,11 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
   const int K = b_ld;
   if (fold && !skinny_fits(R, job.kt)) return fail(SPEC_ESHAPE, "internal: folded stage on a contraction of %d rows", R);
   if (fold) job.fold = *fold;
-  if (skinny_fits(R, job.kt)) {
+  if (skinny_fits(R, job.kt) || skinny32_fits(R, job.kt, job.n_head)) {
     job.nparts = skinny_grid(m->n_cu);
     *nparts = job.nparts;
     const int slot = prof_slot(m, 0, R, job.n_head + job.n_proj, K);
-    HIP_TRY(launch_head_skinny(job, m->n_cu, st, EV0(slot), EV1(slot)));
+    HIP_TRY((R <= 16 ? launch_head_skinny : launch_head_skinny32)(job, m->n_cu, st, EV0(slot), EV1(slot)));
     return SPEC_OK;
   }
   GemmPlan pl = plan_gemm(R, k_top, job.n_head, job.n_proj, job.kt, m->n_cu);
@@ -903,7 +903,7 @@ extern "C" spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const vo
   const int D = m->cfg.inner_dim, V = m->cfg.vocab;
   if (m->bf16) {
     int nparts = 0;
-    if (skinny_fits(rows, D / 32)) {
+    if (skinny_fits(rows, D / 32) || skinny32_fits(rows, D / 32, V)) {
       spec_status_t s = run_contraction(m, m->ws, stage, -1, states, true, D, rows, 0, logp, nullptr, &nparts, st);
       if (s != SPEC_OK) return s;
     } else {
