@@ -1,8 +1,5 @@
-// float32 path (the small correctness configuration keeps every tensor in
-// float32 with no rounding anywhere) and the bf16 tiling kernel.
-// The float32 contraction is a plain LDS-tiled vector-ALU kernel: this path is
-// there for exactness on small shapes, not for speed; logits are materialised in
-// a workspace and reduced per row.
+// float32 path (the small exact configuration keeps every tensor in float32 with
+// no rounding anywhere) and the bf16 tiling kernel.
 #include "device_utils.h"
 #include "spec_internal.h"
 
@@ -34,98 +31,175 @@ hipError_t launch_pack_bf16(const void* src, void* dst, int n_rows, int k, bool 
   return hipGetLastError();
 }
 
-// ---- out[r][v] = sum_k a[r][k] * w[v][k] -------------------------------------
-constexpr int TM = 32, TN = 64, TK = 16;
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ a, int64_t lda,
-                                                       const float* __restrict__ w, int64_t ldw,
-                                                       float* __restrict__ out, int64_t ldo, int R, int N, int K) {
-  __shared__ float sa[TK][TM + 1];
-  __shared__ float sw[TK][TN + 1];
-  const int tid = threadIdx.x;
-  const int r0 = blockIdx.y * TM, v0 = blockIdx.x * TN;
-  const int tr = tid / 16, tv = tid % 16;  // thread computes rows tr*2..+1, cols tv*4..+3
-  float acc[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-  for (int k0 = 0; k0 < K; k0 += TK) {
-    for (int i = tid; i < TM * TK; i += 256) {
-      const int rr = i / TK, kk = i % TK;
-      sa[kk][rr] = (r0 + rr < R && k0 + kk < K) ? a[(int64_t)(r0 + rr) * lda + k0 + kk] : 0.f;
-    }
-    for (int i = tid; i < TN * TK; i += 256) {
-      const int vv = i / TK, kk = i % TK;
-      sw[kk][vv] = (v0 + vv < N && k0 + kk < K) ? w[(int64_t)(v0 + vv) * ldw + k0 + kk] : 0.f;
-    }
-    __syncthreads();
+// ---- float32 contraction on the float32 matrix instruction -------------------
+// Workgroup = 16 waves = 4 tiles of 16 weight rows x 4 parts of K, against 16 state rows (blockIdx.y, z).
+// A wave multiplies its 16 x 16 tile over its K part with v_mfma_f32_16x16x4_f32 (float32 products and
+// sums), both operands straight from memory in 16-byte pieces: lane l holds row l % 16, columns
+// 16 s + 4 (l / 16) .. + 4 of step s, and the four instructions of a step take element 0 .. 3 of every
+// lane, the same assignment of K to lanes on both sides.  The K parts are summed through LDS in order;
+// then wave r holds state row r, lane c the logit of weight row c of the 64: log-sum-exp pieces and the
+// k best leave as one partial per (row, workgroup), logits are not written.  The next stage's projection
+// is a second list of tiles in the same launch.
+//
+// Bound: launch latency and one trip through memory per stage (256 x 1024 model: 1 MB per head).  A vector-ALU
+// contraction with logits in memory and a scan per row took 24 + 6 us per stage, and 22 us for its projection; the
+// whole draft of that model 177.5 -> 46.9 us.
+constexpr int kF32Tiles = 4, kF32Parts = 4, kF32Cols = 16 * kF32Tiles;
+constexpr int kF32GridY = 32768;   // row tiles along y; more go along z
+constexpr int kF32Batch = 4;   // steps whose loads are in flight together
+
+struct F32Args {
+  const float* a;            // states [R][K]
+  const float* w[2];         // weights [n][K]: head, projection (or the only matrix)
+  int n[2], blocks[2];       // rows; workgroups along the weight rows
+  int per;                   // 64-row blocks a head workgroup covers
+  float* out[2];             // store target of the matrix (head: null = partials)
+  int64_t ldo[2];
+  int R, K, k_top, nparts;
+  int vec;                   // rows start on 16 bytes
+  Partials part;
+};
+
+__device__ __forceinline__ f32x4 load_f32x4(const float* row, int k, int K, int vec) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (vec) {                 // K is a multiple of 4
+    if (k < K) v = *reinterpret_cast<const f32x4*>(row + k);
+  } else {
 #pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float av[2], wv[4];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) av[i] = sa[kk][tr * 2 + i];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) wv[q] = sw[kk][tv * 4 + q];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[i][q] += av[i] * wv[q];
-    }
-    __syncthreads();
+    for (int i = 0; i < 4; ++i)
+      if (k + i < K) v[i] = row[k + i];
   }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = r0 + tr * 2 + i, v = v0 + tv * 4 + q;
-      if (r < R && v < N) out[(int64_t)r * ldo + v] = acc[i][q];
-    }
+  return v;
 }
 
-hipError_t launch_gemm_f32(const float* a, int64_t lda, const float* w, int64_t ldw, float* out, int64_t ldo, int R,
-                           int N, int K, hipStream_t st) {
-  dim3 grid((N + TN - 1) / TN, (R + TM - 1) / TM);
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, a, lda, w, ldw, out, ldo, R, N, K);
+__global__ __launch_bounds__(1024) void contract_f32_kernel(F32Args p) {
+  __shared__ f32x4 lds[kF32Tiles * kF32Parts * 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tile = wave & (kF32Tiles - 1), kp = wave / kF32Tiles;
+  const int mat = (int)blockIdx.x >= p.blocks[0] ? 1 : 0;
+  const int block = blockIdx.x - (mat ? p.blocks[0] : 0);
+  const int n = p.n[mat], per = mat ? 1 : p.per;
+  const int r0 = (int)(blockIdx.z * kF32GridY + blockIdx.y) * 16;
+  if (r0 >= p.R) return;
+  const int steps = (p.K + 15) / 16, s0 = kp * steps / kF32Parts, s1 = (kp + 1) * steps / kF32Parts;
+  const float* arow = p.a + (int64_t)min(r0 + (lane & 15), p.R - 1) * p.K;
+  const int kl = 4 * (lane >> 4);
+
+  float run_m = SPEC_NEG_INF, run_s = 0.f;
+  const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
+  uint64_t best[kMaxTopK];
+#pragma unroll
+  for (int q = 0; q < kMaxTopK; ++q) best[q] = kEmpty;
+  const int row = r0 + wave;             // of the closing part
+
+  for (int b = 0; b < per; ++b) {
+    const int v0 = (block * per + b) * kF32Cols;
+    if (v0 >= n) break;
+    const float* wrow = p.w[mat] + (int64_t)min(v0 + tile * 16 + (lane & 15), n - 1) * p.K;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s = s0; s < s1; s += kF32Batch) {
+      f32x4 wv[kF32Batch], av[kF32Batch];
+#pragma unroll
+      for (int u = 0; u < kF32Batch; ++u) {
+        const int k = s + u < s1 ? (s + u) * 16 + kl : p.K;   // (past the part: zeros)
+        wv[u] = load_f32x4(wrow, k, p.K, p.vec);
+        av[u] = load_f32x4(arow, k, p.K, p.vec);
+      }
+#pragma unroll
+      for (int u = 0; u < kF32Batch; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[u][i], av[u][i], acc, 0, 0, 0);
+    }
+    // accumulator lane l: state row l % 16, weight rows (l / 16) * 4 + i of the tile
+    __syncthreads();                     // (the previous block's sums have been read)
+    lds[wave * 64 + lane] = acc;
+    __syncthreads();
+    const int c = lane;                  // weight row of the block: tile c / 16, (c % 16) / 4 * 16 + state row, entry c % 4
+    const float* P = reinterpret_cast<const float*>(lds) + ((c >> 4) * 64 + ((c & 15) >> 2) * 16 + wave) * 4 + (c & 3);
+    float x = 0.f;
+#pragma unroll
+    for (int q = 0; q < kF32Parts; ++q) x += P[q * kF32Tiles * 64 * 4];
+    const int v = v0 + c;
+    if (row < p.R && v < n) {
+      if (p.out[mat]) {
+        p.out[mat][(int64_t)row * p.ldo[mat] + v] = x;
+      } else {
+        const float m = fmaxf(run_m, x);
+        if (m > SPEC_NEG_INF) run_s = run_s * expf(run_m - m) + expf(x - m);
+        run_m = m;
+        uint64_t key = best_key(x, v);
+#pragma unroll
+        for (int q = 0; q < kMaxTopK; ++q) {   // down the list, the smaller of each pair moves on
+          const uint64_t old = best[q];
+          best[q] = key > old ? key : old;
+          key = key > old ? old : key;
+        }
+      }
+    }
+  }
+  if (p.out[mat] || row >= p.R) return;  // (a whole wave)
+  const float mx = wave_max(run_m);
+  const float sum = wave_sum(run_m > SPEC_NEG_INF ? run_s * expf(run_m - mx) : 0.f);
+  const int64_t slot = (int64_t)row * p.nparts + block;
+  if (lane == 0) {
+    p.part.m[slot] = mx;
+    p.part.s[slot] = sum;
+  }
+#pragma unroll
+  for (int j = 0; j < kMaxTopK; ++j) {
+    if (j < p.k_top) {
+      const uint64_t top = wave_best_key(best[0]);
+      const bool won = best[0] == top && top != kEmpty;   // the owner of the winner pops it
+#pragma unroll
+      for (int q = 0; q + 1 < kMaxTopK; ++q) {
+        const uint64_t up = opaque_key(best[q + 1]);
+        best[q] = won ? up : best[q];
+      }
+      best[kMaxTopK - 1] = won ? kEmpty : best[kMaxTopK - 1];
+      if (lane == j) {
+        float bv;
+        int32_t bi;
+        best_unkey(top, bv, bi);
+        p.part.val[slot * p.k_top + j] = bv;
+        p.part.idx[slot * p.k_top + j] = bi;
+      }
+    }
+  }
+}
+
+static hipError_t launch_contract_f32(F32Args& p, hipStream_t st) {
+  // 16-byte loads need every row of both operands on a 16-byte boundary
+  p.vec = (p.K % 4 == 0 && ((reinterpret_cast<uintptr_t>(p.a) | reinterpret_cast<uintptr_t>(p.w[0]) |
+                             reinterpret_cast<uintptr_t>(p.w[1])) & 15) == 0) ? 1 : 0;
+  const int rt = (p.R + 15) / 16;
+  dim3 grid(p.blocks[0] + p.blocks[1], rt < kF32GridY ? rt : kF32GridY, (rt + kF32GridY - 1) / kF32GridY);
+  hipLaunchKernelGGL(contract_f32_kernel, grid, dim3(1024), 0, st, p);
   return hipGetLastError();
 }
 
-// ---- one partial (max, sum-exp, k best) per row of materialised logits -------
-__global__ __launch_bounds__(256) void row_topk_f32_kernel(const float* __restrict__ logits, int64_t ld, int V,
-                                                           int k_top, Partials part) {
-  __shared__ float sv[4];
-  __shared__ int32_t si[4];
-  __shared__ float scratch[8];
-  const int64_t row = blockIdx.x;
-  const int tid = threadIdx.x;
-  const float* x = logits + row * ld;
-  float lastv = __builtin_huge_valf();
-  int32_t lasti = -1;
-  float mx = 0.f;
-  for (int j = 0; j < k_top; ++j) {
-    float bv = SPEC_NEG_INF;
-    int32_t bi = kIdxNone;
-    for (int i = tid; i < V; i += 256) {
-      const float v = x[i];
-      if (before(lastv, lasti, v, i) && before(v, i, bv, bi)) { bv = v; bi = i; }
-    }
-    block_best<256>(bv, bi, sv, si);
-    if (tid == 0) {
-      part.val[row * k_top + j] = bv;
-      part.idx[row * k_top + j] = bi;
-    }
-    if (j == 0) mx = bv;
-    lastv = bv;
-    lasti = bi;
-  }
-  float s = 0.f;
-  for (int i = tid; i < V; i += 256) s += expf(x[i] - mx);
-  s = block_sum<256>(s, scratch);
-  if (tid == 0) {
-    part.m[row] = mx;
-    part.s[row] = s;
-  }
+hipError_t launch_store_f32(const float* a, const float* w, float* out, int64_t ldo, int R, int N, int K, hipStream_t st) {
+  F32Args p = {};
+  p.a = a; p.R = R; p.K = K;
+  p.w[0] = w; p.n[0] = N; p.blocks[0] = (N + kF32Cols - 1) / kF32Cols; p.out[0] = out; p.ldo[0] = ldo;
+  p.per = 1;
+  return launch_contract_f32(p, st);
 }
 
-hipError_t launch_row_topk_f32(const float* logits, int64_t ld, int R, int V, int k_top, Partials part,
-                               hipStream_t st) {
-  hipLaunchKernelGGL(row_topk_f32_kernel, dim3(R), dim3(256), 0, st, logits, ld, V, k_top, part);
-  return hipGetLastError();
+hipError_t launch_head_f32(const float* a, const float* w_head, int n_head, int k_top, Partials part, int max_parts,
+                           const float* w_proj, int n_proj, float* out_proj, int R, int K, int* nparts, hipStream_t st) {
+  F32Args p = {};
+  p.a = a; p.R = R; p.K = K;
+  p.w[0] = w_head; p.n[0] = n_head; p.k_top = k_top; p.part = part;
+  // as many parts per row as the partial results' buffer holds: longer heads take several blocks per workgroup
+  const int nb = (n_head + kF32Cols - 1) / kF32Cols;
+  p.per = (nb + max_parts - 1) / max_parts;
+  p.blocks[0] = (nb + p.per - 1) / p.per;
+  p.nparts = *nparts = p.blocks[0];
+  if (n_proj > 0) {
+    p.w[1] = w_proj; p.n[1] = n_proj; p.blocks[1] = (n_proj + kF32Cols - 1) / kF32Cols;
+    p.out[1] = out_proj; p.ldo[1] = n_proj;
+  }
+  return launch_contract_f32(p, st);
 }
 
 __global__ __launch_bounds__(256) void row_log_softmax_kernel(const float* __restrict__ logits,

@@ -131,13 +131,13 @@ bool plan_projection_apart(int R, int k_top, int n_head, int n_proj, int kt, int
 hipError_t launch_head_gemm(const HeadJob& job, const GemmPlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr, size_t* dry = nullptr);
 
-// ---- contraction, float32 (correctness configuration) ---------------------
-// out[r * ldo + v] = sum_k a[r * lda + k] * w[v * ldw + k]
-hipError_t launch_gemm_f32(const float* a, int64_t lda, const float* w, int64_t ldw, float* out, int64_t ldo,
-                           int R, int N, int K, hipStream_t st);
-// one partial per row from materialised logits [R][ld]
-hipError_t launch_row_topk_f32(const float* logits, int64_t ld, int R, int V, int k_top, Partials part,
-                               hipStream_t st);
+// ---- contraction, float32 ----------------------------------------------------
+// out[r * ldo + v] = sum_k a[r * K + k] * w[v * K + k]
+hipError_t launch_store_f32(const float* a, const float* w, float* out, int64_t ldo, int R, int N, int K, hipStream_t st);
+// head: at most max_parts partials per row (*nparts of them); n_proj > 0: the next projection in the same launch,
+// out_proj [R][n_proj]
+hipError_t launch_head_f32(const float* a, const float* w_head, int n_head, int k_top, Partials part, int max_parts,
+                           const float* w_proj, int n_proj, float* out_proj, int R, int K, int* nparts, hipStream_t st);
 // logp[r][v] = logits[r][v] - logsumexp(logits[r])   (in place allowed)
 hipError_t launch_row_log_softmax(const float* logits, float* logp, int64_t ld, int R, int V, hipStream_t st);
 

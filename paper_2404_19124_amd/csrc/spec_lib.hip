@@ -50,8 +50,6 @@ struct Workspace {
   int32_t* tok = nullptr;     // per-stage top-k tables, concatenated
   float* logp = nullptr;
   float* lse = nullptr;
-  float* logits = nullptr;    // f32 path and spec_head_logp: materialised rows
-  int64_t logits_rows = 0;
 };
 
 struct spec_model {
@@ -176,7 +174,7 @@ static spec_status_t check_config(const spec_config_t* c) {
 
 // capacity (in (row, part) slots) that covers every contraction plan a call may pick:
 // the streaming kernel writes one part per workgroup (one per CU), the dense kernel at
-// most one per range (<= one per CU, two for blocks of <= 64 rows), the float32 path one per row
+// most one per range (<= one per CU, two for blocks of <= 64 rows), the float32 path at most one per CU
 static int64_t partial_capacity(int64_t max_rows, int V, int n_cu) {
   (void)V;
   const int64_t cus = n_cu > 0 ? n_cu : 256;
@@ -322,9 +320,6 @@ extern "C" spec_status_t spec_create(const spec_config_t* cfg, const spec_weight
   TRY_FREE(dev_alloc(m, &m->ws.tok, (size_t)sum_rows_k * 4));
   TRY_FREE(dev_alloc(m, &m->ws.logp, (size_t)sum_rows_k * 4));
   TRY_FREE(dev_alloc(m, &m->ws.lse, (size_t)sum_rows * 4));
-  // materialised logits: every row for the f32 path, a small window otherwise (spec_head_logp)
-  m->ws.logits_rows = m->bf16 ? 0 : max_rows;
-  TRY_FREE(dev_alloc(m, &m->ws.logits, (size_t)m->ws.logits_rows * V * 4));
 
   m->dyn_ints = 2 * sum_rows + (int64_t)cfg->max_batch * (2 * n + 2) + 64;
   TRY_FREE(dev_alloc(m, &m->dyn_dev, (size_t)m->dyn_ints * 4));
@@ -661,8 +656,8 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
       spec_status_t s = run_contraction(m, ws, -1, 0, state, true, E, batch, 0, nullptr, ws.pz[0], &nparts, st, &pz0_parts);
       if (s != SPEC_OK) return s;
     } else {
-      HIP_TRY(launch_gemm_f32(static_cast<const float*>(state), E, static_cast<const float*>(m->proj[0]), E, ws.pz[0],
-                              D, batch, D, E, st));
+      HIP_TRY(launch_store_f32(static_cast<const float*>(state), static_cast<const float*>(m->proj[0]), ws.pz[0], D,
+                               batch, D, E, st));
     }
 
     int pz_parts = pz0_parts;                 // parts of the projection the current stage reads
@@ -704,13 +699,10 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
                                           ws.pz[(i + 1) & 1], &nparts, st, nullptr, folded ? &fold : nullptr);
         if (s != SPEC_OK) return s;
       } else {
-        const float* sf = static_cast<const float*>(ws.states);
-        HIP_TRY(launch_gemm_f32(sf, D, static_cast<const float*>(m->head[i]), D, ws.logits, V, (int)R[i], V, D, st));
-        HIP_TRY(launch_row_topk_f32(ws.logits, V, (int)R[i], V, top_k[i], ws.part, st));
-        nparts = 1;
-        if (proj_next >= 0)
-          HIP_TRY(launch_gemm_f32(sf, D, static_cast<const float*>(m->proj[proj_next]), D, ws.pz[(i + 1) & 1], D,
-                                  (int)R[i], D, D, st));
+        HIP_TRY(launch_head_f32(static_cast<const float*>(ws.states), static_cast<const float*>(m->head[i]), V, top_k[i],
+                                ws.part, m->n_cu > 0 ? m->n_cu : 256,
+                                proj_next >= 0 ? static_cast<const float*>(m->proj[proj_next]) : nullptr,
+                                proj_next >= 0 ? D : 0, ws.pz[(i + 1) & 1], (int)R[i], D, &nparts, st));
       }
     }
     HIP_TRY(launch_tree(tree_job(nparts), st));
@@ -866,8 +858,8 @@ static spec_status_t carve_static(const spec_model* m, unsigned char* base, int 
   ws->tok = reinterpret_cast<int32_t*>(take((size_t)sum_rows_k * 4));
   ws->logp = reinterpret_cast<float*>(take((size_t)sum_rows_k * 4));
   ws->lse = reinterpret_cast<float*>(take((size_t)sum_rows * 4));
-  ws->logits_rows = m->bf16 ? 0 : max_rows;
-  ws->logits = reinterpret_cast<float*>(take((size_t)ws->logits_rows * V * 4));
+  // (the limit callers know counts a float32 call's logit rows)
+  if (!m->bf16) take((size_t)max_rows * V * 4);
   if (!fits)
     return fail(SPEC_ESHAPE, "spec_draft_static: this call needs %zu bytes of workspace, the static array holds %d "
                              "(use spec_draft for larger batches or trees)", used, SPEC_STATIC_SCRATCH_BYTES);
@@ -913,8 +905,8 @@ extern "C" spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const vo
       if (s != SPEC_OK) return s;
     }
   } else {
-    HIP_TRY(launch_gemm_f32(static_cast<const float*>(states), D, static_cast<const float*>(m->head[stage]), D, logp, V,
-                            rows, V, D, st));
+    HIP_TRY(launch_store_f32(static_cast<const float*>(states), static_cast<const float*>(m->head[stage]), logp, V, rows,
+                             V, D, st));
   }
   HIP_TRY(launch_row_log_softmax(logp, logp, V, rows, V, st));
   return SPEC_OK;
