@@ -150,8 +150,8 @@ spec_status_t spec_draft(spec_model_t* m, const void* state, const int32_t* last
  *   dbg        as for spec_draft, with the rows of a stage = those of the active sequences in batch order and
  *              every table of stage i as wide as the widest top_k_seq[.][i] of the call
  * The host arrays are consumed before the call returns.  Unlike spec_draft this call copies a few KB
- * of row maps from host memory to the device on hip_stream (it enqueues kernels and two copies; it may
- * wait for the copy of the call four calls earlier). */
+ * of row maps from host memory to the device on hip_stream (a kernel reads them from pinned memory; it may
+ * wait for that kernel of the call four calls earlier). */
 spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, const int32_t* last_tok, int32_t batch,
                                  const int32_t* top_k_seq, const int32_t* B_seq, int32_t B_pad, int32_t* cand_tokens,
                                  float* cand_scores, int32_t* cand_leaf, int32_t* n_cand, const spec_debug_t* dbg,

@@ -43,6 +43,23 @@ hipError_t launch_stage(const StageJob& job, hipStream_t st) {
   return job.bf16 ? launch_stage_t<true>(job, st) : launch_stage_t<false>(job, st);
 }
 
+// Row maps of a call with per-sequence trees: a few KB straight from pinned host memory, every word requested at
+// once (one trip over PCIe), and the candidate counts to the caller's array.  Two copies by the runtime in its place
+// delayed the draft's first kernel by 15 us.
+__global__ __launch_bounds__(256) void fetch_maps_kernel(const int32_t* __restrict__ maps, int32_t* __restrict__ dev,
+                                                         int n, int32_t* __restrict__ n_cand, int batch) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n + batch) return;
+  const int32_t v = maps[i];
+  if (i < n) dev[i] = v;
+  else n_cand[i - n] = v;
+}
+
+hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, hipStream_t st) {
+  hipLaunchKernelGGL(fetch_maps_kernel, dim3((n + batch + 255) / 256), dim3(256), 0, st, maps, dev, n, n_cand, batch);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Tree kernel (Sec. 3.1, 4.1): merge the last head's partial results, score
 // every leaf by the sum of its tokens' log-probabilities (added in stage order),

@@ -176,6 +176,10 @@ struct StageJob {
 };
 hipError_t launch_stage(const StageJob& job, hipStream_t st);
 
+// ---- per-sequence trees: n words of `maps` (pinned host memory, device address) to dev, the `batch` words behind them
+// to n_cand
+hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, hipStream_t st);
+
 // ---- tree: merge of the last head + leaf scores + top-B ----------------------
 struct TreeJob {
   int batch, n, B, L;
