@@ -10,7 +10,7 @@ namespace specdraft {
 // NCH = 8-element chunks per thread held in registers (D <= NCH * NT * 8).
 template <bool BF16, int NCH, int NT>
 __global__ __launch_bounds__(NT) void stage_kernel(StageJob j) {
-  __shared__ float lds[32 + (NT / 256) * kMergeLds];
+  __shared__ __align__(16) float lds[32 + (NT / 256) * kMergeLds];
   int r = blockIdx.x;
   if (j.xcd_rows) {
     // Workgroup ids go round-robin over the 8 XCDs, and a row's state is stored as one 16-byte slot in
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT) void tree_kernel(TreeJob j) {
   __shared__ __align__(16) uint64_t sk[kMaxLeaves];
   __shared__ int s_k[kMaxStages], s_kw[kMaxStages];
   __shared__ int64_t s_off[kMaxStages], s_rbase[kMaxStages];
-  __shared__ float merge_lds[kMergeLds * (NT / 256)];
+  __shared__ __align__(16) float merge_lds[kMergeLds * (NT / 256)];
   __shared__ int32_t c_tok[kMaxLeaves];
   __shared__ float c_logp[kMaxLeaves];
   TreeArgs a;

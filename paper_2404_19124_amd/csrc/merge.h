@@ -30,11 +30,13 @@ __device__ __forceinline__ void list_insert(float (&tv)[K], int32_t (&ti)[K], fl
 // vocabulary index, so (value, index) is a strict total order.
 //
 // Latency matters here (this sits on the serial chain between two heads at
-// batch 1): every lane first issues the loads of four parts at once, then folds
+// batch 1): every lane first issues the loads of UN parts at once, then folds
 // them into a sorted register list; the k results are popped with wave-wide
-// reductions, no memory traffic in between.
-template <int K>
-__device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t row, int nparts, int k,
+// reductions, no memory traffic in between.  UN is as large as the parts need: with the
+// 17 .. 128 parts of the dense kernel four per lane are mostly masked work (tree kernel, 72 rows of 17 parts
+// per sequence: 23.8 -> 19.1 us; 24 rows of 64 parts: 16.5 -> 13.7 us).
+template <int K, int UN>
+__device__ __forceinline__ void wave_merge_partials_un(const Partials& p, int64_t row, int nparts, int k,
                                                     float (&out_val)[kMaxTopK], int32_t (&out_idx)[kMaxTopK],
                                                     float& lse) {
   const int lane = opaque_tid() & 63;
@@ -50,7 +52,6 @@ __device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t
   for (int q = 0; q < K; ++q) tk[q] = kEmpty;
   float run_m = SPEC_NEG_INF, run_s = 0.f;
 
-  constexpr int UN = 4;
   for (int p0 = 0; p0 < nparts; p0 += 64 * UN) {
     float lm[UN], ls[UN], lv[UN][K];
     int32_t li[UN][K];
@@ -133,22 +134,36 @@ __device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t
   }
 }
 
+template <int K>
+__device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t row, int nparts, int k,
+                                                    float (&out_val)[kMaxTopK], int32_t (&out_idx)[kMaxTopK],
+                                                    float& lse) {
+  if (nparts <= 64) wave_merge_partials_un<K, 1>(p, row, nparts, k, out_val, out_idx, lse);
+  else if (nparts <= 128) wave_merge_partials_un<K, 2>(p, row, nparts, k, out_val, out_idx, lse);
+  else wave_merge_partials_un<K, 4>(p, row, nparts, k, out_val, out_idx, lse);
+}
+
 // The same merge done by a group of 256 consecutive threads for ONE row: with at most
 // 256 parts every thread holds exactly one part's (already sorted) list, so nothing has
 // to be inserted.  Two levels, ONE exchange: every wave reduces its 64 parts to its own
 // (max, sum-exp, k best) with wave-wide reductions only, the four waves' results go
-// through LDS behind a single barrier, and every thread merges the four sorted lists.
-// (A pop per round across the whole group - one barrier and one LDS exchange per result -
-// took 0.65 us per round on the batch-1 chain.)  A workgroup of 256 * n threads runs n such
+// through LDS behind a single barrier, and there every one of the 4 K candidates is given to
+// a lane that counts the candidates before it: its rank.  (A pop per round across the whole group
+// - one barrier and one LDS exchange per result - took 0.65 us per round on the batch-1 chain; the four
+// lists merged in registers by every thread, K shifts of 4 K keys each, made the stage kernel take 7.5 us
+// for 5 rows (256 parts, top-5), 21.7 for 960 rows and 34.4 for 2304, against 6.8, 19.5 and 27.1 now.)
+// A workgroup of 256 * n threads runs n such
 // groups side by side (each on its own row, or all on the same one): the function contains
 // workgroup barriers, so EVERY thread of the workgroup must call it, with the same k
-// and nparts; every thread receives its group's result.  `lds` is the group's own
-// scratch of kMergeLds words.
-constexpr int kMergeWave = 2 + 2 * kMaxTopK;   // words per wave: max, sum-exp, k values, k indices
+// and nparts.  Lane c < 4 K of every wave of the group receives candidate c (value, index, rank; the k
+// best have ranks 0 .. k - 1), the other lanes rank kNoRank; every thread receives lse.  `lds` is the
+// group's own scratch of kMergeLds words, 8-byte aligned.
+constexpr int kMergeWave = 2 + 2 * kMaxTopK;   // words per wave: max, sum-exp, k keys
 constexpr int kMergeLds = 4 * kMergeWave;
+constexpr int kNoRank = 1 << 20;
 template <int K>
 __device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_t row, int nparts, int k,
-                                                     float (&out_val)[kMaxTopK], int32_t (&out_idx)[kMaxTopK],
+                                                     float& out_val, int32_t& out_idx, int& rank,
                                                      float& lse, float* lds) {
   const int gt = opaque_tid() & 255, lane = gt & 63, w = gt >> 6;
   const float* pm = p.m + row * nparts;
@@ -219,10 +234,8 @@ __device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_
     mine[0] = wm;
     mine[1] = wsum;
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      mine[2 + j] = wv[j];
-      reinterpret_cast<int32_t*>(mine)[2 + kMaxTopK + j] = wi[j];
-    }
+    for (int j = 0; j < K; ++j)   // (empty entries are told apart, so that every candidate has its own rank)
+      reinterpret_cast<uint64_t*>(mine + 2)[j] = best_key(wv[j], wi[j] == kIdxNone ? kIdxNone - (w * kMaxTopK + j) : wi[j]);
   }
   __syncthreads();
   float m4[4], s4[4];
@@ -234,51 +247,29 @@ __device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_
   for (int q = 0; q < 4; ++q) sum += m4[q] > SPEC_NEG_INF ? s4[q] * __expf(m4[q] - mx) : 0.f;
   lse = mx + logf(sum);
 
-#pragma unroll
-  for (int j = 0; j < kMaxTopK; ++j) {
-    out_val[j] = SPEC_NEG_INF;
-    out_idx[j] = kIdxNone;
-  }
-  // four sorted lists, as 64-bit keys in registers (one batch of LDS reads): only their heads compete;
-  // the list whose head won moves up by one (keys are unique: every candidate has its own token)
-  uint64_t lk[4][K];
+  const int c = min(lane, 4 * K - 1);
+  const uint64_t key = reinterpret_cast<const uint64_t*>(lds + (c / K) * kMergeWave + 2)[c % K];
+  int before_me = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int t = 0; t < K; ++t)
-      lk[q][t] = best_key(lds[q * kMergeWave + 2 + t],
-                          reinterpret_cast<const int32_t*>(lds)[q * kMergeWave + 2 + kMaxTopK + t]);
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    if (j < k) {
-      uint64_t best = lk[0][0];
-#pragma unroll
-      for (int q = 1; q < 4; ++q) best = lk[q][0] > best ? lk[q][0] : best;
-      best_unkey(best, out_val[j], out_idx[j]);
-      if (j + 1 < k) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bool won = lk[q][0] == best;
-#pragma unroll
-          for (int t = 0; t + 1 < K; ++t) lk[q][t] = won ? lk[q][t + 1] : lk[q][t];
-          lk[q][K - 1] = won ? best_key(SPEC_NEG_INF, kIdxNone) : lk[q][K - 1];
-        }
-      }
-    }
-  }
+      before_me += reinterpret_cast<const uint64_t*>(lds + q * kMergeWave + 2)[t] > key ? 1 : 0;
+  best_unkey(key, out_val, out_idx);
+  rank = lane < 4 * K ? before_me : kNoRank;
 }
 
 __device__ __forceinline__ void group_merge_partials(const Partials& p, int64_t row, int nparts, int k,
-                                                     float (&out_val)[kMaxTopK], int32_t (&out_idx)[kMaxTopK],
+                                                     float& out_val, int32_t& out_idx, int& rank,
                                                      float& lse, float* lds) {
   switch (k) {
-    case 1: group_merge_partials_k<1>(p, row, nparts, k, out_val, out_idx, lse, lds); break;
-    case 2: group_merge_partials_k<2>(p, row, nparts, k, out_val, out_idx, lse, lds); break;
-    case 3: group_merge_partials_k<3>(p, row, nparts, k, out_val, out_idx, lse, lds); break;
-    case 4: group_merge_partials_k<4>(p, row, nparts, k, out_val, out_idx, lse, lds); break;
+    case 1: group_merge_partials_k<1>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
+    case 2: group_merge_partials_k<2>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
+    case 3: group_merge_partials_k<3>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
+    case 4: group_merge_partials_k<4>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
     case 5:
-    case 6: group_merge_partials_k<6>(p, row, nparts, k, out_val, out_idx, lse, lds); break;
-    default: group_merge_partials_k<8>(p, row, nparts, k, out_val, out_idx, lse, lds); break;
+    case 6: group_merge_partials_k<6>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
+    default: group_merge_partials_k<8>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
   }
 }
 

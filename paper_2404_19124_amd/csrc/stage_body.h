@@ -60,24 +60,17 @@ __device__ __forceinline__ void stage_row(const StageJob& j, int r, float* lds) 
   if (j.stage == 0) {
     tok = j.last_tok[parent];   // (uniform tree: parent == r)
   } else {
-    float v[kMaxTopK];
-    int32_t ix[kMaxTopK];
-    float lse;
+    float v, lse;
+    int32_t ix;
+    int at;
     // every 256-thread group merges the same parent row (one group would do; the
     // barriers inside need all of them anyway)
-    group_merge_partials(j.part, parent, j.nparts, j.k_prev, v, ix, lse, merge_lds);
-    tok = ix[0];
-#pragma unroll
-    for (int q = 1; q < kMaxTopK; ++q)
-      if (q == rank) tok = ix[q];
-    if (rank == 0 && tid < 64) {
-#pragma unroll
-      for (int q = 0; q < kMaxTopK; ++q)
-        if (lane == q && q < j.k_prev) {
-          j.prev_tok[(int64_t)parent * j.k_prev + q] = ix[q];
-          j.prev_logp[(int64_t)parent * j.k_prev + q] = v[q] - lse;
-        }
-      if (lane == 0) j.prev_lse[parent] = lse;
+    group_merge_partials(j.part, parent, j.nparts, j.k_prev, v, ix, at, lse, merge_lds);
+    tok = __builtin_amdgcn_readlane(ix, __ffsll((unsigned long long)__ballot(at == rank)) - 1);
+    if (rank == 0 && tid < 64 && at < j.k_prev) {
+      j.prev_tok[(int64_t)parent * j.k_prev + at] = ix;
+      j.prev_logp[(int64_t)parent * j.k_prev + at] = v - lse;
+      if (at == 0) j.prev_lse[parent] = lse;
     }
   }
   tok = min(max(tok, 0), j.V - 1);  // a wild token from the caller must not leave the table
@@ -275,20 +268,18 @@ __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s
       const int rl = r0 + grp;
       const bool live = rl < rows_last;
       const int64_t row = j.rbase_last + (live ? rl : rows_last - 1);
-      float v[kMaxTopK];
-      int32_t ix[kMaxTopK];
-      float lse;
-      group_merge_partials(j.part, row, j.nparts, kw, v, ix, lse, merge_lds + grp * kMergeLds);
-#pragma unroll
-      for (int t = 0; t < kMaxTopK; ++t)
-        if (live && gl == t && t < kw) {
-          j.tok[j.off_last + row * kw + t] = ix[t];
-          j.logp[j.off_last + row * kw + t] = v[t] - lse;
-          if (early) {
-            c_tok[rl * kw + t] = ix[t];
-            c_logp[rl * kw + t] = v[t] - lse;
-          }
+      float v, lse;
+      int32_t ix;
+      int at;
+      group_merge_partials(j.part, row, j.nparts, kw, v, ix, at, lse, merge_lds + grp * kMergeLds);
+      if (live && gl < 64 && at < kw) {
+        j.tok[j.off_last + row * kw + at] = ix;
+        j.logp[j.off_last + row * kw + at] = v - lse;
+        if (early) {
+          c_tok[rl * kw + at] = ix;
+          c_logp[rl * kw + at] = v - lse;
         }
+      }
       if (live && gl == 0) j.lse[j.row_off_last + row] = lse;
     }
   }
