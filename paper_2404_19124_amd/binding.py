@@ -136,14 +136,15 @@ def _dtype_code(name: str) -> int:
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return t.data_ptr() if t is not None else None
 
 
 _TORCH_DTYPE = {SPEC_F32: torch.float32, SPEC_BF16: torch.bfloat16}
+_DTYPE_CODE = {torch.float32: SPEC_F32, torch.bfloat16: SPEC_BF16}
 _CHECK_DEVICE = True   # the CPU-only tests of _require switch the device check off to reach the others
 
 
@@ -151,6 +152,10 @@ def _require(t, name: str, dtype: torch.dtype, shape: Optional[Sequence[int]] = 
     """Host-side check of a tensor argument before its address crosses the boundary: the library reads
     raw pointers, so a wrong element type, a view with strides or a short buffer would be read (or
     written) out of bounds on the device.  Raises ValueError."""
+    # (the usual case in one go: a verify checks a dozen tensors, and its kernels take 9 us)
+    if (type(t) is torch.Tensor and t.dtype is dtype and (shape is None or t.shape == shape) and t.is_contiguous()
+            and (t.is_cuda or not _CHECK_DEVICE)):
+        return
     if t is None:
         if optional:
             return
@@ -358,8 +363,8 @@ def spec_verify_dynamic(base_logits: torch.Tensor, cand_tokens: torch.Tensor, n_
     """Enqueues one verify in which sequence q has n_cand[q] candidates (0 = speculation off)."""
     if not isinstance(base_logits, torch.Tensor) or base_logits.dim() != 4:
         raise ValueError("base_logits must be a [batch, B, n_predict + 1, vocab] tensor")
-    b, B, n1, V = (int(x) for x in base_logits.shape)
-    code = {torch.float32: SPEC_F32, torch.bfloat16: SPEC_BF16}.get(base_logits.dtype, -1)
+    b, B, n1, V = base_logits.shape
+    code = _DTYPE_CODE.get(base_logits.dtype, -1)
     if code < 0:
         raise ValueError("base_logits must be float32 or bfloat16, got %s" % base_logits.dtype)
     _require(base_logits, "base_logits", base_logits.dtype)
@@ -382,8 +387,8 @@ def spec_verify(base_logits: torch.Tensor, cand_tokens: torch.Tensor, greedy: to
     """Enqueues one verify.  base_logits [batch, B, n+1, V] float32 or bfloat16."""
     if not isinstance(base_logits, torch.Tensor) or base_logits.dim() != 4:
         raise ValueError("base_logits must be a [batch, B, n_predict + 1, vocab] tensor")
-    b, B, n1, V = (int(x) for x in base_logits.shape)
-    code = {torch.float32: SPEC_F32, torch.bfloat16: SPEC_BF16}.get(base_logits.dtype, -1)
+    b, B, n1, V = base_logits.shape
+    code = _DTYPE_CODE.get(base_logits.dtype, -1)
     if code < 0:
         raise ValueError("base_logits must be float32 or bfloat16, got %s" % base_logits.dtype)
     _require(base_logits, "base_logits", base_logits.dtype)
@@ -416,7 +421,7 @@ def spec_tree_metadata(cand_tokens: torch.Tensor, node_tok: torch.Tensor, node_p
                        mask: Optional[torch.Tensor] = None, stream=None) -> None:
     if not isinstance(cand_tokens, torch.Tensor) or cand_tokens.dim() != 3:
         raise ValueError("cand_tokens must be a [batch, B, n_predict] tensor")
-    b, Bc, n = (int(x) for x in cand_tokens.shape)
+    b, Bc, n = cand_tokens.shape
     M = Bc * n
     _require(cand_tokens, "cand_tokens", torch.int32)
     _require(node_tok, "node_tok", torch.int32, (b, M))
@@ -434,8 +439,8 @@ def spec_advance(hidden: torch.Tensor, best_cand: torch.Tensor, accept_len: torc
                  next_state: torch.Tensor, next_tok: torch.Tensor, stream=None) -> None:
     if not isinstance(hidden, torch.Tensor) or hidden.dim() != 4:
         raise ValueError("hidden must be a [batch, B, n_predict + 1, emb_dim] tensor")
-    b, Bc, n1, E = (int(x) for x in hidden.shape)
-    dtype = {torch.float32: SPEC_F32, torch.bfloat16: SPEC_BF16}.get(hidden.dtype, -1)
+    b, Bc, n1, E = hidden.shape
+    dtype = _DTYPE_CODE.get(hidden.dtype, -1)
     if dtype < 0:
         raise ValueError("hidden must be float32 or bfloat16, got %s" % hidden.dtype)
     _require(hidden, "hidden", hidden.dtype)
