@@ -524,6 +524,33 @@ __device__ __forceinline__ void interleave_half() {
   }
 }
 
+// ---- top-k lists of the wide kernel ----
+// An entry is ONE float64 number: high word = the logit's bits, low word = a word that makes equal logits compare by
+// vocabulary index, smaller first (~index; for negative logits, whose magnitudes order the other way, index).  A
+// float32 pattern in the high word of a float64 keeps its order (sign and magnitude; only NaN patterns reach the
+// float64 NaNs, and a NaN logit counts as -inf here), and v_max_f64 / v_min_f64 run at the float32 rate, so the
+// insertion into a sorted list of KT is 2 KT - 1 instructions and no compare.  (Compares and selects on value and
+// index apart took 5 KT: KT = 2, 3, 6: 3, 5, 11 instructions per logit instead of 8, 13, 28.  Launches against 32000
+// rows x 4096: 75 rows, top-2, 55.4 -> 50.8 us; 64 rows, top-5, with a projection, 62.1 -> 58.8; 320 rows, top-3,
+// 96.5 -> 92.2; 384 rows, top-3, 120.5 -> 116.4; 960 rows, top-2, 1 to 2 %.)
+__device__ __forceinline__ double key_max(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double key_min(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double logit_key(float x, int32_t not_index) {
+  float v;
+  asm("v_max_f32 %0, 0xff800000, %1" : "=v"(v) : "v"(x));   // NaN -> -inf
+  return __hiloint2double(__float_as_int(v), not_index ^ (__float_as_int(v) >> 31));
+}
+__device__ __forceinline__ float logit_of(double key) { return __int_as_float(__double2hiint(key)); }
+__device__ __forceinline__ int32_t index_of(double key) { return ~(__double2loint(key) ^ (__double2hiint(key) >> 31)); }
+
 // Wide blocks: the same kernel built on v_mfma_f32_32x32x16_bf16.  One wave per SIMD can
 // keep the matrix cores busy with the 32x32 instruction (measured: 2.1 PFLOP/s in a bare
 // loop) but not with the 16x16 one (1.46 PFLOP/s: it needs a second wave per SIMD, and
@@ -580,10 +607,11 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
 
   // weight fragment pointers of this wave for a given tile of the list
   // VT (variable tile): a tile holds p.ts <= 4 * NI 16-row weight tiles instead of 4 * NI; wave w
-  // owns tiles [w * NI, (w + 1) * NI) of it.  A 32-row block past the tile's end is masked in the
-  // epilogue; its loads repeat the
+  // owns tiles [w * NI, (w + 1) * NI) of it.  A 32-row block past the tile's end is left out of the
+  // epilogue, a 16-row half masked there; their loads repeat the
   // tile's last 16 rows (lines another wave of the workgroup requests at the same time: no
-  // extra HBM traffic, and short tiles are only planned where HBM is the bound).
+  // extra HBM traffic, and short tiles are only planned where HBM is the bound).  (Tiles shared out evenly over the
+  // waves shorten the epilogue and lengthen the K loop: 144 rows, 96 state rows: 66.2 -> 69.9 us.)
   const u32x4* wptr[NB];
   auto set_tile = [&](int t, const u32x4* (&wp)[NB], int (&ntv)[NB], int& mat, int& tend) {
     mat = t >= p.n_tiles[0] ? 1 : 0;
@@ -624,14 +652,14 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
   };
 
   // running softmax / top-k state of this lane, per state row (mi, col)
-  float run_m[MB], run_s[MB], lv[MB][KT];
-  int32_t li[MB][KT];
+  float run_m[MB], run_s[MB];
+  double lk[MB][KT];
 #pragma unroll
   for (int mi = 0; mi < MB; ++mi) {
     run_m[mi] = SPEC_NEG_INF;
     run_s[mi] = 0.f;
 #pragma unroll
-    for (int q = 0; q < KT; ++q) { lv[mi][q] = SPEC_NEG_INF; li[mi][q] = kIdxNone; }
+    for (int q = 0; q < KT; ++q) lk[mi][q] = logit_key(SPEC_NEG_INF, ~kIdxNone);
   }
   bool any_head = false;
 
@@ -775,55 +803,57 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
     // (a wave whose rows all lie past the tile's end has nothing to add)
     if (cur_mat == 0 && p.mode0 == 0 && (!VT || cur_nt[0] < cur_end)) {
       // only a block that reaches past the end of the tile or of the vocabulary needs the validity mask
-      const bool edge = (cur_nt[NB - 1] + 2) * 16 > n_valid;
-      constexpr float kLog2e = 1.4426950408889634f;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        // this lane's 16*NB logits of state row (mb, c32), in increasing vocabulary order
-        float x[NB * 16];
-        float tmax = SPEC_NEG_INF;
+      if ((cur_nt[NB - 1] + 2) * 16 > n_valid) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int v = cur_nt[nb] * 16 + half * 4 + 8 * (e >> 2) + (e & 3);
-            const float xv = (!edge || v < n_valid) ? acc[mb][nb][e] : SPEC_NEG_INF;
-            x[nb * 16 + e] = xv;
-            tmax = fmaxf(tmax, xv);
+            const bool ok = cur_nt[nb] * 16 + half * 4 + 8 * (e >> 2) + (e & 3) < n_valid;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc[mb][nb][e] = ok ? acc[mb][nb][e] : SPEC_NEG_INF;
           }
-        const float new_m = fmaxf(run_m[mb], tmax);
+      }
+      // The lane's 16*NB logits of every state row (mb, c32) into the row's list.  Every one of them, without a branch:
+      // a range is only a few tiles long, so the lists never warm up, and some lane of the wave takes a new entry for
+      // almost every element.  The MB lists are independent chains: one entry each in turn.
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        if (!VT || nb == 0 || cur_nt[nb] < cur_end) {
+          const int32_t base = ~(cur_nt[nb] * 16 + half * 4);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int32_t not_index = base - (8 * (e >> 2) + (e & 3));
+            double x[MB];
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) x[mb] = logit_key(acc[mb][nb][e], not_index);
+#pragma unroll
+            for (int q = 0; q + 1 < KT; ++q)   // down the list, the smaller of each pair moves on
+#pragma unroll
+              for (int mb = 0; mb < MB; ++mb) {
+                const double old = lk[mb][q];
+                lk[mb][q] = key_max(old, x[mb]);
+                x[mb] = key_min(old, x[mb]);
+              }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) lk[mb][KT - 1] = key_max(lk[mb][KT - 1], x[mb]);
+          }
+        }
+      constexpr float kLog2e = 1.4426950408889634f;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const float new_m = logit_of(lk[mb][0]);   // (the first entry is the largest logit so far)
         if (new_m > SPEC_NEG_INF) {
           // exp(x - m) as exp2(x * log2(e) - m * log2(e)): one fused multiply-add per logit
           const float ml = new_m * kLog2e;
           float s = run_s[mb] * __builtin_amdgcn_exp2f((run_m[mb] - new_m) * kLog2e);
 #pragma unroll
-          for (int e = 0; e < NB * 16; ++e) s += __builtin_amdgcn_exp2f(__builtin_fmaf(x[e], kLog2e, -ml));
+          for (int nb = 0; nb < NB; ++nb)
+            if (!VT || nb == 0 || cur_nt[nb] < cur_end) {
+#pragma unroll
+              for (int e = 0; e < 16; ++e) s += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[mb][nb][e], kLog2e, -ml));
+            }
           run_s[mb] = s;
           run_m[mb] = new_m;
-        }
-        if (tmax > lv[mb][KT - 1]) {
-          // Branch-free insertion of every logit.  A range is only a few tiles long, so
-          // the lists never warm up: some lane of the wave takes a new entry for almost every
-          // element, and an insertion guarded by a per-element branch makes the whole wave
-          // walk it anyway (measured: 9k-21k cycles per tile against 3k-7k this way).
-          // Strict compares: a later vocabulary entry of equal value loses the tie.
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-              const float xv = x[nb * 16 + e];
-              const int32_t xi = cur_nt[nb] * 16 + half * 4 + 8 * (e >> 2) + (e & 3);
-              bool c[KT];
-#pragma unroll
-              for (int q = 0; q < KT; ++q) c[q] = xv > lv[mb][q];
-#pragma unroll
-              for (int q = KT - 1; q >= 1; --q) {
-                lv[mb][q] = c[q - 1] ? lv[mb][q - 1] : (c[q] ? xv : lv[mb][q]);
-                li[mb][q] = c[q - 1] ? li[mb][q - 1] : (c[q] ? xi : li[mb][q]);
-              }
-              lv[mb][0] = c[0] ? xv : lv[mb][0];
-              li[mb][0] = c[0] ? xi : li[mb][0];
-            }
         }
       }
     }
@@ -849,7 +879,7 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
     for (int mb = 0; mb < MB; ++mb) {
       const int rl = mb * 32 + c32;
 #pragma unroll
-      for (int q = 0; q < KT; ++q) sk[rl * RS + src * KT + q] = best_key(lv[mb][q], li[mb][q]);
+      for (int q = 0; q < KT; ++q) sk[rl * RS + src * KT + q] = best_key(logit_of(lk[mb][q]), index_of(lk[mb][q]));
       sm[rl * 8 + src] = run_m[mb];
       ss[rl * 8 + src] = run_s[mb];
     }
