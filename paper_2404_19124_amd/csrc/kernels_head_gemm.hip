@@ -94,9 +94,11 @@ GemmPlan plan_gemm(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   pl.ts = 4;
   pl.ksplit = 1;
   if (R <= 32) { pl.mi = 2; pl.ni = 1; pl.kcap = 8; }
-  // 33..64 rows against a long weight matrix (at least one 256-row tile per two CUs): the
-  // wide kernel re-reads the states a quarter as often per weight byte as the narrow one
-  else if (R <= 64 && (int64_t)n_head + n_proj >= (int64_t)128 * (n_cu > 0 ? n_cu : 256)) {
+  // 33..64 rows, at least one 64-row tile of weights per CU: the wide kernel, HBM-bound with 64-row state blocks and short
+  // tiles (40 rows x 4096, 16400 + 4096 weight rows 60.6 us with the narrow kernel's 64-row blocks, 48.1 here; 32000:
+  // 65.8 against 51).  Fewer tiles than CUs: the narrow kernel with two 32-row blocks, which doubles the workgroups
+  // (the second reads the weights from L2): 12000 + 4096 rows 37 us.
+  else if (R <= 64 && (int64_t)n_head + n_proj >= (int64_t)64 * (n_cu > 0 ? n_cu : 256)) {
     pl.mi = 4; pl.ni = 4; pl.ts = 16;
     pl.kcap = k_top <= 2 ? 2 : (k_top <= 4 ? 4 : (k_top <= 6 ? 6 : 8));
     fill_plan(pl, R, n_head, n_proj, n_cu);
@@ -104,10 +106,7 @@ GemmPlan plan_gemm(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
     return pl;
   }
   else if (R <= 64) {
-    // a short weight matrix (a projection alone) has too few 64-row tiles to fill the chip with
-    // 64-row state blocks: two 32-row blocks double the workgroups (the second reads the weights from L2)
-    const int64_t tiles = ((int64_t)n_head + 63) / 64 + ((int64_t)n_proj + 63) / 64;
-    pl.mi = tiles < (n_cu > 0 ? n_cu : 256) ? 2 : 4;
+    pl.mi = 2;
     pl.ni = 1;
     pl.kcap = 8;
   }
@@ -201,10 +200,10 @@ struct GemmArgs {
   int nparts;
 };
 
-// Narrow blocks (MI <= 4) are bandwidth-bound: two workgroups per CU (two waves per
+// Narrow blocks are bandwidth-bound: two workgroups per CU (two waves per
 // SIMD, 256 registers each) keep twice the loads in flight; wide blocks take all 512.
 template <int MI, int NI, int KT>
-__global__ __launch_bounds__(256, (MI <= 4 ? 2 : 1)) void head_gemm_kernel(GemmArgs p) {
+__global__ __launch_bounds__(256, 2) void head_gemm_kernel(GemmArgs p) {
   extern __shared__ __align__(16) unsigned char smem[];
   u32x4* ldsB = reinterpret_cast<u32x4*>(smem);  // [NSET][MI*KS*64]
   constexpr int SLAB = MI * KS * 64;             // slots per slab
@@ -1024,7 +1023,6 @@ hipError_t launch_head_gemm(const HeadJob& job, const GemmPlan& pl, hipStream_t 
   const bool vt = pl.ni == 4 && pl.ts != 16;  // wide kernel with short tiles
   switch (key) {
     case 2 * 100 + 1 * 10 + 8: return launch_gemm_t<2, 1, 8>(a, st, ev_start, ev_stop, dry);
-    case 4 * 100 + 1 * 10 + 8: return launch_gemm_t<4, 1, 8>(a, st, ev_start, ev_stop, dry);
 #define WIDE_CASE(MB_, KT_)                                                             \
     case (2 * MB_) * 100 + 4 * 10 + KT_:                                                \
       return vt ? launch_gemm32_t<MB_, 2, KT_, true>(a, st, ev_start, ev_stop, dry)      \

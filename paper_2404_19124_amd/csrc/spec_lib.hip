@@ -436,7 +436,7 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
   if (launch_head_gemm(job, pl, nullptr, nullptr, nullptr, &lds) != hipSuccess)
     return fail(SPEC_ESHAPE, "no kernel instance for %d-row blocks, %d weight rows per wave, top-k lists of %d, tiles of %d",
                 16 * pl.mi, 16 * pl.ni, pl.kcap, 16 * pl.ts);
-  out->kernel = pl.ni == 1 ? (pl.mi == 2 ? 1 : 2) : 1000 + 50 * pl.mi + 2 * pl.kcap + (pl.ts != 16 ? 1 : 0);
+  out->kernel = pl.ni == 1 ? 1 : 1000 + 50 * pl.mi + 2 * pl.kcap + (pl.ts != 16 ? 1 : 0);
   out->block_rows = 16 * pl.mi;
   out->tile_rows = 16 * pl.ts;
   out->row_blocks = pl.m_tiles;
@@ -522,7 +522,7 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
   *nparts = job.nparts;
   if (stage >= 0 && !out_head && (int64_t)R * job.nparts > ws.part_rows_parts)
     return fail(SPEC_ESHAPE, "internal: partial workspace too small (%d rows x %d parts)", R, job.nparts);
-  const int slot = prof_slot(m, pl.ni == 1 ? (pl.mi == 2 ? 1 : 2) : 1000 + 50 * pl.mi + 2 * pl.kcap + (pl.ts != 16 ? 1 : 0), R, job.n_head + job.n_proj, K);
+  const int slot = prof_slot(m, pl.ni == 1 ? 1 : 1000 + 50 * pl.mi + 2 * pl.kcap + (pl.ts != 16 ? 1 : 0), R, job.n_head + job.n_proj, K);
   HIP_TRY(launch_head_gemm(job, pl, st, EV0(slot), EV1(slot)));
   return SPEC_OK;
 }
