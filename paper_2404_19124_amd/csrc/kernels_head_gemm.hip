@@ -98,7 +98,8 @@ GemmPlan plan_gemm(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   // tiles (40 rows x 4096, 16400 + 4096 weight rows 60.6 us with the narrow kernel's 64-row blocks, 48.1 here; 32000:
   // 65.8 against 51).  Fewer tiles than CUs: the narrow kernel with two 32-row blocks, which doubles the workgroups
   // (the second reads the weights from L2): 12000 + 4096 rows 37 us.
-  else if (R <= 64 && (int64_t)n_head + n_proj >= (int64_t)64 * (n_cu > 0 ? n_cu : 256)) {
+  // (A projection alone stays there too: it is split along K.)
+  else if (R <= 64 && n_head > 0 && (int64_t)n_head + n_proj >= (int64_t)64 * (n_cu > 0 ? n_cu : 256)) {
     pl.mi = 4; pl.ni = 4; pl.ts = 16;
     pl.kcap = k_top <= 2 ? 2 : (k_top <= 4 ? 4 : (k_top <= 6 ? 6 : 8));
     fill_plan(pl, R, n_head, n_proj, n_cu);
