@@ -35,6 +35,9 @@ __device__ __forceinline__ int opaque_tid() {
 
 
 #define SPEC_NEG_INF (-__builtin_huge_valf())
+// Where a running maximum of logits starts: below every finite one, and finite itself, so that exp(x - max) of a first
+// logit of -inf is 0 (from a maximum of -inf it would be NaN) and that of a NaN is NaN, which the row's sum then shows.
+constexpr float kLowest = -__FLT_MAX__;
 constexpr int32_t kIdxNone = 0x7fffffff;
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }

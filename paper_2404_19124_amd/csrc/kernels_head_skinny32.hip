@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kS32Waves * 64) void head_skinny32_kernel(HeadJob p
   // running state of the 512 epilogue threads: state row en, weight row vi of the tile (16 consecutive
   // threads own one state row: their closing merge runs on DPP)
   const int en = (tid >> 4) & 31, vi = tid & 15;
-  float run_m = SPEC_NEG_INF, run_s = 0.f;
+  float run_m = kLowest, run_s = 0.f;
   const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
   if (tid < 512) {
 #pragma unroll
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kS32Waves * 64) void head_skinny32_kernel(HeadJob p
   // ---- merge the 16 residue lists of each row (16 consecutive lanes) into the workgroup's partial
   if (tid < 512) {
     const float mx = row16_max(run_m);
-    const float s = row16_sum((run_m > SPEC_NEG_INF) ? run_s * __expf(run_m - mx) : 0.f);
+    const float s = row16_sum(run_s * __expf(run_m - mx));
     const int64_t slot = (int64_t)en * p.nparts + wg;
     if (en < R && vi == 0) {
       p.part.m[slot] = mx;

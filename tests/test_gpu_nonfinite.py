@@ -1,0 +1,71 @@
+"""Logits that are not finite: one of -inf takes nothing from the rest of its row, one that is NaN shows."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import spec_oracle as O
+from paper_2404_19124_amd import workloads as W
+from paper_2404_19124_amd.runner import Step
+
+pytestmark = pytest.mark.gpu
+
+BIG = 3.0e38   # a head row of it: the logit of a state around 1 overflows
+
+
+def _first_stage(dtype, V, batch, k, edit):
+    """The tables of a one-stage draft, and its states and head."""
+    wl = W.Workload("nonfinite", 128, 128, V, 1, (k,), k, batch, dtype, "f32", 0.5, seed=43, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    w["ln_beta"][0] += 1.0
+    edit(w["head"][0])
+    state, last = W.make_draft_inputs(wl, gen)
+    step = Step(wl, {key: [t.cuda() for t in v] for key, v in w.items()}, debug=True)
+    step.draft(state.cuda(), last.cuda())
+    torch.cuda.synchronize()
+    t = step.debug_tables()
+    got = {key: t[key][0].float().cpu().numpy() for key in ("tok", "logp", "lse", "states")}
+    step.close()
+    return got, W.to_numpy_f32(w["head"][0])
+
+
+# 17 to 32 rows (streaming kernel), float32: two tiles of weight rows and more per workgroup, so that finite logits
+# follow in the same thread
+STREAM = [("bf16", 20500, 20, 3), ("f32", 20500, 5, 3)]
+
+
+@pytest.mark.parametrize("dtype,V,batch,k", STREAM)
+def test_logits_of_minus_infinity_count_nothing(dtype, V, batch, k):
+    low = np.zeros(V, bool)
+    low[:4096] = True      # the first tiles of every workgroup
+    low[5000::7] = True
+
+    def edit(head):
+        head[torch.from_numpy(low)] = -BIG
+
+    got, head = _first_stage(dtype, V, batch, k, edit)
+    logits = O.head_logits(got["states"], head)
+    assert (got["states"].sum(1) > 2).all()   # so these logits are below the smallest float32
+    logits[:, low] = -np.inf
+    logp, lse = O.log_softmax(logits)
+    # float32 sums of 128 products against float64: the bound of the other float32 shapes
+    assert np.abs(got["lse"] - lse).max() < 1e-3
+    for r in range(batch):
+        want = O.topk_desc(logits[r].astype(np.float32), k)
+        assert np.array_equal(got["tok"][r], want)
+        assert np.abs(got["logp"][r] - logp[r, want]).max() < 1e-3
+
+
+@pytest.mark.parametrize("at", [0, -1], ids=["first", "last"])
+@pytest.mark.parametrize("dtype,V,batch,k", [("bf16", 4097, 20, 2), ("bf16", 9, 32, 3), ("bf16", 20500, 17, 2)])
+def test_a_logit_that_is_nan_shows_in_its_rows_sum(dtype, V, batch, k, at):
+    """Also where it is the only logit of its thread, or (the last row of a ragged tile) of its workgroup."""
+    def edit(head):
+        head[at] = float("nan")
+
+    got, head = _first_stage(dtype, V, batch, k, edit)
+    assert np.isnan(got["lse"]).all() and np.isnan(got["logp"]).all()
+    logits = O.head_logits(got["states"], head)
+    logits[:, at] = -np.inf   # and takes no place among the row's best
+    for r in range(batch):
+        assert np.array_equal(got["tok"][r], O.topk_desc(logits[r].astype(np.float32), k))
