@@ -85,7 +85,7 @@ __global__ __launch_bounds__(1024) void contract_f32_kernel(F32Args p) {
   const float* arow = p.a + (int64_t)min(r0 + (lane & 15), p.R - 1) * p.K;
   const int kl = 4 * (lane >> 4);
 
-  float run_m = SPEC_NEG_INF, run_s = 0.f;
+  float run_m = kLowest, run_s = 0.f;
   const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
   uint64_t best[kMaxTopK];
 #pragma unroll
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(1024) void contract_f32_kernel(F32Args p) {
         p.out[mat][(int64_t)row * p.ldo[mat] + v] = x;
       } else {
         const float m = fmaxf(run_m, x);
-        if (m > SPEC_NEG_INF) run_s = run_s * expf(run_m - m) + expf(x - m);
+        run_s = run_s * expf(run_m - m) + expf(x - m);
         run_m = m;
         uint64_t key = best_key(x, v);
 #pragma unroll
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(1024) void contract_f32_kernel(F32Args p) {
   }
   if (p.out[mat] || row >= p.R) return;  // (a whole wave)
   const float mx = wave_max(run_m);
-  const float sum = wave_sum(run_m > SPEC_NEG_INF ? run_s * expf(run_m - mx) : 0.f);
+  const float sum = wave_sum(run_s * expf(run_m - mx));
   const int64_t slot = (int64_t)row * p.nparts + block;
   if (lane == 0) {
     p.part.m[slot] = mx;

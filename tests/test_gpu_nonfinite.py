@@ -57,7 +57,8 @@ def test_logits_of_minus_infinity_count_nothing(dtype, V, batch, k):
 
 
 @pytest.mark.parametrize("at", [0, -1], ids=["first", "last"])
-@pytest.mark.parametrize("dtype,V,batch,k", [("bf16", 4097, 20, 2), ("bf16", 9, 32, 3), ("bf16", 20500, 17, 2)])
+@pytest.mark.parametrize("dtype,V,batch,k", [("bf16", 4097, 20, 2), ("bf16", 9, 32, 3), ("bf16", 20500, 17, 2),
+                                             ("f32", 65, 3, 3), ("f32", 1024, 17, 2), ("f32", 20500, 2, 2)])
 def test_a_logit_that_is_nan_shows_in_its_rows_sum(dtype, V, batch, k, at):
     """Also where it is the only logit of its thread, or (the last row of a ragged tile) of its workgroup."""
     def edit(head):
