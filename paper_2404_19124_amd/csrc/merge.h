@@ -256,6 +256,7 @@ __device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_
     for (int t = 0; t < K; ++t)
       before_me += reinterpret_cast<const uint64_t*>(lds + q * kMergeWave + 2)[t] > key ? 1 : 0;
   best_unkey(key, out_val, out_idx);
+  if (out_idx > kIdxNone - 4 * kMaxTopK) out_idx = kIdxNone;   // (an empty entry: no token has such an index)
   rank = lane < 4 * K ? before_me : kNoRank;
 }
 

@@ -70,3 +70,23 @@ def test_a_logit_that_is_nan_shows_in_its_rows_sum(dtype, V, batch, k, at):
     logits[:, at] = -np.inf   # and takes no place among the row's best
     for r in range(batch):
         assert np.array_equal(got["tok"][r], O.topk_desc(logits[r].astype(np.float32), k))
+
+
+@pytest.mark.parametrize("dtype,V,batch", [("bf16", 3001, 3), ("bf16", 3001, 20), ("bf16", 3001, 50), ("f32", 300, 3)])
+def test_a_row_without_an_order_names_no_made_up_token(dtype, V, batch):
+    """All logits NaN: every entry of the row is a token of the vocabulary or the mark of none (2^31 - 1)."""
+    k = 5
+    wl = W.Workload("nonfinite", 128, 128, V, 2, (k, 2), 2 * k, batch, dtype, "f32", 0.5, seed=44, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    state, last = W.make_draft_inputs(wl, gen)
+    state[1] = float("nan")
+    step = Step(wl, {key: [t.cuda() for t in v] for key, v in w.items()}, debug=True)
+    step.draft(state.cuda(), last.cuda())
+    torch.cuda.synchronize()
+    tok = step.debug_tables()["tok"][0].cpu().numpy()
+    assert (tok[[0, 2]] < V).all() and (tok[[0, 2]] >= 0).all()
+    assert (((tok[1] >= 0) & (tok[1] < V)) | (tok[1] == 2**31 - 1)).all()
+    cand = step.cand_tokens.cpu().numpy()
+    assert (((cand >= 0) & (cand < V)) | (cand == 2**31 - 1)).all()
+    step.close()
