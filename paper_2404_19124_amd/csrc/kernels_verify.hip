@@ -13,7 +13,7 @@
 
 namespace specdraft {
 
-template <bool BF16, int NT>
+template <bool BF16, int NT, int U>
 __global__ __launch_bounds__(NT) void argmax_rows_kernel(const void* logits, int V, int B, int n1,
                                                            const int32_t* n_cand, int32_t* greedy) {
   __shared__ float sv[16];
@@ -35,27 +35,34 @@ __global__ __launch_bounds__(NT) void argmax_rows_kernel(const void* logits, int
   float bv = SPEC_NEG_INF;
   int32_t bi = kIdxNone;
   // 16-byte loads from the row's first 16-byte boundary on; the few elements before it (a vocabulary whose rows do
-  // not start on one) and behind the last whole word go one to a thread.  Eight loads of a thread are in flight: at
-  // small batch the kernel is a chain of memory round trips, not a stream.  Non-temporal: the logits are read once.
-  // (24 x 64 rows of 32003 floats: 40.2 us element by element -> 17.1 us = 6.0 TB/s; rows that start on a
-  // boundary take what they took.)
+  // not start on one) and behind the last whole word go one to a thread, requested with the rest: at small batch the
+  // kernel is a chain of memory round trips, not a stream.  U words of a thread are in flight.  Non-temporal: the
+  // logits are read once.
   typedef typename std::conditional<BF16, uint16_t, float>::type elem;
   constexpr int PER = BF16 ? 8 : 4;
   const elem* x = static_cast<const elem*>(logits) + row * V;
   auto take = [&](float v, int i) {
     if (v > bv) { bv = v; bi = i; }
   };
-  auto one = [&](int i) {
-    if constexpr (BF16) take(bf16_bits_to_f32(x[i]), i);
-    else take(x[i], i);
+  auto value = [](elem e) {
+    if constexpr (BF16) return bf16_bits_to_f32(e);
+    else return e;
   };
-  const int lead = min(V, (int)((16 - (reinterpret_cast<uintptr_t>(x) & 15)) & 15) / (int)sizeof(elem));
-  if (tid < lead) one(tid);
+  if constexpr (U == 0) {
+    for (int i = tid; i < V; i += NT) take(value(x[i]), i);
+  }
+  const uint32_t past = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(x)) & 15;
+  const int lead = min(V, (int)(((16 - past) & 15) / (uint32_t)sizeof(elem)));
   const u32x4* xv = reinterpret_cast<const u32x4*>(x + lead);
-  const int nvec = (V - lead) / PER;
-  constexpr int U = 8192 / NT;
+  const int nvec = U == 0 ? 0 : (int)((uint32_t)(V - lead) / PER), rest = lead + nvec * PER;
+  const bool ends = U > 0 && lead + (V - rest) > 0;   // (the same for every thread)
+  elem first = 0, last = 0;
+  if (ends) {
+    if (tid < lead) first = x[tid];
+    if (tid < V - rest) last = x[rest + tid];
+  }
   for (int c0 = tid; c0 < nvec; c0 += NT * U) {
-    u32x4 raw[U];
+    u32x4 raw[U > 0 ? U : 1];
 #pragma unroll
     for (int u = 0; u < U; ++u) raw[u] = __builtin_nontemporal_load(xv + min(c0 + u * NT, nvec - 1));
 #pragma unroll
@@ -74,27 +81,45 @@ __global__ __launch_bounds__(NT) void argmax_rows_kernel(const void* logits, int
       }
     }
   }
-  const int rest = lead + nvec * PER;
-  if (tid < V - rest) one(rest + tid);
+  if (ends) {
+    if (tid < V - rest) take(value(last), rest + tid);
+    // (the element before the boundary comes before the thread's others: it wins a tie)
+    if (tid < lead && value(first) > SPEC_NEG_INF && value(first) >= bv) { bv = value(first); bi = tid; }
+  }
   block_best<NT>(bv, bi, sv, si);
   // a row of NaNs (or of -inf) has no "larger" element: report index 0 like a first-maximum scan
   if (tid == 0) greedy[row] = (bi == kIdxNone) ? 0 : bi;
 }
 
+// As many words of a thread in flight as a row has: a row of fewer loads its last word over and over in the others (4096
+// rows of 1001 floats with 16 in flight: 20.1 us).  Two elements of a thread and less: no words at all, the row's ends
+// would cost more than they save (the same rows: 10.1 us by words, 9.8 by elements).  4096 rows of 8001 floats: 30.8 us
+// by elements, 35.2 with 16 words in flight, 22.4 with 4; of 32003: 157 by elements, 80 now.
+template <bool BF16, int NT>
+static void launch_argmax_t(const void* logits, int64_t rows, int V, int B, int n1, const int32_t* n_cand,
+                            int32_t* greedy, hipStream_t st) {
+  const int words = V / (BF16 ? 8 : 4);
+#define LAUNCH_ARGMAX(U) \
+  hipLaunchKernelGGL((argmax_rows_kernel<BF16, NT, U>), dim3((unsigned)rows), dim3(NT), 0, st, logits, V, B, n1, n_cand, greedy)
+  if (V <= 2 * NT) LAUNCH_ARGMAX(0);
+  else if (words <= NT) LAUNCH_ARGMAX(1);
+  else if (words <= 2 * NT) LAUNCH_ARGMAX(2);
+  else if (words <= 4 * NT) LAUNCH_ARGMAX(4);
+  else LAUNCH_ARGMAX(8192 / NT);
+#undef LAUNCH_ARGMAX
+}
+
 hipError_t launch_argmax_rows(const void* logits, int bf16, int64_t rows, int V, int B, int n1, const int32_t* n_cand,
                               int32_t* greedy, hipStream_t st) {
-  dim3 grid((unsigned)rows);
   // a few rows (small batch): a chain of memory round trips, the more loads in flight per row the better;
   // thousands of rows: a stream, which runs a little faster from 512-thread workgroups (7B batch 64: 81 -> 79.4 us)
-  const int nt = rows >= 1024 ? 512 : 1024;
-#define LAUNCH_ARGMAX(B16, NT) \
-  hipLaunchKernelGGL((argmax_rows_kernel<B16, NT>), grid, dim3(NT), 0, st, logits, V, B, n1, n_cand, greedy)
-  if (bf16) {
-    if (nt == 512) LAUNCH_ARGMAX(true, 512); else LAUNCH_ARGMAX(true, 1024);
+  if (rows >= 1024) {
+    if (bf16) launch_argmax_t<true, 512>(logits, rows, V, B, n1, n_cand, greedy, st);
+    else launch_argmax_t<false, 512>(logits, rows, V, B, n1, n_cand, greedy, st);
   } else {
-    if (nt == 512) LAUNCH_ARGMAX(false, 512); else LAUNCH_ARGMAX(false, 1024);
+    if (bf16) launch_argmax_t<true, 1024>(logits, rows, V, B, n1, n_cand, greedy, st);
+    else launch_argmax_t<false, 1024>(logits, rows, V, B, n1, n_cand, greedy, st);
   }
-#undef LAUNCH_ARGMAX
   return hipGetLastError();
 }
 

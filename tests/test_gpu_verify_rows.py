@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("V", [1, 3, 7, 8, 9, 4097, 8195, 33001])
+@pytest.mark.parametrize("V", [1, 3, 7, 8, 9, 1025, 2048, 2051, 4097, 8195, 16389, 33001])
 @pytest.mark.parametrize("rows", [6, 1026])
 def test_first_maximum_of_rows_that_start_anywhere(dtype, V, rows):
     """Both workgroup sizes (rows), every offset of a row from its 16-byte boundary, the maximum at each edge of the
