@@ -94,12 +94,13 @@ GemmPlan plan_gemm(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   pl.ts = 4;
   pl.ksplit = 1;
   if (R <= 32) { pl.mi = 2; pl.ni = 1; pl.kcap = 8; }
-  // 33..64 rows, at least one 64-row tile of weights per CU: the wide kernel, HBM-bound with 64-row state blocks and short
+  // 33..64 rows, more than one 64-row tile of weights per CU: the wide kernel, HBM-bound with 64-row state blocks and short
   // tiles (40 rows x 4096, 16400 + 4096 weight rows 60.6 us with the narrow kernel's 64-row blocks, 48.1 here; 32000:
-  // 65.8 against 51).  Fewer tiles than CUs: the narrow kernel with two 32-row blocks, which doubles the workgroups
-  // (the second reads the weights from L2): 12000 + 4096 rows 37 us.
+  // 65.8 against 51).  Up to one tile per CU: the narrow kernel with two 32-row blocks, which doubles the workgroups
+  // (the second reads the weights from L2): 12000 + 4096 rows 37 us; 64 rows against exactly 16384 of
+  // K = 2048 / 4096 / 8192: 18.8 / 27.8 / 60.6 us, 24.2 / 45.1 / 81.1 with the wide kernel; one row more: 44.7 at 4096.
   // (A projection alone stays there too: it is split along K.)
-  else if (R <= 64 && n_head > 0 && (int64_t)n_head + n_proj >= (int64_t)64 * (n_cu > 0 ? n_cu : 256)) {
+  else if (R <= 64 && n_head > 0 && (int64_t)n_head + n_proj > (int64_t)64 * (n_cu > 0 ? n_cu : 256)) {
     pl.mi = 4; pl.ni = 4; pl.ts = 16;
     pl.kcap = k_top <= 2 ? 2 : (k_top <= 4 ? 4 : (k_top <= 6 ? 6 : 8));
     fill_plan(pl, R, n_head, n_proj, n_cu);
