@@ -34,8 +34,15 @@ constexpr int kS32Acc = 3 * kS32Group + 16;
 constexpr size_t kS32LdsP = (size_t)2 * kS32Waves * 2 * kS32Acc * 16;
 constexpr size_t kS32Lds = kS32LdsP + (size_t)kMaxTopK * 512 * 8;   // + the epilogue threads' top-k lists
 
-bool skinny32_fits(int R, int kt, int n_head) {
-  return R > 16 && R <= 32 && n_head > 0 && n_head <= kS32MaxHead && (kt + kS32Waves - 1) / kS32Waves <= kS32Steps;
+// A tile costs 0.9 us of 16 waves, a barrier and an epilogue however short K is, so many tiles of few columns stay with
+// the dense kernel, whose waves share nothing.  24 rows, us here / there:  16000 rows of K = 64, 256:  9.2 / 9.9,
+// 9.9 / 10.5;  32000 of 64, 256, 384, 512:  12.5 / 10.2, 13.2 / 11.5, 13.2 / 13.4, 14.1 / 14.9;  65536 of 64, 256, 512,
+// 768, 1024:  19.4 / 13.2, 19.8 / 15.9, 21.5 / 18.9 (with a projection 21.1 / 21.6), 22.0 / 22.7, 25.5 / 27.6.
+// Hence four tiles per workgroup, or one per 48 columns.
+bool skinny32_fits(int R, int kt, int n_head, int n_cu) {
+  const int tiles = kt * 32 / 48 > 4 ? kt * 32 / 48 : 4;   // of a workgroup
+  return R > 16 && R <= 32 && n_head > 0 && n_head <= kS32MaxHead && (kt + kS32Waves - 1) / kS32Waves <= kS32Steps &&
+         (n_head + 15) / 16 <= (int64_t)tiles * skinny_grid(n_cu);
 }
 size_t skinny32_lds_bytes() { return kS32Lds; }
 

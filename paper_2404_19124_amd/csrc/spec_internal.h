@@ -100,7 +100,7 @@ size_t skinny_lds_bytes(int R, int kt);   // dynamic LDS of one workgroup
 // 17 .. 32 rows against a head: the same streaming design with the states in registers (K <= 4096).
 // nparts = grid size.  (A projection alone stays with the dense kernel, split along K: 24 rows x 4096 x 4096
 // row-major 10.4 us there, 12.2 us here, where 16 waves gather the rows in 64-byte pieces.)
-bool skinny32_fits(int R, int kt, int n_head);
+bool skinny32_fits(int R, int kt, int n_head, int n_cu);
 size_t skinny32_lds_bytes();
 hipError_t launch_head_skinny32(const HeadJob& job, int n_cu, hipStream_t st, hipEvent_t ev_start = nullptr,
                                 hipEvent_t ev_stop = nullptr);

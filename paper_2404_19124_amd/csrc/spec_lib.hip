@@ -406,7 +406,7 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
   if (n_cu < 1) return fail(SPEC_EINVAL, "n_cu = %d must be >= 1", n_cu);
   memset(out, 0, sizeof(*out));
   const int kt = k / 32;
-  if (skinny_fits(rows, kt) || skinny32_fits(rows, kt, n_head)) {
+  if (skinny_fits(rows, kt) || skinny32_fits(rows, kt, n_head, n_cu)) {
     out->kernel = 0;
     out->block_rows = rows <= 16 ? 16 : 32;
     out->tile_rows = 16;
@@ -499,7 +499,7 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
   const int K = b_ld;
   if (fold && !skinny_fits(R, job.kt)) return fail(SPEC_ESHAPE, "internal: folded stage on a contraction of %d rows", R);
   if (fold) job.fold = *fold;
-  if (skinny_fits(R, job.kt) || skinny32_fits(R, job.kt, job.n_head)) {
+  if (skinny_fits(R, job.kt) || skinny32_fits(R, job.kt, job.n_head, m->n_cu)) {
     job.nparts = skinny_grid(m->n_cu);
     *nparts = job.nparts;
     const int slot = prof_slot(m, 0, R, job.n_head + job.n_proj, K);
@@ -897,7 +897,7 @@ extern "C" spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const vo
   const int D = m->cfg.inner_dim, V = m->cfg.vocab;
   if (m->bf16) {
     int nparts = 0;
-    if (skinny_fits(rows, D / 32) || skinny32_fits(rows, D / 32, V)) {
+    if (skinny_fits(rows, D / 32) || skinny32_fits(rows, D / 32, V, m->n_cu)) {
       spec_status_t s = run_contraction(m, m->ws, stage, -1, states, true, D, rows, 0, logp, nullptr, &nparts, st);
       if (s != SPEC_OK) return s;
     } else {

@@ -19,7 +19,7 @@ CASES = [
     (128, 3072, 8200, (8, 1), 4, 31),     # 31 rows, widest lists, two tiles in flight
     (192, 4032, 4097, (3, 1), 3, 25),     # 126 steps: the last slice is two steps short
     (128, 4096, 4097, (5, 1), 5, 32),     # full slices, ragged vocabulary, projection behind the head
-    (64, 128, 65536, (2, 1), 2, 20),      # the longest head: 16 tiles per workgroup
+    (64, 768, 65536, (2, 1), 2, 20),      # the longest head: 16 tiles per workgroup
 ]
 
 
@@ -28,7 +28,7 @@ def test_17_to_32_rows(case):
     E, D, V, top_k, Bc, batch = case
     wl = W.Workload("stream32", E, D, V, len(top_k), top_k, Bc, batch, "bf16", "f32", 0.6, seed=23, emb_std=0.3)
     rows = [r for r in wl.rows() if 16 < r <= 32]
-    assert B.spec_plan_contraction(20, 128, 65537, 1, 128)["kernel"] == 1   # longer heads: the dense kernel
+    assert B.spec_plan_contraction(20, 768, 65537, 1, 768)["kernel"] == 1   # longer heads: the dense kernel
     assert rows and all(B.spec_plan_contraction(r, D, V, 1, D)["kernel"] == 0 for r in rows)
     rep, step, od, ov = run_workload(wl, ln_affine="random", gen_device="cpu")
     assert rep.rows_checked + rep.rows_skipped_below_exempt == sum(wl.rows())

@@ -104,6 +104,15 @@ def test_plans_of_the_benchmark_shapes(args, want):
     assert p["proj_apart"] == (1 if args == (320, 4096, 32000, 3, 4096) else 0)
 
 
+# 17 to 32 rows: the streaming kernel up to four 16-row tiles of head per CU or one per 48 columns, whichever is more
+@pytest.mark.parametrize("k,n_head,n_cu", [(64, 16 * 4 * 256, 256), (256, 16 * 5 * 256, 256), (384, 16 * 8 * 256, 256),
+                                           (768, 16 * 16 * 256, 256), (128, 16 * 4 * 40, 40)])
+@pytest.mark.parametrize("rows", [17, 32])
+def test_short_rows_against_a_long_head_stay_on_the_dense_kernel(rows, k, n_head, n_cu):
+    assert check_plan(rows, k, n_head, 3, k, n_cu)["kernel"] == 0
+    assert check_plan(rows, k, n_head + 1, 3, 0, n_cu)["kernel"] == 1
+
+
 @pytest.mark.parametrize("args", [(0, 4096, 32000, 2, 0, 256), (4, 100, 32000, 2, 0, 256), (4, 4096, 0, 0, 0, 256),
                                   (4, 4096, 32000, 9, 0, 256), (4, 4096, 32000, 0, 0, 256), (4, 4096, -1, 2, 64, 256),
                                   (4, 4096, 32000, 2, 0, 0)])
