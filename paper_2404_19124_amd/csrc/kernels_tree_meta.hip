@@ -13,7 +13,8 @@ namespace specdraft {
 // looks for the first one with the same first(., p - 1) and the same token: two words per comparison whatever the
 // depth, four comparisons per trip; the numbering is a scan over ballots; the mask is cleared in 16-byte stores while
 // that runs.  (Whole prefixes compared token by token, a count over all earlier items per item and single-byte
-// stores: 19.8 us for 16 sequences of 32 candidates x 3, 11.8 us now.)
+// stores: 18 us for 16 sequences of 32 candidates x 3, calls back to back; one word after the other per comparison:
+// 9.4, and slower than that on chains and trees of a few candidates; now 6.4.)
 // M = B * n <= kMaxTreeItems.  Dynamic LDS: 3 * M ints.
 __global__ __launch_bounds__(256) void tree_meta_kernel(const int32_t* __restrict__ cand, int B, int n,
                                                         int32_t* node_tok, int32_t* node_parent, int32_t* node_depth,
@@ -27,8 +28,24 @@ __global__ __launch_bounds__(256) void tree_meta_kernel(const int32_t* __restric
   int32_t* nid = lds + 2 * M;    // [M] node number of a prefix, where first(c, p) == c
   const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int32_t* cq = cand + (int64_t)q * M;
+  if (B == 1) {   // a chain: every prefix is a node (24 chains of 7: 4.5 us through the passes below, 2.2 here)
+    for (int p = tid; p < n; p += 256) {
+      node_tok[(int64_t)q * M + p] = cq[p];
+      node_parent[(int64_t)q * M + p] = p - 1;
+      node_depth[(int64_t)q * M + p] = p + 1;
+      cand_node[(int64_t)q * M + p] = p;
+    }
+    if (tid == 0) n_nodes[q] = n;
+    if (mask)
+      for (int i = tid; i < n * n; i += 256) mask[(int64_t)q * n * n + i] = i % n <= i / n ? 1 : 0;
+    return;
+  }
+  // item i -> candidate i / n by a reciprocal: (i + 0.5) / n is at least 0.5 / n from every whole number, the product at
+  // most 4096 / n * 2^-22 off
+  const float rn = 1.0f / (float)n;
+  auto cand_of = [&](int i) { return (int)(((float)i + 0.5f) * rn); };
   for (int i = tid; i < M; i += 256) {
-    const int c = i / n, p = i - c * n;
+    const int c = cand_of(i), p = i - c * n;
     tok[p * B + c] = cq[i];
   }
   if (mask) {
@@ -38,23 +55,28 @@ __global__ __launch_bounds__(256) void tree_meta_kernel(const int32_t* __restric
     const int64_t lead = lead0 < bytes ? lead0 : bytes, n16 = (bytes - lead) / 16;
     if (tid < lead) mq[tid] = 0;
     u32x4* mv = reinterpret_cast<u32x4*>(mq + lead);
-    for (int64_t i = tid; i < n16; i += 256) mv[i] = (u32x4){0, 0, 0, 0};
+#pragma unroll 4
+    for (int i = tid; i < (int)n16; i += 256) mv[i] = (u32x4){0, 0, 0, 0};
     if (tid < bytes - lead - n16 * 16) mq[lead + n16 * 16 + tid] = 0;
   }
   __syncthreads();
   for (int p = 0; p < n; ++p) {
     const int32_t* tp = tok + p * B;
-    const int32_t* fp = first + (p - 1) * B;   // (not read at depth 0)
+    const int32_t* fp = first + (p - 1) * B;   // (at depth 0: the tail of tok[], read and not used)
     for (int c = tid; c < B; c += 256) {
       const int t = tp[c], f0 = p ? fp[c] : 0;
       int f = c;
       // (the first candidate of the longer prefix is not before the first of the shorter one)
       for (int c2 = f0; c2 < f; c2 += 4) {
+        int ot[4], of[4];   // all eight words are requested before the first is looked at
 #pragma unroll
-        for (int u = 3; u >= 0; --u) {
-          const int o = min(c2 + u, c);
-          if (tp[o] == t && (p == 0 || fp[o] == f0)) f = min(f, o);
+        for (int u = 0; u < 4; ++u) {
+          ot[u] = tp[min(c2 + u, c)];
+          of[u] = fp[min(c2 + u, c)];
         }
+#pragma unroll
+        for (int u = 3; u >= 0; --u)
+          if ((ot[u] == t) & ((p == 0) | (of[u] == f0))) f = min(f, c2 + u);
       }
       first[p * B + c] = f;
     }
@@ -63,7 +85,7 @@ __global__ __launch_bounds__(256) void tree_meta_kernel(const int32_t* __restric
   // numbering in item order
   int total = 0;
   for (int i0 = 0; i0 < M; i0 += 256) {
-    const int i = i0 + tid, c = i / n, p = i - c * n;
+    const int i = i0 + tid, c = cand_of(i), p = i - c * n;
     const bool node = i < M && first[p * B + c] == c;
     const uint64_t votes = __ballot(node);
     if (lane == 0) s_wave[wave] = __popcll(votes);
@@ -78,7 +100,7 @@ __global__ __launch_bounds__(256) void tree_meta_kernel(const int32_t* __restric
   }
   if (tid == 0) n_nodes[q] = total;
   for (int i = tid; i < M; i += 256) {
-    const int c = i / n, p = i - c * n, f = first[p * B + c];
+    const int c = cand_of(i), p = i - c * n, f = first[p * B + c];
     const int me = nid[p * B + f];
     cand_node[(int64_t)q * M + i] = me;
     if (f == c) {

@@ -9,8 +9,9 @@ from tests.test_gpu_next_rows import _device_metadata
 pytestmark = pytest.mark.gpu
 
 # b, B, n, V: odd mask sizes for several sequences (rows of the mask start anywhere), more candidates than threads,
-# items across the chunks of the scan, all candidates equal, padding candidates
-CASES = [(3, 67, 5, 2), (2, 300, 1, 2), (1, 4096, 1, 3000), (5, 3, 3, 2), (2, 257, 3, 6), (2, 40, 7, 1)]
+# items across the chunks of the scan, all candidates equal, padding candidates, chains
+CASES = [(3, 67, 5, 2), (2, 300, 1, 2), (1, 4096, 1, 3000), (5, 3, 3, 2), (2, 257, 3, 6), (2, 40, 7, 1),
+         (24, 1, 7, 3), (1, 1, 1, 3), (3, 2, 5, 1), (2, 64, 8, 3), (2, 65, 8, 3)]
 
 
 @pytest.mark.parametrize("b,Bc,n,V", CASES)
