@@ -544,10 +544,25 @@ __device__ __forceinline__ double key_min(double a, double b) {
   asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+// (x: not a matrix result the compiler has not waited for, see matrix_results_settled)
 __device__ __forceinline__ double logit_key(float x, int32_t not_index) {
   float v;
   asm("v_max_f32 %0, 0xff800000, %1" : "=v"(v) : "v"(x));   // NaN -> -inf
   return __hiloint2double(__float_as_int(v), not_index ^ (__float_as_int(v) >> 31));
+}
+// A VALU read of a matrix result has to stand up to 20 wait states behind the matrix instruction.  The compiler keeps
+// that distance for its own instructions, not for the asm statement of logit_key: every accumulator passes through one
+// that waits, 24 states in the ten-thousands of cycles of a tile.  (fmaxf in logit_key needs none of this and costs a
+// second instruction per logit: 43 launches of 64 to 2304 rows 0.3 % slower on average, with the wait equal.)
+template <int MB>
+__device__ __forceinline__ void matrix_results_settled(f32x16 (&a)[MB][2]) {
+  static_assert(MB >= 2 && MB <= 5, "one list per block height");
+#define ROW_(m) "+v"(a[m][0]), "+v"(a[m][1])
+  if constexpr (MB == 2) asm volatile("s_nop 15\n\ts_nop 7" : ROW_(0), ROW_(1));
+  if constexpr (MB == 3) asm volatile("s_nop 15\n\ts_nop 7" : ROW_(0), ROW_(1), ROW_(2));
+  if constexpr (MB == 4) asm volatile("s_nop 15\n\ts_nop 7" : ROW_(0), ROW_(1), ROW_(2), ROW_(3));
+  if constexpr (MB == 5) asm volatile("s_nop 15\n\ts_nop 7" : ROW_(0), ROW_(1), ROW_(2), ROW_(3), ROW_(4));
+#undef ROW_
 }
 __device__ __forceinline__ float logit_of(double key) { return __int_as_float(__double2hiint(key)); }
 __device__ __forceinline__ int32_t index_of(double key) { return ~(__double2loint(key) ^ (__double2hiint(key) >> 31)); }
@@ -803,6 +818,7 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
     }
     // (a wave whose rows all lie past the tile's end has nothing to add)
     if (cur_mat == 0 && p.mode0 == 0 && (!VT || cur_nt[0] < cur_end)) {
+      matrix_results_settled<MB>(acc);
       // only a block that reaches past the end of the tile or of the vocabulary needs the validity mask
       if ((cur_nt[NB - 1] + 2) * 16 > n_valid) {
 #pragma unroll

@@ -1,0 +1,29 @@
+"""What the compiler does not check about the kernels' inline assembly."""
+import glob
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2404_19124_amd", "csrc")
+
+
+def _sources():
+    for path in sorted(glob.glob(os.path.join(CSRC, "*"))):
+        with open(path) as f:
+            yield os.path.basename(path), re.sub(r"//[^\n]*", "", f.read())
+
+
+def test_assembly_that_reads_matrix_results_stands_behind_a_wait():
+    """The compiler keeps the distance between a matrix instruction and the reader of its result for its own
+    instructions only.  So assembly stays in one file, and there every accumulator passes through the statement that
+    waits before the first one of the epilogue is read by assembly."""
+    for name, text in _sources():
+        emitted = {m.split()[0] for t in re.findall(r'asm(?: volatile)?\(\s*"([^"]*)"', text) for m in t.split("\\n\\t")
+                   if m.strip()}
+        assert emitted <= ({"v_max_f64", "v_min_f64", "v_max_f32", "s_nop"} if name == "kernels_head_gemm.hip" else set())
+        if emitted:
+            reads = [m.start() for m in re.finditer(r"logit_key\(acc", text)]
+            waits = [m.start() for m in re.finditer(r"matrix_results_settled<MB>\(acc\)", text)]
+            products = [m.start() for m in re.finditer(r"__builtin_amdgcn_mfma_f32_32x32", text)]
+            assert len(reads) == 1 and len(waits) == 1 and max(products) < waits[0] < reads[0]
+            # two s_nop of 16 and 8 states: 16 passes of the instruction and 4 more are needed
+            assert text.count('"s_nop 15\\n\\ts_nop 7"') == 4
