@@ -534,6 +534,10 @@ __device__ __forceinline__ void interleave_half() {
 // index apart took 5 KT: KT = 2, 3, 6: 3, 5, 11 instructions per logit instead of 8, 13, 28.  Launches against 32000
 // rows x 4096: 75 rows, top-2, 55.4 -> 50.8 us; 64 rows, top-5, with a projection, 62.1 -> 58.8; 320 rows, top-3,
 // 96.5 -> 92.2; 384 rows, top-3, 120.5 -> 116.4; 960 rows, top-2, 1 to 2 %.)
+// The key of a logit of exactly 0 has an empty high word: a float64 denormal, whose low word alone makes the order.  So
+// float64 denormals must not be flushed, which is what kernels are compiled for unless a flag says otherwise (the
+// flag that flushes float32 ones leaves these alone).  A logit of -0 would sort behind +0; the accumulators start at +0
+// and stay there unless the whole sum underflows.
 __device__ __forceinline__ double key_max(double a, double b) {
   double r;
   asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));

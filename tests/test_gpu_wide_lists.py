@@ -42,3 +42,28 @@ def test_exact_ties_go_to_the_smaller_index(batch, k, V, sign):
     want = np.stack([np.flatnonzero(of.numpy() == int(c))[:k] for c in best])
     assert np.array_equal(step.cand_tokens.cpu().numpy()[:, :, 0], want)
     step.close()
+
+
+@pytest.mark.parametrize("batch,k,V", [(40, 2, 33003), (64, 4, 33003), (40, 6, 33003), (33, 8, 33003), (96, 3, 33003),
+                                       (310, 2, 20300), (465, 4, 16500)])
+def test_logits_of_exactly_zero_tie_by_index(batch, k, V):
+    """Head rows of zeros above all others: the float64 keys of their logits are denormal numbers, told apart by the
+    index alone."""
+    D = 128
+    wl = W.Workload("ties", D, D, V, 1, (k,), k, batch, "bf16", "f32", 0.5, seed=47, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    zero = torch.rand(V, generator=gen) < 0.2
+    zero[-1] = True
+    w["head"][0] = -(torch.rand((V, D), generator=gen) + 0.1).to(torch.bfloat16)
+    w["head"][0][zero] = 0
+    w["ln_beta"][0] += 1.0     # states around 1: the other rows' logits are negative
+    state, last = W.make_draft_inputs(wl, gen)
+    step = Step(wl, {key: [t.cuda() for t in v] for key, v in w.items()}, debug=True)
+    step.draft(state.cuda(), last.cuda())
+    torch.cuda.synchronize()
+    s = step.debug_tables()["states"][0].float().cpu()
+    assert float((s @ w["head"][0][~zero][:500].float().t()).max()) < -1e-3
+    want = np.flatnonzero(zero.numpy())[:k]
+    assert (step.cand_tokens.cpu().numpy()[:, :, 0] == want).all()
+    step.close()
