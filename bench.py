@@ -43,7 +43,7 @@ def kernel_name(kid: int) -> str:
     if kid >= 1000:
         mb, rest = divmod(kid - 1000, 100)
         return "head_gemm32_kernel<%d, 2, %d, %s>" % (mb, rest // 2, "true" if rest % 2 else "false")
-    return {0: "head_skinny_kernel", 1: "head_gemm_kernel<2, 1, 8>"}[kid]
+    return {0: "head_skinny_kernel", 1: "head_gemm_kernel<2, 1, 8>", 2: "head_skinny32_kernel"}[kid]
 
 
 def kernel_sources_digest() -> str:

@@ -218,9 +218,9 @@ spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const void* states,
  * roofline reports.  While enabled, spec_draft attaches a pair of HIP events to
  * every contraction launch (they receive that kernel's begin / end time on the
  * caller's stream); nothing else changes.
- *   kernel: 0 = streaming kernel (head_skinny_kernel for up to 16 rows, head_skinny32_kernel for 17 to 32 rows
- *               of at most 4096 columns against a head of at most 65536 rows),
+ *   kernel: 0 = streaming kernel of up to 16 rows, head_skinny_kernel,
  *           1 = narrow dense kernel head_gemm_kernel<2,1,8> (32-row state blocks),
+ *           2 = streaming kernel of 17 to 32 rows, head_skinny32_kernel (with a head, whose length and width it suits),
  *           1000 + 100 * MB + 2 * KT + VT = wide dense kernel head_gemm32_kernel<MB,2,KT,VT>
  *           (32 * MB-row state blocks, per-lane top-k lists of KT entries, VT = 1 with short tiles)
  *   rows, weight_rows, k: the contraction is [rows, k] x [weight_rows, k]^T

@@ -407,7 +407,7 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
   memset(out, 0, sizeof(*out));
   const int kt = k / 32;
   if (skinny_fits(rows, kt) || skinny32_fits(rows, kt, n_head, n_cu)) {
-    out->kernel = 0;
+    out->kernel = rows <= 16 ? 0 : 2;
     out->block_rows = rows <= 16 ? 16 : 32;
     out->tile_rows = 16;
     out->row_blocks = 1;
@@ -502,7 +502,7 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
   if (skinny_fits(R, job.kt) || skinny32_fits(R, job.kt, job.n_head, m->n_cu)) {
     job.nparts = skinny_grid(m->n_cu);
     *nparts = job.nparts;
-    const int slot = prof_slot(m, 0, R, job.n_head + job.n_proj, K);
+    const int slot = prof_slot(m, R <= 16 ? 0 : 2, R, job.n_head + job.n_proj, K);
     HIP_TRY((R <= 16 ? launch_head_skinny : launch_head_skinny32)(job, m->n_cu, st, EV0(slot), EV1(slot)));
     return SPEC_OK;
   }

@@ -29,7 +29,7 @@ def test_17_to_32_rows(case):
     wl = W.Workload("stream32", E, D, V, len(top_k), top_k, Bc, batch, "bf16", "f32", 0.6, seed=23, emb_std=0.3)
     rows = [r for r in wl.rows() if 16 < r <= 32]
     assert B.spec_plan_contraction(20, 768, 65537, 1, 768)["kernel"] == 1   # longer heads: the dense kernel
-    assert rows and all(B.spec_plan_contraction(r, D, V, 1, D)["kernel"] == 0 for r in rows)
+    assert rows and all(B.spec_plan_contraction(r, D, V, 1, D)["kernel"] == 2 for r in rows)
     rep, step, od, ov = run_workload(wl, ln_affine="random", gen_device="cpu")
     assert rep.rows_checked + rep.rows_skipped_below_exempt == sum(wl.rows())
     assert rep.rows_exempt <= 1

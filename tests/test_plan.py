@@ -19,13 +19,16 @@ def check_plan(rows, k, n_head, k_top, n_proj, n_cu):
     assert p["row_blocks"] * p["block_rows"] >= rows > (p["row_blocks"] - 1) * p["block_rows"], what
     # all weight rows: tiles of both matrices, every range owns at least one
     tiles = -(-n_head // p["tile_rows"]) + -(-n_proj // p["tile_rows"])
-    if p["kernel"] != 0:
+    stream = p["kernel"] in (0, 2)
+    assert p["kernel"] != 0 or rows <= 16, what
+    assert p["kernel"] != 2 or (16 < rows <= 32 and 0 < n_head <= 65536 and k <= 4096), what
+    if not stream:
         assert p["tiles"] == tiles, what
         assert p["ranges"] <= p["tiles"], what
         assert p["workgroups"] == p["row_blocks"] * p["ranges"] * p["k_split"], what
     # parts per row: the ranges that hold head tiles
     if n_head == 0:
-        assert p["kernel"] == 0 or p["parts"] == 0, what
+        assert stream or p["parts"] == 0, what
     else:
         assert 1 <= p["parts"] <= p["ranges"], what
         if n_proj == 0:
@@ -33,9 +36,9 @@ def check_plan(rows, k, n_head, k_top, n_proj, n_cu):
     # the workspace holds max(128 * n_cu, rows * n_cu, 16 * n_cu) (row, part) slots
     assert rows * p["parts"] <= max(128 * n_cu, rows * n_cu), what
     assert 0 < p["lds_bytes"] <= LDS_PER_CU, what
-    narrow = p["kernel"] in (1, 2)
+    narrow = p["kernel"] == 1
     if p["k_split"] > 1:
-        assert p["kernel"] != 0 and n_head == 0, what
+        assert not stream and n_head == 0, what
         assert (k // 64) // p["k_split"] >= 8 and p["workgroups"] <= (2 if narrow else 1) * n_cu, what
     if p["proj_apart"]:
         # two launches instead of one: both halves have plans of their own, on the wide kernel
@@ -85,6 +88,12 @@ PINNED = [
     ((1, 4096, 0, 0, 4096), (0, 16, 16, 1, 256, 256, 1)),
     ((1, 4096, 32000, 5, 4096), (0, 16, 16, 1, 256, 256, 1)),
     ((15, 4096, 32000, 2, 0), (0, 16, 16, 1, 256, 256, 1)),
+    ((17, 4096, 32000, 5, 4096), (2, 32, 16, 1, 256, 256, 1)),
+    ((32, 4096, 49152, 1, 0), (2, 32, 16, 1, 256, 256, 1)),
+    ((24, 4096, 0, 0, 4096), (1, 32, 64, 1, 64, 0, 4)),                # a projection alone
+    ((24, 4160, 32000, 5, 4160), (1, 32, 64, 1, 512, 454, 1)),         # rows too wide for the registers
+    ((24, 3072, 65536, 5, 3072), (2, 32, 16, 1, 256, 256, 1)),
+    ((24, 3072, 65537, 5, 3072), (1, 32, 64, 1, 512, 490, 1)),         # longer than the streaming kernel's heads
     ((64, 4096, 0, 0, 4096), (1, 32, 64, 2, 64, 0, 4)),
     ((64, 4096, 32000, 5, 4096), (1213, 64, 144, 1, 252, 223, 1)),
     ((320, 4096, 32000, 3, 4096), (1406, 128, 256, 3, 85, 76, 1)),     # not launched like this: proj_apart
@@ -109,7 +118,7 @@ def test_plans_of_the_benchmark_shapes(args, want):
                                            (768, 16 * 16 * 256, 256), (128, 16 * 4 * 40, 40)])
 @pytest.mark.parametrize("rows", [17, 32])
 def test_short_rows_against_a_long_head_stay_on_the_dense_kernel(rows, k, n_head, n_cu):
-    assert check_plan(rows, k, n_head, 3, k, n_cu)["kernel"] == 0
+    assert check_plan(rows, k, n_head, 3, k, n_cu)["kernel"] == 2
     assert check_plan(rows, k, n_head + 1, 3, 0, n_cu)["kernel"] == 1
 
 
