@@ -325,7 +325,10 @@ extern "C" spec_status_t spec_create(const spec_config_t* cfg, const spec_weight
   m->dyn_ints = 2 * sum_rows + (int64_t)cfg->max_batch * (2 * n + 2) + 64;
   TRY_FREE(dev_alloc(m, &m->dyn_dev, (size_t)m->dyn_ints * 4));
   for (int q = 0; q < spec_model::kDynSlots; ++q) {
-    HIP_TRY_FREE(hipHostMalloc(reinterpret_cast<void**>(&m->dyn_host[q]), (size_t)m->dyn_ints * 4, hipHostMallocDefault));
+    // coherent: a kernel reads the slot, and what an earlier call's kernel left of it in a cache must not be found there
+    // (without the flag that is the environment's choice)
+    HIP_TRY_FREE(hipHostMalloc(reinterpret_cast<void**>(&m->dyn_host[q]), (size_t)m->dyn_ints * 4,
+                               hipHostMallocMapped | hipHostMallocCoherent));
     HIP_TRY_FREE(hipHostGetDevicePointer(reinterpret_cast<void**>(&m->dyn_host_dev[q]), m->dyn_host[q], 0));
     HIP_TRY_FREE(hipEventCreateWithFlags(&m->dyn_ev[q], hipEventDisableTiming));
   }

@@ -202,3 +202,35 @@ def test_dynamic_draft_rejects_bad_arguments():
     torch.cuda.synchronize()
     assert (out[0][0] == -1).all() and (out[0][1] >= 0).all()
     step.close()
+
+
+def test_calls_behind_one_another_read_their_own_row_maps():
+    """Two dozen calls with other trees each, enqueued without a wait: every slot of row maps is used several times,
+    and every call's candidates are those of the call on its own."""
+    wl = W.Workload("in_a_row", 128, 128, 700, 3, (4, 3, 2), 8, 6, "bf16", "f32", 0.6, seed=53, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen, device="cpu")
+    state, last = W.make_draft_inputs(wl, gen)
+    state, last = state.cuda(), last.cuda()
+    step = Step(wl, {k: [t.cuda() for t in v] for k, v in w.items()}, max_batch=wl.batch, max_top_k=wl.top_k)
+    rng = np.random.default_rng(53)
+    calls = []
+    for _ in range(24):
+        trees = [[int(rng.integers(1, k + 1)) for k in wl.top_k] for _ in range(wl.batch)]
+        calls.append((trees, [int(rng.integers(0, min(8, int(np.prod(t))) + 1)) for t in trees]))
+
+    def run(trees, counts):
+        i32 = dict(dtype=torch.int32, device="cuda")
+        out = [torch.empty((wl.batch, 8, 3), **i32), torch.empty((wl.batch, 8), device="cuda"),
+               torch.empty((wl.batch, 8), **i32), torch.empty((wl.batch,), **i32)]
+        B.spec_draft_dynamic(step.model, state, last, trees, counts, *out)
+        return out
+
+    together = [run(*c) for c in calls]
+    torch.cuda.synchronize()
+    for c, got in zip(calls, together):
+        alone = run(*c)
+        torch.cuda.synchronize()
+        assert got[3].tolist() == c[1]
+        assert all(torch.equal(a, b) for a, b in zip(got, alone))
+    step.close()
