@@ -187,7 +187,7 @@ __device__ __forceinline__ void skinny_run(const HeadJob& p, int wg, int G, u32x
   // DPP alone, no transposition through LDS; the price is a 4-way bank conflict on the 16 partial-sum
   // reads per tile, a few hundred LDS cycles in a tile of several thousand)
   const int en = (tid >> 4) & 15, vi = tid & 15;
-  float run_m = SPEC_NEG_INF, run_s = 0.f;
+  float run_m = kLowest, run_s = 0.f;
   float tv[kMaxTopK];
   int32_t ti[kMaxTopK];
 #pragma unroll
@@ -263,7 +263,7 @@ __device__ __forceinline__ void skinny_run(const HeadJob& p, int wg, int G, u32x
   // ---- merge the 16 residue lists of each row (16 consecutive lanes) into the workgroup's partial
   if (tid < 256) {
     const float mx = row16_max(run_m);
-    const float s = row16_sum((run_m > SPEC_NEG_INF) ? run_s * __expf(run_m - mx) : 0.f);
+    const float s = row16_sum(run_s * __expf(run_m - mx));
     const int64_t slot = (int64_t)en * p.nparts + wg;
     if (en < R && vi == 0) {
       p.part.m[slot] = mx;

@@ -29,16 +29,17 @@ def _first_stage(dtype, V, batch, k, edit):
     return got, W.to_numpy_f32(w["head"][0])
 
 
-# 17 to 32 rows (streaming kernel), float32: two tiles of weight rows and more per workgroup, so that finite logits
+# up to 16 and 17 to 32 rows (streaming kernels), float32: two tiles of weight rows and more per workgroup, so that finite logits
 # follow in the same thread
-STREAM = [("bf16", 20500, 20, 3), ("f32", 20500, 5, 3)]
+STREAM = [("bf16", 20500, 20, 3), ("bf16", 20500, 3, 3), ("f32", 20500, 5, 3),
+          ("bf16", 3001, 50, 3), ("bf16", 20500, 50, 3), ("bf16", 20500, 100, 3)]   # and the two dense kernels
 
 
 @pytest.mark.parametrize("dtype,V,batch,k", STREAM)
 def test_logits_of_minus_infinity_count_nothing(dtype, V, batch, k):
     low = np.zeros(V, bool)
-    low[:4096] = True      # the first tiles of every workgroup
-    low[5000::7] = True
+    low[:min(4096, V // 2)] = True      # the first tiles of every workgroup
+    low[V // 4::7] = True
 
     def edit(head):
         head[torch.from_numpy(low)] = -BIG
@@ -58,7 +59,9 @@ def test_logits_of_minus_infinity_count_nothing(dtype, V, batch, k):
 
 @pytest.mark.parametrize("at", [0, -1], ids=["first", "last"])
 @pytest.mark.parametrize("dtype,V,batch,k", [("bf16", 4097, 20, 2), ("bf16", 9, 32, 3), ("bf16", 20500, 17, 2),
-                                             ("f32", 65, 3, 3), ("f32", 1024, 17, 2), ("f32", 20500, 2, 2)])
+                                             ("f32", 65, 3, 3), ("f32", 1024, 17, 2), ("f32", 20500, 2, 2),
+                                             ("bf16", 4097, 3, 2), ("bf16", 9, 16, 3), ("bf16", 3004, 50, 2),
+                                             ("bf16", 20500, 50, 2), ("bf16", 20500, 100, 2)])
 def test_a_logit_that_is_nan_shows_in_its_rows_sum(dtype, V, batch, k, at):
     """Also where it is the only logit of its thread, or (the last row of a ragged tile) of its workgroup."""
     def edit(head):
