@@ -175,7 +175,8 @@ __global__ __launch_bounds__(kS32Waves * 64) void head_skinny32_kernel(HeadJob p
   // ---- merge the 16 residue lists of each row (16 consecutive lanes) into the workgroup's partial
   if (tid < 512) {
     const float mx = row16_max(run_m);
-    const float s = row16_sum(run_s * __expf(run_m - mx));
+    // (always true; the product is rounded before it is added, not fused into one of the sum's two sides)
+    const float s = row16_sum(run_m > SPEC_NEG_INF ? run_s * __expf(run_m - mx) : 0.f);
     const int64_t slot = (int64_t)en * p.nparts + wg;
     if (en < R && vi == 0) {
       p.part.m[slot] = mx;
