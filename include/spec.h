@@ -166,7 +166,8 @@ spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, const int32
  * workspace.  The call allocates nothing and frees nothing (no hipMalloc / hipFree, no
  * allocating library routine); it only enqueues kernels on hip_stream.
  *   Limit: the workspace of THIS call (it grows with batch * prod(top_k) and with the widths)
- *   must fit the array: SPEC_ESHAPE otherwise, before anything is enqueued.  A 7B-shaped
+ *   must fit the array: SPEC_ESHAPE otherwise, before anything is enqueued.  (A float32 model's call is
+ *   counted with 4 * rows * vocab bytes for the logits of its widest stage.)  A 7B-shaped
  *   model with one sequence and the 5/3/2 tree needs 1.2 MB.
  *   The current device must be the model's (SPEC_EINVAL).
  *   Every call on a GPU, from any model and any stream, shares that GPU's array (each GPU the

@@ -22,10 +22,11 @@ namespace specdraft {
 
 constexpr int kS32Waves = 16;
 constexpr int kS32Steps = 8;   // K-steps (of 32) per wave -> K <= 4096
-// Longest head.  With 128256 rows of 3072 the dense kernel's ranges hold four to five tiles and lose little to the
-// uneven last one: 150 us against 128 here, under 1 % of that model's draft, and the projection's sums, split over 16
-// waves, round differently (closer to 64 bits, 0.9 .. 1.0 of the error), which reorders near-tied ones among its
-// candidates: not worth it there.
+// Longest head: a line of results, not of speed.  Against 128256 rows of 3072 this kernel takes 128 us and the dense one
+// 150, but its sums over 16 slices of K (error against 64 bits 0.9 .. 1.0 of the other's) turned the order of near-tied
+// candidates of a 6, 4, 3, 2 tree in 1 of 10 seeds: 3 % of the whole numbers of its token tree, where 1 % is the bound
+// that such a draft is held to.  With 32000 and 49152 rows ten seeds stayed within it; between 65536 and 128256 nothing
+// was measured.
 constexpr int kS32MaxHead = 65536;
 // slots of one wave's 16x16 accumulator in LDS: the four 16-lane groups are 20 slots apart, so that the
 // 16 threads that read one state row's sums hit distinct banks

@@ -863,7 +863,7 @@ static spec_status_t carve_static(const spec_model* m, unsigned char* base, int 
   ws->tok = reinterpret_cast<int32_t*>(take((size_t)sum_rows_k * 4));
   ws->logp = reinterpret_cast<float*>(take((size_t)sum_rows_k * 4));
   ws->lse = reinterpret_cast<float*>(take((size_t)sum_rows * 4));
-  // (the limit callers know counts a float32 call's logit rows)
+  // (not used: the documented limit counts a float32 call's logit rows, and what it refused stays refused)
   if (!m->bf16) take((size_t)max_rows * V * 4);
   if (!fits)
     return fail(SPEC_ESHAPE, "spec_draft_static: this call needs %zu bytes of workspace, the static array holds %d "
