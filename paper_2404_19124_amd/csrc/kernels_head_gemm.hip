@@ -167,6 +167,11 @@ static double plan_cost(const GemmPlan& pl, int n_head, int n_proj) {
   return per_tile * ((total + pl.n_ranges - 1) / pl.n_ranges) / pl.ksplit;
 }
 
+double dense_head_cost(int R, int k_top, int n_head, int kt, int n_cu) {
+  const GemmPlan pl = plan_gemm(R, k_top, n_head, 0, kt, n_cu);
+  return pl.ts != 16 ? 0.0 : plan_cost(pl, n_head, 0);
+}
+
 // Head and next projection in ONE launch share the state reads, but their tiles form one list, and a list
 // that is a little longer than a multiple of the ranges makes the launch one tile longer for a few ranges
 // (320 rows against 125 + 16 tiles: 128 ranges, 13 of them with two tiles).  Then two launches are cheaper:

@@ -126,10 +126,24 @@ constexpr int kMaxKSplit = 4;
 GemmPlan plan_gemm(int R, int k_top, int n_head, int n_proj, int kt, int n_cu);
 // true: the head and the next projection are cheaper as two launches than as one
 bool plan_projection_apart(int R, int k_top, int n_head, int n_proj, int kt, int n_cu);
+// what plan_gemm expects of a head launched alone, in units of one 96-row tile; 0: it shortens its tiles
+double dense_head_cost(int R, int k_top, int n_head, int kt, int n_cu);
 // dry != nullptr: nothing is launched (no HIP call at all); the result says whether a kernel
 // instance exists for the plan, and *dry receives its LDS bytes.
 hipError_t launch_head_gemm(const HeadJob& job, const GemmPlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr, size_t* dry = nullptr);
+
+// A head alone (top-k partials, no projection in the launch) against more than 64 rows: 256-weight-row tiles x blocks of
+// 32 * block state rows.  block = 0: not for this kernel.  nparts = n_ranges.
+struct TilePlan {
+  int block, kcap;           // block height / 32, capacity of the per-lane top-k lists
+  int m_tiles, n_tiles;      // blocks of state rows, tiles of weight rows
+  int n_ranges;              // contiguous ranges of the tiles, one workgroup per range and block
+};
+TilePlan plan_tile(int R, int k_top, int n_head, int kt, int n_cu);
+size_t tile_lds_bytes(const TilePlan& plan);
+hipError_t launch_head_tile(const HeadJob& job, const TilePlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
+                            hipEvent_t ev_stop = nullptr);
 
 // ---- contraction, float32 ----------------------------------------------------
 // out[r * ldo + v] = sum_k a[r * K + k] * w[v * K + k]

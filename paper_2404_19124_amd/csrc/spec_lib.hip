@@ -453,6 +453,26 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
   return SPEC_OK;
 }
 
+extern "C" spec_status_t spec_plan_head(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_cu,
+                                        spec_plan_t* out) {
+  spec_status_t s = spec_plan_contraction(rows, k, n_head, k_top, 0, n_cu, out);
+  if (s != SPEC_OK) return s;
+  const TilePlan tp = plan_tile(rows, k_top, n_head, k / 32, n_cu);
+  if (!tp.block) return SPEC_OK;
+  memset(out, 0, sizeof(*out));
+  out->kernel = 100 + 10 * tp.block + tp.kcap;
+  out->block_rows = 32 * tp.block;
+  out->tile_rows = 256;
+  out->row_blocks = tp.m_tiles;
+  out->ranges = tp.n_ranges;
+  out->tiles = tp.n_tiles;
+  out->parts = tp.n_ranges;
+  out->k_split = 1;
+  out->workgroups = tp.m_tiles * tp.n_ranges;
+  out->lds_bytes = (int32_t)tile_lds_bytes(tp);
+  return SPEC_OK;
+}
+
 extern "C" spec_status_t spec_copy_probe(const void* src, void* dst, int64_t bytes, void* hip_stream) {
   if (!src || !dst) return fail(SPEC_EINVAL, "a required pointer is NULL");
   if (bytes <= 0 || bytes % 16) return fail(SPEC_EINVAL, "bytes = %lld must be a positive multiple of 16", (long long)bytes);
@@ -508,6 +528,18 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
     const int slot = prof_slot(m, R <= 16 ? 0 : 2, R, job.n_head + job.n_proj, K);
     HIP_TRY((R <= 16 ? launch_head_skinny : launch_head_skinny32)(job, m->n_cu, st, EV0(slot), EV1(slot)));
     return SPEC_OK;
+  }
+  if (stage >= 0 && proj_stage < 0 && !out_head && !b_rowmajor) {
+    const TilePlan tp = plan_tile(R, k_top, job.n_head, job.kt, m->n_cu);
+    if (tp.block) {
+      job.nparts = tp.n_ranges;
+      *nparts = job.nparts;
+      if ((int64_t)R * job.nparts > ws.part_rows_parts)
+        return fail(SPEC_ESHAPE, "internal: partial workspace too small (%d rows x %d parts)", R, job.nparts);
+      const int slot = prof_slot(m, 100 + 10 * tp.block + tp.kcap, R, job.n_head, K);
+      HIP_TRY(launch_head_tile(job, tp, st, EV0(slot), EV1(slot)));
+      return SPEC_OK;
+    }
   }
   GemmPlan pl = plan_gemm(R, k_top, job.n_head, job.n_proj, job.kt, m->n_cu);
   // the wide kernel wants tiled states; the narrow one gathers row-major rows itself
