@@ -45,7 +45,7 @@ __device__ __forceinline__ void skinny_prefetch(const HeadJob& p, int wg, int G,
     const int tile = wg + d * G;
     if (tile < total) {
       const u32x4* base =
-          tile < p.vt_head ? wh + (int64_t)tile * kt * 64 : wp + (int64_t)(tile - p.vt_head) * kt * 64;
+          tile < p.vt_head ? wh + tile * packed_tile_slots(kt) : wp + (tile - p.vt_head) * packed_tile_slots(kt);
       const u32x4* ptr = base + (int64_t)s0 * 64 + lane;
 #pragma unroll
       for (int t = 0; t < NS; ++t)
@@ -159,7 +159,7 @@ __device__ __forceinline__ void skinny_run(const HeadJob& p, int wg, int G, u32x
   const u32x4* wh = static_cast<const u32x4*>(p.w_head);
   const u32x4* wp = static_cast<const u32x4*>(p.w_proj);
   auto tile_ptr = [&](int tile) -> const u32x4* {
-    const u32x4* base = tile < p.vt_head ? wh + (int64_t)tile * kt * 64 : wp + (int64_t)(tile - p.vt_head) * kt * 64;
+    const u32x4* base = tile < p.vt_head ? wh + tile * packed_tile_slots(kt) : wp + (tile - p.vt_head) * packed_tile_slots(kt);
     return base + (int64_t)s0 * 64 + lane;
   };
 

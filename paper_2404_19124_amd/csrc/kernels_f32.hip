@@ -9,7 +9,7 @@ namespace specdraft {
 
 // ---- tiling of a row-major bf16 matrix into matrix-core fragment order -------
 __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
-                                                        int n_rows, int kt, int64_t n_slots, int zero_pad) {
+                                                        int n_rows, int kt, int64_t n_slots, int weights) {
   const int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (slot >= n_slots) return;
   const int lane = (int)(slot & 63);
@@ -17,19 +17,20 @@ __global__ __launch_bounds__(256) void pack_bf16_kernel(const uint4* __restrict_
   const int t = (int)(frag % kt);
   const int64_t nt = frag / kt;
   const int64_t row = nt * 16 + (lane & 15);
+  uint4* const d = dst + (weights ? nt * packed_tile_slots(kt) : nt * kt * 64) + t * 64 + lane;
   if (row < n_rows) {
-    dst[slot] = src[row * (kt * 4) + t * 4 + (lane >> 4)];   // 8 bf16 = one 16-byte unit
-  } else if (zero_pad) {
-    dst[slot] = make_uint4(0, 0, 0, 0);
+    *d = src[row * (kt * 4) + t * 4 + (lane >> 4)];   // 8 bf16 = one 16-byte unit
+  } else if (weights) {
+    *d = make_uint4(0, 0, 0, 0);
   }
 }
 
-hipError_t launch_pack_bf16(const void* src, void* dst, int n_rows, int k, bool zero_pad, hipStream_t st) {
+hipError_t launch_pack_bf16(const void* src, void* dst, int n_rows, int k, bool weights, hipStream_t st) {
   const int kt = k / 32;
   const int64_t n_slots = (int64_t)((n_rows + 15) / 16) * kt * 64;
   const unsigned grid = (unsigned)((n_slots + 255) / 256);
   hipLaunchKernelGGL(pack_bf16_kernel, dim3(grid), dim3(256), 0, st, static_cast<const uint4*>(src),
-                     static_cast<uint4*>(dst), n_rows, kt, n_slots, zero_pad ? 1 : 0);
+                     static_cast<uint4*>(dst), n_rows, kt, n_slots, weights ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256, 2) void head_gemm_kernel(GemmArgs p) {
     for (int ni = 0; ni < NI; ++ni) {
       ntv[ni] = (ntile * 4 + wave) * NI + ni;
       const int ntc = min(ntv[ni], p.nt_total[mat] - 1);
-      wp[ni] = p.w[mat] + (int64_t)ntc * kt * 64 + (int64_t)slab0 * KS * 64 + lane;
+      wp[ni] = p.w[mat] + ntc * packed_tile_slots(kt) + (int64_t)slab0 * KS * 64 + lane;
     }
   };
 
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
     for (int nb = 0; nb < NB; ++nb) {
       ntv[nb] = ntile * ts + wave * NI + 2 * nb;  // first 16-row tile of the block
       const int ntc = min(ntv[nb] + (c32 >> 4), tend - 1);
-      wp[nb] = p.w[mat] + (int64_t)ntc * kt * 64 + (int64_t)slab0 * KS * 64 + half * 16 + (c32 & 15);
+      wp[nb] = p.w[mat] + ntc * packed_tile_slots(kt) + (int64_t)slab0 * KS * 64 + half * 16 + (c32 & 15);
     }
   };
 

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kS32Waves * 64) void head_skinny32_kernel(HeadJob p
   const u32x4* wp = static_cast<const u32x4*>(p.w_proj);
   auto tile_slice = [&](int tile) {
     const int t = min(tile, total - 1);
-    const u32x4* base = t < p.vt_head ? wh + (int64_t)t * kt * 64 : wp + (int64_t)(t - p.vt_head) * kt * 64;
+    const u32x4* base = t < p.vt_head ? wh + t * packed_tile_slots(kt) : wp + (t - p.vt_head) * packed_tile_slots(kt);
     return weight_buffer(base + (int64_t)s0 * 64, tile < total ? ns * 1024 : 0);
   };
 

@@ -109,13 +109,14 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
   for (int i = 0; i < G::SP; ++i) s_off[i] = min(min(i * kWaves + wave, G::SF - 1), mt_last) * kt * 1024;
   // The cursor moves by whole groups of kSteps steps: scalar work at every step would leave the matrix cores waiting.
   int c_step = 0, c_tile = t0;   // first step of the group that is copied, and its tile
+  const int tile_bytes = (int)packed_tile_slots(kt) * 16;
   auto group_bufs = [&](auto& w, auto& s) {
     const int last = min(kWF, p.nt_total - c_tile * kWF) - 1;
 #pragma unroll
-    for (int i = 0; i < G::WP; ++i) w_off[i] = min(i * kWaves + wave, last) * kt * 1024;
+    for (int i = 0; i < G::WP; ++i) w_off[i] = min(i * kWaves + wave, last) * tile_bytes;
     w = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<unsigned char*>(wb + (int64_t)c_tile * kWF * kt * 1024 + c_step * 1024), 0,
-        (last + 1) * kt * 1024 - c_step * 1024, 0x00020000);
+        const_cast<unsigned char*>(wb + (int64_t)c_tile * kWF * tile_bytes + c_step * 1024), 0,
+        (last + 1) * tile_bytes - c_step * 1024, 0x00020000);
     s = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(sb + c_step * 1024), 0,
                                           (mt_last + 1) * kt * 1024 - c_step * 1024, 0x00020000);
   };

@@ -25,6 +25,11 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 //     address (in 16-byte slots) = (nt * (K/32) + t) * 64 + lane
 // so that a wave reads one fragment as one fully coalesced 1 KiB access.  Rows
 // beyond N are zero (weights) or unspecified (states).
+// Weight tiles lie four fragments further apart than they are long: tile nt starts at slot nt * packed_tile_slots(K / 32).
+// At K = 4096 a tile is 128 KiB, and workgroups that walk K in step, or start their tiles together, would ask the same
+// few channels and cache sets.  Launches of 32000 rows x 4096, us, tiles end to end / 4 KiB apart / 8 KiB:  1 row (with
+// the projection) 47.0 / 46.1 / 45.7, 15 rows 43.5 / 42.2 / 42.4, 24 rows of 49152 67.4 / 66.4 / 66.7, 384 rows 102 / 101 / 98;
+// 1 KiB apart, off the 4 KiB page, 64 and 96 rows lose 4 %.
 // ---------------------------------------------------------------------------
 
 // Partial result of a head contraction for one (row, part): the running maximum
@@ -38,9 +43,11 @@ struct Partials {
   int32_t* idx;
 };
 
+constexpr int64_t packed_tile_slots(int kt) { return (int64_t)(kt + 4) * 64; }
+
 // ---- packing --------------------------------------------------------------
-// src row-major [n_rows][k] bf16 -> dst packed with ceil(n_rows/16) row tiles.
-hipError_t launch_pack_bf16(const void* src, void* dst, int n_rows, int k, bool zero_pad, hipStream_t st);
+// src row-major [n_rows][k] bf16 -> dst packed with ceil(n_rows/16) row tiles, as weights or as states.
+hipError_t launch_pack_bf16(const void* src, void* dst, int n_rows, int k, bool weights, hipStream_t st);
 
 // ---- contraction, bf16 on the matrix cores --------------------------------
 // Optional prologue of the streaming kernel for the FIRST stage of a draft with one or two

@@ -284,7 +284,8 @@ extern "C" spec_status_t spec_create(const spec_config_t* cfg, const spec_weight
     if (same_proj >= 0) m->proj[i] = m->proj[same_proj];
     if (same_head >= 0) m->head[i] = m->head[same_head];
     if (m->bf16) {
-      const size_t pb = (size_t)((D + 15) / 16) * 16 * in * 2, hb = (size_t)((V + 15) / 16) * 16 * D * 2;
+      const size_t pb = (size_t)((D + 15) / 16) * packed_tile_slots(in / 32) * 16;
+      const size_t hb = (size_t)((V + 15) / 16) * packed_tile_slots(D / 32) * 16;
       if (same_proj < 0) {
         TRY_FREE(dev_alloc(m, &m->proj[i], pb));
         HIP_TRY_FREE(launch_pack_bf16(w->proj[i], m->proj[i], D, in, true, stream));
