@@ -67,11 +67,13 @@ size_t skinny_lds_bytes(int R, int kt) { return skinny_state_bytes(R, kt) + kSki
 hipError_t launch_head_skinny(const HeadJob& job, int n_cu, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const size_t smem = skinny_lds_bytes(job.R, job.kt);
   const int grid = skinny_grid(n_cu);
-  // K = 512 * NS gets an exact instantiation with as many tiles in flight as 16 fragments allow
+  // K = 512 * NS gets an exact instantiation.  About 128 KiB of a CU in flight (8 fragments of a wave) saturate HBM; twice as
+  // much only queues there, and the states queue behind it.  Launches, us, with twice that and now: 32000 rows of K = 4096
+  // 42.4 -> 41.2, with the projection 46.0 -> 45.5; 32003 of 2048 22.8 -> 21.8; 128256 of 2048 80 -> 78.7; 128256 of 3072 119 -> 118.
   switch (job.kt % kSkinnyWaves == 0 ? job.kt / kSkinnyWaves : 0) {
-    case 4: return launch_skinny_t<4, 4, true>(job, grid, smem, st, ev_start, ev_stop);
-    case 6: return launch_skinny_t<6, 2, true>(job, grid, smem, st, ev_start, ev_stop);
-    case 8: return launch_skinny_t<8, 2, true>(job, grid, smem, st, ev_start, ev_stop);
+    case 4: return launch_skinny_t<4, 2, true>(job, grid, smem, st, ev_start, ev_stop);
+    case 6: return launch_skinny_t<6, 1, true>(job, grid, smem, st, ev_start, ev_stop);
+    case 8: return launch_skinny_t<8, 1, true>(job, grid, smem, st, ev_start, ev_stop);
     case 10: return launch_skinny_t<10, 1, true>(job, grid, smem, st, ev_start, ev_stop);
     case 16: return launch_skinny_t<16, 1, true>(job, grid, smem, st, ev_start, ev_stop);
     default: return launch_skinny_t<kSkinnySteps, 1, false>(job, grid, smem, st, ev_start, ev_stop);
