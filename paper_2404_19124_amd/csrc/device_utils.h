@@ -50,6 +50,13 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
   return u >> 16;
 }
 
+// two of them in one word, the first in the low half: one instruction on gfx950 (the same rounding; a NaN stays one)
+__device__ __forceinline__ uint32_t f32_to_bf16_pair(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 p = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
+  return __builtin_bit_cast(uint32_t, p);
+}
+
 // Total order used everywhere a "best" is chosen: larger value first, then
 // smaller index.  true when (v1, i1) comes strictly before (v2, i2).
 __device__ __forceinline__ bool before(float v1, int32_t i1, float v2, int32_t i2) {
@@ -183,6 +190,24 @@ __device__ __forceinline__ float block_sum(float x, float* scratch) {
   float t = 0.f;
   for (int j = 0; j < nw; ++j) t += scratch[j];
   return t;
+}
+// the same for N values at once; `scratch` needs N * (NT/64) words that nobody has used before in this workgroup
+template <int NT, int N>
+__device__ __forceinline__ void block_sums(float (&x)[N], float* scratch) {
+  const int w = threadIdx.x >> 6, nw = NT / 64;
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = wave_sum(x[i]);
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) scratch[i * nw + w] = x[i];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    float t = 0.f;
+    for (int j = 0; j < nw; ++j) t += scratch[i * nw + j];
+    x[i] = t;
+  }
 }
 template <int NT>
 __device__ __forceinline__ float block_max(float x, float* scratch) {

@@ -7,10 +7,16 @@
 
 namespace specdraft {
 
-// NCH = 8-element chunks per thread held in registers (D <= NCH * NT * 8).
-template <bool BF16, int NCH, int NT>
+// Parents from which siblings share a workgroup: one for every CU.  With fewer, what a CU saves others do not lend (a child is
+// 2 us of arithmetic on one CU): 96 parents of 4 children 11.9 us together, 10.2 one by one; 16 of 6: 11.2 and 8.5; 64 of 5:
+// 11.6 and 10.9; 256 of 3: 12.8 and 13.8; 320 of 3: 16.9 and 17.1; 768 of 3: 21.0 and 29.4 (D = 4096, 13B: 5120).
+constexpr int kSiblingParents = 256;
+
+// K: the width that registers are kept for, see stage_rows; NCH = 8-element chunks per thread (D <= NCH * NT * 8).  One
+// row per workgroup (every sibling repeats its parent's merge).
+template <bool BF16, int K, int NCH, int NT>
 __global__ __launch_bounds__(NT) void stage_kernel(StageJob j) {
-  __shared__ __align__(16) float lds[32 + (NT / 256) * kMergeLds];
+  __shared__ __align__(16) float lds[32 + kMergeLds];
   int r = blockIdx.x;
   if (j.xcd_rows) {
     // Workgroup ids go round-robin over the 8 XCDs, and a row's state is stored as one 16-byte slot in
@@ -21,22 +27,73 @@ __global__ __launch_bounds__(NT) void stage_kernel(StageJob j) {
     r = (((s >> 4) << 3) + xcd) * 16 + (s & 15);
     if (r >= j.R) return;
   }
-  stage_row<BF16, NCH, NT>(j, r, lds);
+  int parent = r / j.k_prev, rank = r - parent * j.k_prev;
+  if (j.row_parent) {  // per-sequence trees: the host laid the rows out
+    parent = j.row_parent[r];
+    rank = j.row_rank[r];
+  }
+  stage_rows<BF16, K, NCH, NT, 1>(j, parent, rank, r, 1, lds);
+}
+
+// KC siblings per workgroup, `per` workgroups per parent (uniform trees, packed states).  The merge and the parent's
+// projection are read and computed once for the siblings, which are a third to a half of a row's instructions.
+template <int K, int NCH, int NT, int KC>
+__global__ __launch_bounds__(NT) void stage_siblings_kernel(StageJob j, int per, int group) {
+  __shared__ __align__(16) float lds[32 * KC + kMergeLds];
+  // `group` parents have whole 16-row tiles of children: they run on one XCD (see above)
+  const int xcd = blockIdx.x & 7, s = blockIdx.x >> 3, span = group * per;
+  const int g = s / span, in = s - g * span, pin = in / per;
+  const int parent = (g * 8 + xcd) * group + pin;
+  const int rank0 = (in - pin * per) * KC, r0 = parent * j.k_prev + rank0;
+  if (r0 >= j.R) return;
+  stage_rows<true, K, NCH, NT, KC>(j, parent, rank0, r0, min(KC, j.k_prev - rank0), lds);
+}
+
+template <int K, int NCH, int NT>
+static hipError_t launch_siblings(const StageJob& job, hipStream_t st) {
+  constexpr int KC = K <= 4 ? K : K / 2;   // (widths 5 and 6: 3 of 6, 7 and 8: 4 of 8)
+  const int k = job.k_prev, parents = job.R / k, per = (k + KC - 1) / KC;
+  const int group = 16 / ((k & 1) ? 1 : (k & 2) ? 2 : (k & 4) ? 4 : 8);
+  const int groups = (parents + group - 1) / group;
+  const dim3 grid((groups + 7) / 8 * 8 * group * per);
+  hipLaunchKernelGGL((stage_siblings_kernel<K, NCH, NT, KC>), grid, dim3(NT), 0, st, job, per, group);
+  return hipGetLastError();
+}
+
+template <bool BF16, int K, int NCH, int NT>
+static hipError_t launch_stage_n(const StageJob& job, hipStream_t st) {
+  if constexpr (BF16 && K >= 2 && NCH <= 2)
+    if (job.xcd_rows && !job.row_parent && job.R / job.k_prev >= kSiblingParents) return launch_siblings<K, NCH, NT>(job, st);
+  // tile-per-XCD order: whole groups of 8 tiles, the workgroups past the last row leave at once
+  const dim3 grid(job.xcd_rows ? (job.R + 127) / 128 * 128 : job.R);
+  hipLaunchKernelGGL((stage_kernel<BF16, K, NCH, NT>), grid, dim3(NT), 0, st, job);
+  return hipGetLastError();
+}
+
+template <bool BF16, int K>
+static hipError_t launch_stage_k(const StageJob& job, hipStream_t st) {
+  const int nchunk = job.D / 8;
+  // 512 threads per row from D = 4096 on: the row's LayerNorm / GELU arithmetic is what a workgroup spends its
+  // time on once its loads are back, and eight waves halve it (7B batch 1: -1 us per step; 7-stage chain: -3.6 us)
+  if (nchunk <= 256) return launch_stage_n<BF16, K, 1, 256>(job, st);
+  if (nchunk <= 512) return launch_stage_n<BF16, K, 1, 512>(job, st);
+  if (nchunk <= 1024) return launch_stage_n<BF16, K, 2, 512>(job, st);
+  if (nchunk <= 2048) return launch_stage_n<BF16, K, 4, 512>(job, st);
+  return hipErrorInvalidValue;
 }
 
 template <bool BF16>
 static hipError_t launch_stage_t(const StageJob& job, hipStream_t st) {
-  const int nchunk = job.D / 8;
-  // tile-per-XCD order: whole groups of 8 tiles, the workgroups past the last row leave at once
-  const dim3 grid(job.xcd_rows ? (job.R + 127) / 128 * 128 : job.R);
-  // 512 threads per row from D = 4096 on: the row's LayerNorm / GELU arithmetic is what a workgroup spends its
-  // time on once its loads are back, and eight waves halve it (7B batch 1: -1 us per step; 7-stage chain: -3.6 us)
-  if (nchunk <= 256) hipLaunchKernelGGL((stage_kernel<BF16, 1, 256>), grid, dim3(256), 0, st, job);
-  else if (nchunk <= 512) hipLaunchKernelGGL((stage_kernel<BF16, 1, 512>), grid, dim3(512), 0, st, job);
-  else if (nchunk <= 1024) hipLaunchKernelGGL((stage_kernel<BF16, 2, 512>), grid, dim3(512), 0, st, job);
-  else if (nchunk <= 2048) hipLaunchKernelGGL((stage_kernel<BF16, 4, 512>), grid, dim3(512), 0, st, job);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  if (job.stage == 0) return launch_stage_k<BF16, 0>(job, st);
+  switch (job.k_prev) {
+    case 1: return launch_stage_k<BF16, 1>(job, st);
+    case 2: return launch_stage_k<BF16, 2>(job, st);
+    case 3: return launch_stage_k<BF16, 3>(job, st);
+    case 4: return launch_stage_k<BF16, 4>(job, st);
+    case 5:
+    case 6: return launch_stage_k<BF16, 6>(job, st);
+    default: return launch_stage_k<BF16, 8>(job, st);
+  }
 }
 
 hipError_t launch_stage(const StageJob& job, hipStream_t st) {

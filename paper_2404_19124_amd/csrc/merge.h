@@ -161,81 +161,94 @@ __device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t
 constexpr int kMergeWave = 2 + 2 * kMaxTopK;   // words per wave: max, sum-exp, k keys
 constexpr int kMergeLds = 4 * kMergeWave;
 constexpr int kNoRank = 1 << 20;
+// What a thread reads for it, its own part's list: to be requested before anything else that a caller wants from memory.
 template <int K>
-__device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_t row, int nparts, int k,
-                                                     float& out_val, int32_t& out_idx, int& rank,
-                                                     float& lse, float* lds) {
-  const int gt = opaque_tid() & 255, lane = gt & 63, w = gt >> 6;
-  const float* pm = p.m + row * nparts;
-  const float* ps = p.s + row * nparts;
-  const float* pv = p.val + row * (int64_t)nparts * k;
-  const int32_t* pi = p.idx + row * (int64_t)nparts * k;
-
-  float tv[K];
-  int32_t ti[K];
-  float run_m = SPEC_NEG_INF, run_s = 0.f;
-  {
-    const bool ok = gt < nparts;
-    const int pc = ok ? gt : nparts - 1;
-    const float m_ = pm[pc], s_ = ps[pc];
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const int jc = j < k ? j : k - 1;
-      const float v_ = pv[(int64_t)pc * k + jc];
-      const int32_t i_ = pi[(int64_t)pc * k + jc];
-      const bool okj = ok && j < k;
-      tv[j] = okj ? v_ : SPEC_NEG_INF;
-      ti[j] = okj ? i_ : kIdxNone;
-    }
-    if (ok) { run_m = m_; run_s = s_; }
-  }
-  for (int part = gt + 256; part < nparts; part += 256) {   // more parts than threads: fold the rest in
-    const float m_ = pm[part], s_ = ps[part];
-    if (m_ > SPEC_NEG_INF) {
-      const float mn = fmaxf(run_m, m_);
-      run_s = run_s * __expf(run_m - mn) + s_ * __expf(m_ - mn);
-      run_m = mn;
-    }
-    for (int j = 0; j < k; ++j) {
-      const float v_ = pv[(int64_t)part * k + j];
-      const int32_t i_ = pi[(int64_t)part * k + j];
-      if (before(v_, i_, tv[K - 1], ti[K - 1])) list_insert<K>(tv, ti, v_, i_);
-    }
-  }
-
-  // ---- this wave's 64 parts
-  const float wm = wave_max(run_m);
-  const float wsum = wave_sum(run_m > SPEC_NEG_INF ? run_s * __expf(run_m - wm) : 0.f);
-  float wv[K];
-  int32_t wi[K];
+struct MergePart {
+  float m, s, v[K];
+  int32_t i[K];
+};
+template <int K>
+__device__ __forceinline__ void group_merge_load(const Partials& p, int64_t row, int nparts, int k, MergePart<K>& x) {
+  const int pc = min(opaque_tid() & 255, nparts - 1);   // (past the last part: that one again, masked below)
+  x.m = p.m[row * nparts + pc];
+  x.s = p.s[row * nparts + pc];
+  const float* pv = p.val + (row * nparts + pc) * (int64_t)k;
+  const int32_t* pi = p.idx + (row * nparts + pc) * (int64_t)k;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    wv[j] = SPEC_NEG_INF;
-    wi[j] = kIdxNone;
-    if (j < k) {
-      float bv = tv[0];
-      int32_t bi = ti[0];
-      wave_best(bv, bi);
-      if (ti[0] == bi && tv[0] == bv) {  // the owner of the winner pops it
-#pragma unroll
-        for (int q = 0; q + 1 < K; ++q) { tv[q] = tv[q + 1]; ti[q] = ti[q + 1]; }
-        tv[K - 1] = SPEC_NEG_INF;
-        ti[K - 1] = kIdxNone;
-      }
-      wv[j] = bv;
-      wi[j] = bi;
-    }
+    const int jc = j < k ? j : k - 1;
+    x.v[j] = pv[jc];
+    x.i[j] = pi[jc];
   }
+}
+// ONE: the whole workgroup wants the same row, `lds` is the workgroup's and nobody has used it before: the first 256
+// threads merge, the others wait at the barrier (they would only take issue slots: DPP chains of eight waves on four
+// SIMDs ran half as fast).
+template <int K, bool ONE>
+__device__ __forceinline__ void group_merge_loaded(const MergePart<K>& x, const Partials& p, int64_t row, int nparts, int k,
+                                                 float& out_val, int32_t& out_idx, int& rank,
+                                                 float& lse, float* lds) {
+  const int tid = opaque_tid(), gt = tid & 255, lane = gt & 63, w = gt >> 6;
 
-  // ---- the four waves' results through LDS
-  float* mine = lds + w * kMergeWave;
-  __syncthreads();                                    // scratch may still be read from an earlier call
-  if (lane == 0) {
-    mine[0] = wm;
-    mine[1] = wsum;
+  if (!ONE) __syncthreads();                          // scratch may still be read from an earlier call
+  if (!ONE || __builtin_amdgcn_readfirstlane(tid >> 8) == 0) {
+    uint64_t tk[K];   // the thread's list as keys (best_key)
+    const bool ok = gt < nparts;
+    float run_m = ok ? x.m : SPEC_NEG_INF, run_s = ok ? x.s : 0.f;
+    const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
 #pragma unroll
-    for (int j = 0; j < K; ++j)   // (empty entries are told apart, so that every candidate has its own rank)
-      reinterpret_cast<uint64_t*>(mine + 2)[j] = best_key(wv[j], wi[j] == kIdxNone ? kIdxNone - (w * kMaxTopK + j) : wi[j]);
+    for (int j = 0; j < K; ++j) tk[j] = ok && j < k ? best_key(x.v[j], x.i[j]) : kEmpty;
+    const float* pm = p.m + row * nparts;
+    const float* ps = p.s + row * nparts;
+    const float* pv = p.val + row * (int64_t)nparts * k;
+    const int32_t* pi = p.idx + row * (int64_t)nparts * k;
+    for (int part = gt + 256; part < nparts; part += 256) {   // more parts than threads: fold the rest in
+      const float m_ = pm[part], s_ = ps[part];
+      if (m_ > SPEC_NEG_INF) {
+        const float mn = fmaxf(run_m, m_);
+        run_s = run_s * __expf(run_m - mn) + s_ * __expf(m_ - mn);
+        run_m = mn;
+      }
+      for (int j = 0; j < k; ++j) {
+        uint64_t c = best_key(pv[(int64_t)part * k + j], pi[(int64_t)part * k + j]);
+#pragma unroll
+        for (int q = 0; q < K; ++q) {   // (an entry that does not belong falls through and changes nothing)
+          const bool gt_q = c > tk[q];
+          const uint64_t lower = gt_q ? tk[q] : c;
+          tk[q] = gt_q ? c : tk[q];
+          c = lower;
+        }
+      }
+    }
+
+    // ---- this wave's 64 parts
+    const float wm = wave_max(run_m);
+    const float wsum = wave_sum(run_m > SPEC_NEG_INF ? run_s * __expf(run_m - wm) : 0.f);
+    uint64_t won_key[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      won_key[j] = kEmpty;
+      if (j < k) {
+        won_key[j] = wave_best_key(tk[0]);
+        const bool won = tk[0] == won_key[j];   // the owner of the winner pops it (keys of real entries are unique)
+#pragma unroll
+        for (int q = 0; q + 1 < K; ++q) {
+          const uint64_t up = opaque_key(tk[q + 1]);
+          tk[q] = won ? up : tk[q];
+        }
+        tk[K - 1] = won ? kEmpty : tk[K - 1];
+      }
+    }
+    // ---- the four waves' results through LDS
+    float* mine = lds + w * kMergeWave;
+    if (lane == 0) {
+      mine[0] = wm;
+      mine[1] = wsum;
+#pragma unroll
+      for (int j = 0; j < K; ++j)   // (empty entries are told apart, so that every candidate has its own rank)
+        reinterpret_cast<uint64_t*>(mine + 2)[j] =
+            won_key[j] == kEmpty ? best_key(SPEC_NEG_INF, kIdxNone - (w * kMaxTopK + j)) : won_key[j];
+    }
   }
   __syncthreads();
   float m4[4], s4[4];
@@ -258,6 +271,15 @@ __device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_
   best_unkey(key, out_val, out_idx);
   if (out_idx > kIdxNone - 4 * kMaxTopK) out_idx = kIdxNone;   // (an empty entry: no token has such an index)
   rank = lane < 4 * K ? before_me : kNoRank;
+}
+
+template <int K>
+__device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_t row, int nparts, int k,
+                                                     float& out_val, int32_t& out_idx, int& rank,
+                                                     float& lse, float* lds) {
+  MergePart<K> x;
+  group_merge_load<K>(p, row, nparts, k, x);
+  group_merge_loaded<K, false>(x, p, row, nparts, k, out_val, out_idx, rank, lse, lds);
 }
 
 __device__ __forceinline__ void group_merge_partials(const Partials& p, int64_t row, int nparts, int k,

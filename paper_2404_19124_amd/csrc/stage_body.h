@@ -6,148 +6,168 @@
 
 namespace specdraft {
 
-// One node (child row r) of a stage, computed by a whole workgroup of NT threads:
+// KC sibling nodes of a stage, computed by a whole workgroup of NT threads: the children rank0 .. of row `parent` of
+// the stage before, as rows r0 .. of this one (those past the parent's last child, `live` < KC, are not stored):
 //   state = GELU(LayerNorm(w_s * (W s_parent) + w_e * Emb[token]))
-// The token the node carries is the rank-th best of its parent's head row; that row's
-// partial results are merged here (every sibling repeats the small merge, which saves
-// a separate launch on the latency-critical batch-1 chain).
+// The token a node carries is the rank-th best of its parent's head row; that row's partial results are merged here, once
+// for the KC siblings (which saves a separate launch on the latency-critical batch-1 chain).
+// K: entries per partial list that registers are kept for (>= k_prev; 0: stage 0, where the token is given).
 // NCH = 8-element chunks per thread held in registers (D <= NCH * NT * 8).
-// `lds`: 32 + (NT / 256) * kMergeLds words of scratch.  Contains workgroup barriers.
+// `lds`: 32 * KC + kMergeLds words of scratch.  Contains workgroup barriers.
+// A chain of trips to memory is what a row takes, so what hangs on nothing is requested up front, the partial lists
+// before all else, without a branch between two requests (the compiler waits for what is on its way where paths join);
+// the other parts of a split projection come with the embedding row.
 // States are stored as whole 16-byte slots; the L2 gathers the eight rows that share a 128-byte line.
-template <bool BF16, int NCH, int NT>
-__device__ __forceinline__ void stage_row(const StageJob& j, int r, float* lds) {
-  float* scratch = lds;                 // NT / 64 <= 16 words
-  const int tid = opaque_tid(), lane = tid & 63;
-  float* merge_lds = lds + 32 + (tid >> 8) * kMergeLds;
-  int parent = r / j.k_prev, rank = r - parent * j.k_prev;
-  if (j.row_parent) {  // per-sequence trees: the host laid the rows out
-    parent = j.row_parent[r];
-    rank = j.row_rank[r];
-  }
+template <bool BF16, int K, int NCH, int NT, int KC>
+__device__ __forceinline__ void stage_rows(const StageJob& j, int parent, int rank0, int r0, int live, float* lds) {
+  const int tid = opaque_tid();
   const int D = j.D, nchunk = D / 8;
 
-  // everything that does not depend on the token is requested first: the
-  // projected parent state and the LayerNorm affine
+  MergePart<K ? K : 1> list;
+  if (K) group_merge_load<K ? K : 1>(j.part, parent, j.nparts, j.k_prev, list);
   const float* pz = j.pz + (int64_t)parent * D;
-  float z[NCH][8], ga[NCH][8], be[NCH][8];
+  float zp[NCH][8], ga[NCH][8], be[NCH][8];
+  auto load8 = [](float (&x)[8], const float* src) {
+    const float4 a = *reinterpret_cast<const float4*>(src), b = *reinterpret_cast<const float4*>(src + 4);
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+  };
+  int at8[NCH];   // the thread's chunks (past the row: its last one again, masked where it would count)
 #pragma unroll
   for (int ci = 0; ci < NCH; ++ci) {
-    const int c = tid + ci * NT;
-    if (c < nchunk) {
-      float4 p0 = *reinterpret_cast<const float4*>(pz + c * 8);
-      float4 p1 = *reinterpret_cast<const float4*>(pz + c * 8 + 4);
-      for (int q = 1; q < j.pz_parts; ++q) {  // a projection split along K: add the parts in order
-        const float* pq = pz + q * j.pz_part_stride + c * 8;
-        const float4 q0 = *reinterpret_cast<const float4*>(pq);
-        const float4 q1 = *reinterpret_cast<const float4*>(pq + 4);
-        p0.x += q0.x; p0.y += q0.y; p0.z += q0.z; p0.w += q0.w;
-        p1.x += q1.x; p1.y += q1.y; p1.z += q1.z; p1.w += q1.w;
-      }
-      const float4 g0 = *reinterpret_cast<const float4*>(j.gamma + c * 8);
-      const float4 g1 = *reinterpret_cast<const float4*>(j.gamma + c * 8 + 4);
-      const float4 b0 = *reinterpret_cast<const float4*>(j.beta + c * 8);
-      const float4 b1 = *reinterpret_cast<const float4*>(j.beta + c * 8 + 4);
-      z[ci][0] = p0.x; z[ci][1] = p0.y; z[ci][2] = p0.z; z[ci][3] = p0.w;
-      z[ci][4] = p1.x; z[ci][5] = p1.y; z[ci][6] = p1.z; z[ci][7] = p1.w;
-      ga[ci][0] = g0.x; ga[ci][1] = g0.y; ga[ci][2] = g0.z; ga[ci][3] = g0.w;
-      ga[ci][4] = g1.x; ga[ci][5] = g1.y; ga[ci][6] = g1.z; ga[ci][7] = g1.w;
-      be[ci][0] = b0.x; be[ci][1] = b0.y; be[ci][2] = b0.z; be[ci][3] = b0.w;
-      be[ci][4] = b1.x; be[ci][5] = b1.y; be[ci][6] = b1.z; be[ci][7] = b1.w;
-    }
+    at8[ci] = min(tid + ci * NT, nchunk - 1) * 8;
+    load8(zp[ci], pz + at8[ci]);
+    load8(ga[ci], j.gamma + at8[ci]);
+    load8(be[ci], j.beta + at8[ci]);
   }
 
-  int tok;
-  if (j.stage == 0) {
-    tok = j.last_tok[parent];   // (uniform tree: parent == r)
+  int tok[KC], at = kNoRank;
+  float v = 0.f, lse = 0.f;
+  int32_t ix = 0;
+  if (K == 0) {
+#pragma unroll
+    for (int h = 0; h < KC; ++h) tok[h] = j.last_tok[parent];   // (uniform tree: parent == r)
   } else {
-    float v, lse;
-    int32_t ix;
-    int at;
-    // every 256-thread group merges the same parent row (one group would do; the
-    // barriers inside need all of them anyway)
-    group_merge_partials(j.part, parent, j.nparts, j.k_prev, v, ix, at, lse, merge_lds);
-    tok = __builtin_amdgcn_readlane(ix, __ffsll((unsigned long long)__ballot(at == rank)) - 1);
-    if (rank == 0 && tid < 64 && at < j.k_prev) {
-      j.prev_tok[(int64_t)parent * j.k_prev + at] = ix;
-      j.prev_logp[(int64_t)parent * j.k_prev + at] = v - lse;
-      if (at == 0) j.prev_lse[parent] = lse;
+    group_merge_loaded<K ? K : 1, true>(list, j.part, parent, j.nparts, j.k_prev, v, ix, at, lse, lds + 32 * KC);
+#pragma unroll
+    for (int h = 0; h < KC; ++h) {
+      const int rank = h < live ? rank0 + h : rank0;
+      tok[h] = __builtin_amdgcn_readlane(ix, __ffsll((unsigned long long)__ballot(at == rank)) - 1);
     }
   }
-  tok = min(max(tok, 0), j.V - 1);  // a wild token from the caller must not leave the table
 
-  // gather + mix
-  float lsum = 0.f;
+  // gather
+  uint4 raw[KC][NCH][BF16 ? 1 : 2];
 #pragma unroll
-  for (int ci = 0; ci < NCH; ++ci) {
-    const int c = tid + ci * NT;
-    if (c < nchunk) {
-      float e[8];
-      if (BF16) {
-        const uint4 raw =
-            *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(j.emb) + (int64_t)tok * D + c * 8);
-        const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+  for (int h = 0; h < KC; ++h) {
+    const int64_t t = min(max(tok[h], 0), j.V - 1);  // a wild token from the caller must not leave the table
+    const uint4* row = reinterpret_cast<const uint4*>(static_cast<const char*>(j.emb) + t * D * (BF16 ? 2 : 4));
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          e[2 * q] = bf16_bits_to_f32(w[q] & 0xffffu);
-          e[2 * q + 1] = bf16_bits_to_f32(w[q] >> 16);
+    for (int ci = 0; ci < NCH; ++ci)
+#pragma unroll
+      for (int u = 0; u < (BF16 ? 1 : 2); ++u) raw[h][ci][u] = row[(at8[ci] >> 3) * (BF16 ? 1 : 2) + u];
+  }
+  // a projection split along K: its other parts, added in order, four of them (long rows: two) on their way at a time
+  constexpr int PU = NCH > 2 ? 2 : 4;
+  for (int q0 = 1; q0 < j.pz_parts; q0 += PU) {
+    float pq[PU][NCH][8];
+#pragma unroll
+    for (int u = 0; u < PU; ++u)
+#pragma unroll
+      for (int ci = 0; ci < NCH; ++ci)
+        load8(pq[u][ci], pz + min(q0 + u, j.pz_parts - 1) * j.pz_part_stride + at8[ci]);
+#pragma unroll
+    for (int u = 0; u < PU; ++u)
+#pragma unroll
+      for (int ci = 0; ci < NCH; ++ci)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float sum = zp[ci][q] + pq[u][ci][q];
+          zp[ci][q] = q0 + u < j.pz_parts ? sum : zp[ci][q];
         }
-      } else {
-        const float* er = static_cast<const float*>(j.emb) + (int64_t)tok * D + c * 8;
-        const float4 e0 = *reinterpret_cast<const float4*>(er);
-        const float4 e1 = *reinterpret_cast<const float4*>(er + 4);
-        e[0] = e0.x; e[1] = e0.y; e[2] = e0.z; e[3] = e0.w;
-        e[4] = e1.x; e[5] = e1.y; e[6] = e1.z; e[7] = e1.w;
-      }
+  }
+  if (K && rank0 == 0 && tid < 64 && at < j.k_prev) {   // (behind the requests: a wait for those would wait for these)
+    j.prev_tok[(int64_t)parent * j.k_prev + at] = ix;
+    j.prev_logp[(int64_t)parent * j.k_prev + at] = v - lse;
+    if (at == 0) j.prev_lse[parent] = lse;
+  }
+  // mix
+  float z[KC][NCH][8], lsum[KC];
+#pragma unroll
+  for (int h = 0; h < KC; ++h) {
+    lsum[h] = 0.f;
+#pragma unroll
+    for (int ci = 0; ci < NCH; ++ci) {
+      const bool counts = tid + ci * NT < nchunk;
+      float sum = lsum[h];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        z[ci][q] = j.w_s * z[ci][q] + j.w_e * e[q];
-        lsum += z[ci][q];
+        const uint4 w = raw[h][ci][BF16 ? 0 : q >> 2];
+        const uint32_t word = (BF16 ? q >> 1 : q & 3) == 0 ? w.x : (BF16 ? q >> 1 : q & 3) == 1 ? w.y
+                              : (BF16 ? q >> 1 : q & 3) == 2 ? w.z : w.w;
+        const float e = !BF16 ? __uint_as_float(word)
+                        : (q & 1) ? bf16_bits_to_f32(word >> 16) : bf16_bits_to_f32(word & 0xffffu);
+        z[h][ci][q] = j.w_s * zp[ci][q] + j.w_e * e;
+        sum += z[h][ci][q];
       }
+      lsum[h] = counts ? sum : lsum[h];
     }
   }
-  const float mean = block_sum<NT>(lsum, scratch) / (float)D;
-  float lvar = 0.f;
+  float mean[KC], lvar[KC], rstd[KC];
+  block_sums<NT, KC>(lsum, lds);
 #pragma unroll
-  for (int ci = 0; ci < NCH; ++ci) {
-    if (tid + ci * NT < nchunk) {
+  for (int h = 0; h < KC; ++h) {
+    mean[h] = lsum[h] / (float)D;
+    lvar[h] = 0.f;
+#pragma unroll
+    for (int ci = 0; ci < NCH; ++ci) {
+      const bool counts = tid + ci * NT < nchunk;
+      float sum = lvar[h];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const float d = z[ci][q] - mean;
-        lvar += d * d;
+        const float d = z[h][ci][q] - mean[h];
+        sum += d * d;
       }
+      lvar[h] = counts ? sum : lvar[h];
     }
   }
-  const float var = block_sum<NT>(lvar, scratch) / (float)D;
-  const float rstd = 1.0f / sqrtf(var + j.eps);
+  block_sums<NT, KC>(lvar, lds + 16 * KC);
+#pragma unroll
+  for (int h = 0; h < KC; ++h) rstd[h] = 1.0f / sqrtf(lvar[h] / (float)D + j.eps);
 
 #pragma unroll
-  for (int ci = 0; ci < NCH; ++ci) {
-    const int c = tid + ci * NT;
-    if (c < nchunk) {
-      float s[8];
+  for (int h = 0; h < KC; ++h) {
+    if (h >= live) break;
+    const int r = r0 + h;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float y = (z[ci][q] - mean) * rstd * ga[ci][q] + be[ci][q];
-        s[q] = 0.5f * y * (1.0f + erf_as(y * 0.70710678118654752440f));
-      }
-      if (BF16) {
-        uint4 o;
-        o.x = f32_to_bf16_bits(s[0]) | (f32_to_bf16_bits(s[1]) << 16);
-        o.y = f32_to_bf16_bits(s[2]) | (f32_to_bf16_bits(s[3]) << 16);
-        o.z = f32_to_bf16_bits(s[4]) | (f32_to_bf16_bits(s[5]) << 16);
-        o.w = f32_to_bf16_bits(s[6]) | (f32_to_bf16_bits(s[7]) << 16);
-        // tiled layout: row tile r/16, column fragment c/4, lane slot (c%4)*16 + r%16
-        const int64_t slot = ((int64_t)(r >> 4) * (D / 32) + (c >> 2)) * 64 + ((c & 3) << 4) + (r & 15);
-        reinterpret_cast<uint4*>(j.state_out)[slot] = o;
-        if (j.state_dbg) reinterpret_cast<uint4*>(j.state_dbg)[((int64_t)r * D) / 8 + c] = o;
-      } else {
-        float* so = static_cast<float*>(j.state_out) + (int64_t)r * D + c * 8;
-        *reinterpret_cast<float4*>(so) = make_float4(s[0], s[1], s[2], s[3]);
-        *reinterpret_cast<float4*>(so + 4) = make_float4(s[4], s[5], s[6], s[7]);
-        if (j.state_dbg) {
-          float* sd = static_cast<float*>(j.state_dbg) + (int64_t)r * D + c * 8;
-          *reinterpret_cast<float4*>(sd) = make_float4(s[0], s[1], s[2], s[3]);
-          *reinterpret_cast<float4*>(sd + 4) = make_float4(s[4], s[5], s[6], s[7]);
+    for (int ci = 0; ci < NCH; ++ci) {
+      const int c = tid + ci * NT;
+      if (c < nchunk) {
+        float s[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float y = (z[h][ci][q] - mean[h]) * rstd[h] * ga[ci][q] + be[ci][q];
+          s[q] = 0.5f * y * (1.0f + erf_as(y * 0.70710678118654752440f));
+        }
+        if (BF16) {
+          uint4 o;
+          o.x = f32_to_bf16_pair(s[0], s[1]);
+          o.y = f32_to_bf16_pair(s[2], s[3]);
+          o.z = f32_to_bf16_pair(s[4], s[5]);
+          o.w = f32_to_bf16_pair(s[6], s[7]);
+          // tiled layout: row tile r/16, column fragment c/4, lane slot (c%4)*16 + r%16
+          const int64_t slot = ((int64_t)(r >> 4) * (D / 32) + (c >> 2)) * 64 + ((c & 3) << 4) + (r & 15);
+          reinterpret_cast<uint4*>(j.state_out)[slot] = o;
+          if (j.state_dbg) reinterpret_cast<uint4*>(j.state_dbg)[((int64_t)r * D) / 8 + c] = o;
+        } else {
+          float* so = static_cast<float*>(j.state_out) + (int64_t)r * D + c * 8;
+          *reinterpret_cast<float4*>(so) = make_float4(s[0], s[1], s[2], s[3]);
+          *reinterpret_cast<float4*>(so + 4) = make_float4(s[4], s[5], s[6], s[7]);
+          if (j.state_dbg) {
+            float* sd = static_cast<float*>(j.state_dbg) + (int64_t)r * D + c * 8;
+            *reinterpret_cast<float4*>(sd) = make_float4(s[0], s[1], s[2], s[3]);
+            *reinterpret_cast<float4*>(sd + 4) = make_float4(s[4], s[5], s[6], s[7]);
+          }
         }
       }
     }
