@@ -1,8 +1,7 @@
 // Stage kernel (Sec. 3.1 of the paper): for every node of the current depth,
 //   state = GELU(LayerNorm(w_s * (W s_parent) + w_e * Emb[token]))
 // The token a node carries is the j-th best of its parent's head row; that row's
-// partial results are merged here (every sibling repeats the small merge, which
-// saves a separate launch on the latency-critical batch-1 chain).
+// partial results are merged here (which saves a separate launch on the latency-critical batch-1 chain).
 #include "stage_body.h"
 
 namespace specdraft {
@@ -124,15 +123,16 @@ hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* 
 // ---------------------------------------------------------------------------
 // NT = 512: eight waves merge eight rows at a time and each wave may use 256 registers (the
 // widest merges need more than the 128 a 1024-thread workgroup would leave).  NT = 1024 for
-// last-stage top-k <= 4 (KWAVE = 4): sixteen rows per pass, one pass for the paper's trees.
+// last-stage top-k <= 4 (KWAVE = 4): sixteen rows per pass.
+// KWAVE = 0: merge_rows_kernel has been here.
 template <int NT, int KWAVE>
 __global__ __launch_bounds__(NT) void tree_kernel(TreeJob j) {
   __shared__ __align__(16) uint64_t sk[kMaxLeaves];
   __shared__ int s_k[kMaxStages], s_kw[kMaxStages];
   __shared__ int64_t s_off[kMaxStages], s_rbase[kMaxStages];
-  __shared__ __align__(16) float merge_lds[kMergeLds * (NT / 256)];
-  __shared__ int32_t c_tok[kMaxLeaves];
-  __shared__ float c_logp[kMaxLeaves];
+  __shared__ __align__(16) float merge_lds[KWAVE ? kMergeLds * (NT / 256) : 1];
+  __shared__ int32_t c_tok[KWAVE ? kMaxLeaves : 1];
+  __shared__ float c_logp[KWAVE ? kMaxLeaves : 1];
   TreeArgs a;
   tree_args_for_sequence(j, blockIdx.x, a, s_k, s_off, s_rbase, s_kw);
   // (no barrier here: a wave reads back only what it wrote itself until the merge in tree_body ends in one,
@@ -140,14 +140,55 @@ __global__ __launch_bounds__(NT) void tree_kernel(TreeJob j) {
   tree_body<NT, KWAVE>(a, blockIdx.x, s_k, s_off, s_rbase, s_kw, sk, merge_lds, c_tok, c_logp);
 }
 
+// The last head's tables ahead of the tree kernel, one row per wave and workgroup, over the whole chip.
+template <int K>
+__global__ __launch_bounds__(64) void merge_rows_kernel(TreeJob j) {
+  const int64_t row = blockIdx.x;
+  const int lane = threadIdx.x, kw = j.kstride[j.n - 1];
+  const int64_t at = j.off[j.n - 1] + row * kw, row_at = j.row_off[j.n - 1] + row;
+  float v[kMaxTopK], lse;
+  int32_t ix[kMaxTopK];
+  wave_merge_partials_k<K>(j.part, row, j.nparts, kw, v, ix, lse);
+#pragma unroll
+  for (int t = 0; t < K; ++t)
+    if (lane == t && t < kw) {
+      j.tok[at + t] = ix[t];
+      j.logp[at + t] = v[t] - lse;
+    }
+  if (lane == 0) j.lse[row_at] = lse;
+}
+
+static void launch_merge_rows(const TreeJob& job, hipStream_t st) {
+  const dim3 grid(job.rows_last), block(64);
+  switch (job.kstride[job.n - 1]) {
+    case 1: hipLaunchKernelGGL(merge_rows_kernel<1>, grid, block, 0, st, job); break;
+    case 2: hipLaunchKernelGGL(merge_rows_kernel<2>, grid, block, 0, st, job); break;
+    case 3: hipLaunchKernelGGL(merge_rows_kernel<3>, grid, block, 0, st, job); break;
+    case 4: hipLaunchKernelGGL(merge_rows_kernel<4>, grid, block, 0, st, job); break;
+    case 5:
+    case 6: hipLaunchKernelGGL(merge_rows_kernel<6>, grid, block, 0, st, job); break;
+    default: hipLaunchKernelGGL(merge_rows_kernel<8>, grid, block, 0, st, job); break;
+  }
+}
+
 hipError_t launch_tree(const TreeJob& job, hipStream_t st) {
   // (per-sequence trees: the widest table decides the merge variant, rows_last is then an upper bound)
   const int kw_last = job.kstride[job.n - 1];
   const int rows_last = job.seq_desc ? kMaxLeaves : job.L / job.top_k[job.n - 1];
-  if (kw_last <= 4 && rows_last > 8)
+  // More rows per sequence than one pass of sixteen waves: a pass is 3 us and more of arithmetic on one CU while others
+  // are idle, and the rows get a launch of their own.  Tree kernel alone, and both launches, us: 24 rows x 16 sequences
+  // 16.2 and 13.0, 72 x 32 19.8 and 13.4; in one pass 15 x 64 12.2 and 11.8, 15 x 5 10.3 and 10.5, 15 x 1 8.5 and 9.6.
+  if (!job.seq_desc && rows_last > 16) {
+    launch_merge_rows(job, st);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (job.L <= 256) hipLaunchKernelGGL((tree_kernel<256, 0>), dim3(job.batch), dim3(256), 0, st, job);
+    else hipLaunchKernelGGL((tree_kernel<1024, 0>), dim3(job.batch), dim3(1024), 0, st, job);
+  } else if (kw_last <= 4 && rows_last > 8) {
     hipLaunchKernelGGL((tree_kernel<1024, 4>), dim3(job.batch), dim3(1024), 0, st, job);
-  else
+  } else {
     hipLaunchKernelGGL((tree_kernel<512, kMaxTopK>), dim3(job.batch), dim3(512), 0, st, job);
+  }
   return hipGetLastError();
 }
 

@@ -6,24 +6,6 @@
 
 namespace specdraft {
 
-// Insert (v, i) into a list kept sorted by "larger value, then smaller index";
-// the last entry falls off.
-template <int K>
-__device__ __forceinline__ void list_insert(float (&tv)[K], int32_t (&ti)[K], float v, int32_t i) {
-  float cv = v;
-  int32_t ci = i;
-#pragma unroll
-  for (int q = 0; q < K; ++q) {
-    const bool gt = before(cv, ci, tv[q], ti[q]);
-    const float ov = tv[q];
-    const int32_t oi = ti[q];
-    tv[q] = gt ? cv : ov;
-    ti[q] = gt ? ci : oi;
-    cv = gt ? ov : cv;
-    ci = gt ? oi : ci;
-  }
-}
-
 // All 64 lanes of a wave call this for the same row; every lane receives the
 // result.  out_val / out_idx must be indexed with compile-time constants by the
 // caller (they live in registers).  Candidates of different parts never share a

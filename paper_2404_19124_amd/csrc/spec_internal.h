@@ -212,6 +212,7 @@ struct TreeJob {
   int top_k[kMaxStages];
   Partials part;           // last head
   int nparts;
+  int rows_last;           // rows of the last head, all sequences
   // per-stage tables [R_i][k_i], concatenated; offsets in elements
   int32_t* tok;
   float* logp;

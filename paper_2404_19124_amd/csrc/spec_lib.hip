@@ -676,6 +676,7 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
     for (int i = n; i < kMaxStages; ++i) tj.top_k[i] = 1;
     tj.part = ws.part;
     tj.nparts = nparts;
+    tj.rows_last = (int)R[n - 1];
     tj.tok = ws.tok;
     tj.logp = ws.logp;
     tj.lse = ws.lse;

@@ -202,7 +202,7 @@ struct TreeArgs {
 // the same: the debug outputs and the caller's next step read them).
 // KWAVE: widest kw_last merged one row per wave (register-hungry for wide lists: a wave
 // of a 1024-thread workgroup has 128 registers); wider ones are merged one row per
-// 256-thread group.  Contains workgroup barriers.
+// 256-thread group; 0: the tables of the last stage are there already.  Contains workgroup barriers.
 template <int NT, int KWAVE>
 __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s_k, const int64_t* s_off,
                                           const int64_t* s_rbase, const int* s_kw, uint64_t* sk, float* merge_lds,
@@ -234,7 +234,7 @@ __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s
   // come from the merge through LDS.  The leaf scores then wait for no memory at all.
   const bool one_pass = nleaf <= NT;   // every thread has at most one leaf: its tokens stay in registers
   constexpr int kEarly = 3;            // earlier stages whose entries a thread holds across the merge (registers)
-  const bool early = one_pass && n - 1 <= kEarly && (int64_t)rows_last * kw <= kMaxLeaves;
+  const bool early = KWAVE > 0 && one_pass && n - 1 <= kEarly && (int64_t)rows_last * kw <= kMaxLeaves;
   float lp_e[kEarly];
   int32_t tk_e[kEarly];
   int last_at = 0;
@@ -251,7 +251,8 @@ __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s
     }
   }
 
-  if (kw <= KWAVE) {
+  if (KWAVE == 0) {
+  } else if (kw <= KWAVE) {
     // (the first wave has just spent its time on the leaves' paths: it stays out of the merge when the
     // other waves cover the rows in one pass)
     const int w0 = (early && rows_last <= NT / 64 - 1) ? 1 : 0;
@@ -303,8 +304,10 @@ __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s
       if (live && gl == 0) j.lse[j.row_off_last + row] = lse;
     }
   }
-  __threadfence_block();
-  __syncthreads();
+  if (KWAVE > 0) {
+    __threadfence_block();
+    __syncthreads();
+  }
 
   int32_t tk[kMaxStages];
   if (early) {
