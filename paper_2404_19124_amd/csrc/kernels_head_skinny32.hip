@@ -227,10 +227,15 @@ static hipError_t launch_skinny32_t(const HeadJob& job, int grid, hipStream_t st
 hipError_t launch_head_skinny32(const HeadJob& job, int n_cu, hipStream_t st, hipEvent_t ev_start,
                                 hipEvent_t ev_stop) {
   const int grid = skinny_grid(n_cu);
-  // as many tiles in flight as the registers hold beside the states (8 * NS of a wave's 128)
+  // 8 fragments of a wave in flight, or as near as whole tiles come, are 128 KiB of a CU and saturate HBM; half as much again
+  // only queues there.  Launches of 17 to 32 rows with 12 and now 8 (K = 2048) or 6 (3072) of them, us: 32003 rows of 2048
+  // 25.4 -> 23.7, 65024 of 2048 44.3 -> 43.1, 32000 of 3072 32.7 -> 31.8, 65024 of 3072 65.9 -> 64.9.  Shorter K within an
+  // instance leaves fragments of a tile unused: there the deeper ring.
   const int ns = (job.kt + kS32Waves - 1) / kS32Waves;
-  if (ns <= 4) return launch_skinny32_t<4, 3>(job, grid, st, ev_start, ev_stop);
-  if (ns <= 6) return launch_skinny32_t<6, 2>(job, grid, st, ev_start, ev_stop);
+  if (ns == 4) return launch_skinny32_t<4, 2>(job, grid, st, ev_start, ev_stop);
+  if (ns < 4) return launch_skinny32_t<4, 3>(job, grid, st, ev_start, ev_stop);
+  if (ns == 6) return launch_skinny32_t<6, 1>(job, grid, st, ev_start, ev_stop);
+  if (ns < 6) return launch_skinny32_t<6, 2>(job, grid, st, ev_start, ev_stop);
   return launch_skinny32_t<kS32Steps, 1>(job, grid, st, ev_start, ev_stop);
 }
 

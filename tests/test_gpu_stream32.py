@@ -35,6 +35,14 @@ def test_17_to_32_rows(case):
     assert rep.rows_exempt <= 1
 
 
+@pytest.mark.parametrize("D,V", [(1536, 16400), (1600, 8200), (2560, 8209), (2624, 4100)])
+def test_rings_on_either_side_of_a_slice_length(D, V):
+    """Slices of 3, 4, 5 and 6 K-steps: the rings of three, two, two and one tile."""
+    wl = W.Workload("rings32", 64, D, V, 2, (1, 2), 2, 29, "bf16", "f32", 0.6, seed=29, emb_std=0.3)
+    assert B.spec_plan_contraction(29, D, V, 1, D)["kernel"] == 2
+    run_workload(wl, ln_affine="random", gen_device="cpu", check_verify=False)
+
+
 @pytest.mark.parametrize("rows,D,V", [(17, 64, 33), (32, 4096, 4111)])
 def test_store_epilogue_of_row_major_states(rows, D, V):
     wl = W.Workload("logp32", 64, D, V, 1, (2,), 2, 32, "bf16", "f32", 0.6, seed=24)
