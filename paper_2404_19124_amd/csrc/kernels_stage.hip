@@ -7,8 +7,8 @@
 namespace specdraft {
 
 // Parents from which siblings share a workgroup: one for every CU.  With fewer, what a CU saves others do not lend (a child is
-// 2 us of arithmetic on one CU): 96 parents of 4 children 11.9 us together, 10.2 one by one; 16 of 6: 11.2 and 8.5; 64 of 5:
-// 11.6 and 10.9; 256 of 3: 12.8 and 13.8; 320 of 3: 16.9 and 17.1; 768 of 3: 21.0 and 29.4 (D = 4096, 13B: 5120).
+// 2 us of arithmetic on one CU).  Together and one by one, us: D = 4096, 16 parents of 6 11.2 and 8.5, 64 of 5 11.6 and 10.9, 96 of
+// 4 11.9 and 10.2, 320 of 3 16.9 and 17.1; D = 3072, 32 of 6 12.2 and 10.0, 192 of 4 12.8 and 13.8, 768 of 3 21.0 and 29.4.
 constexpr int kSiblingParents = 256;
 
 // K: the width that registers are kept for, see stage_rows; NCH = 8-element chunks per thread (D <= NCH * NT * 8).  One
@@ -36,6 +36,7 @@ __global__ __launch_bounds__(NT) void stage_kernel(StageJob j) {
 
 // KC siblings per workgroup, `per` workgroups per parent (uniform trees, packed states).  The merge and the parent's
 // projection are read and computed once for the siblings, which are a third to a half of a row's instructions.
+// Bound: vector ALU (38 instructions per element of a row).  2304 rows of 3 siblings, D = 3072: 28.3 us one by one, 21.0 so.
 template <int K, int NCH, int NT, int KC>
 __global__ __launch_bounds__(NT) void stage_siblings_kernel(StageJob j, int per, int group) {
   __shared__ __align__(16) float lds[32 * KC + kMergeLds];
@@ -140,7 +141,8 @@ __global__ __launch_bounds__(NT) void tree_kernel(TreeJob j) {
   tree_body<NT, KWAVE>(a, blockIdx.x, s_k, s_off, s_rbase, s_kw, sk, merge_lds, c_tok, c_logp);
 }
 
-// The last head's tables ahead of the tree kernel, one row per wave and workgroup, over the whole chip.
+// The last head's tables ahead of the tree kernel, one row per wave and workgroup, over the whole chip.  Bound: latency, one trip
+// to memory and the merge's chain (4.6 us for 2304 rows as for 15).  A wave alone on its SIMD: no reason for larger workgroups.
 template <int K>
 __global__ __launch_bounds__(64) void merge_rows_kernel(TreeJob j) {
   const int64_t row = blockIdx.x;
