@@ -57,6 +57,13 @@ __device__ __forceinline__ uint32_t f32_to_bf16_pair(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, p);
 }
 
+// The mix of a stage, w_s * projection + w_e * embedding, written out: of the two products it is always this one that is
+// rounded.  Left to the compiler that was one or the other from instance to instance (element to element, even), and a
+// row's state hung on the size of the batch and on which kernel computed it.
+__device__ __forceinline__ float stage_mix(float w_s, float proj, float w_e, float emb) {
+  return __builtin_fmaf(w_s, proj, w_e * emb);
+}
+
 // Total order used everywhere a "best" is chosen: larger value first, then
 // smaller index.  true when (v1, i1) comes strictly before (v2, i2).
 __device__ __forceinline__ bool before(float v1, int32_t i1, float v2, int32_t i2) {

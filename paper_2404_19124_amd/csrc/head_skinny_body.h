@@ -95,7 +95,7 @@ __device__ __forceinline__ void fold_states(const HeadJob& p, u32x4* ldsB, float
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const float e = bf16_bits_to_f32((q & 1) ? (ew[q >> 1] >> 16) : (ew[q >> 1] & 0xffffu));
-        z[q] = f.w_s * pzv[q] + f.w_e * e;
+        z[q] = stage_mix(f.w_s, pzv[q], f.w_e, e);
         lsum += z[q];
       }
     } else {

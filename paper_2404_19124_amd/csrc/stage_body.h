@@ -109,7 +109,7 @@ __device__ __forceinline__ void stage_rows(const StageJob& j, int parent, int ra
                               : (BF16 ? q >> 1 : q & 3) == 2 ? w.z : w.w;
         const float e = !BF16 ? __uint_as_float(word)
                         : (q & 1) ? bf16_bits_to_f32(word >> 16) : bf16_bits_to_f32(word & 0xffffu);
-        z[h][ci][q] = j.w_s * zp[ci][q] + j.w_e * e;
+        z[h][ci][q] = stage_mix(j.w_s, zp[ci][q], j.w_e, e);
         sum += z[h][ci][q];
       }
       lsum[h] = counts ? sum : lsum[h];
