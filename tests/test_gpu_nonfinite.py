@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from oracle import spec_oracle as O
+from paper_2404_19124_amd import binding as B
 from paper_2404_19124_amd import workloads as W
 from paper_2404_19124_amd.runner import Step
 
@@ -93,3 +94,82 @@ def test_a_row_without_an_order_names_no_made_up_token(dtype, V, batch):
     cand = step.cand_tokens.cpu().numpy()
     assert (((cand >= 0) & (cand < V)) | (cand == 2**31 - 1)).all()
     step.close()
+
+
+# the tile kernel of many rows, by blocks of 192 and of 256 rows: its last weight tile has one row of the vocabulary, or 235
+TILES = [(1000, 24577, 3, 256), (1000, 24577, 1, 256), (513, 33003, 4, 192), (900, 12289, 2, 192)]
+
+
+def _tile_plan(batch, V, k, block):
+    plan = B.spec_plan_head(batch, 128, V, k)
+    assert 100 <= plan["kernel"] < 1000 and plan["block_rows"] == block
+    return plan
+
+
+@pytest.mark.parametrize("batch,V,k,block", TILES)
+def test_tile_kernel_logits_of_minus_infinity(batch, V, k, block):
+    """The first tile of every other range whole (of a range with one tile: nothing finite), and rows all over the others."""
+    plan = _tile_plan(batch, V, k, block)
+    low = np.zeros(V, bool)
+    low[V // 4::7] = True
+    for t0 in (r * plan["tiles"] // plan["ranges"] for r in range(0, plan["ranges"], 2)):
+        low[256 * t0:256 * (t0 + 1)] = True
+    assert not low.all()
+
+    def edit(head):
+        head[torch.from_numpy(low)] = -BIG
+
+    got, head = _first_stage("bf16", V, batch, k, edit)
+    assert (got["states"].sum(1) > 2).all()
+    logits = O.head_logits(got["states"], head)
+    logits[:, low] = -np.inf
+    logp, lse = O.log_softmax(logits)
+    assert np.abs(got["lse"] - lse).max() < 1e-3
+    for r in range(batch):
+        want = O.topk_desc(logits[r].astype(np.float32), k)
+        assert np.array_equal(got["tok"][r], want)
+        assert np.abs(got["logp"][r] - logp[r, want]).max() < 1e-3
+
+
+@pytest.mark.parametrize("at", [0, -1], ids=["first", "last"])
+@pytest.mark.parametrize("batch,V,k,block", TILES)
+def test_tile_kernel_logit_that_is_nan(batch, V, k, block, at):
+    """In the first row of the vocabulary, and in the last, behind which the tile goes on."""
+    _tile_plan(batch, V, k, block)
+
+    def edit(head):
+        head[at] = float("nan")
+
+    got, head = _first_stage("bf16", V, batch, k, edit)
+    assert np.isnan(got["lse"]).all() and np.isnan(got["logp"]).all()
+    logits = O.head_logits(got["states"], head)
+    logits[:, at] = -np.inf
+    for r in range(batch):
+        assert np.array_equal(got["tok"][r], O.topk_desc(logits[r].astype(np.float32), k))
+
+
+@pytest.mark.parametrize("batch,V,k,block", TILES)
+def test_tile_kernel_rows_of_nan_only(batch, V, k, block):
+    """A row without one finite logit: NaN in its sum, tokens of the vocabulary or the mark of none; the others as they were."""
+    _tile_plan(batch, V, k, block)
+    wl = W.Workload("nonfinite", 128, 128, V, 1, (k,), k, batch, "bf16", "f32", 0.5, seed=45, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    state, last = W.make_draft_inputs(wl, gen)
+    odd = torch.tensor([0, 17, 200, batch - 1])
+    step = Step(wl, {key: [t.cuda() for t in v] for key, v in w.items()}, debug=True)
+    tables = []
+    for _ in range(2):
+        step.draft(state.cuda(), last.cuda())
+        torch.cuda.synchronize()
+        t = step.debug_tables()
+        tables.append({key: t[key][0].cpu() for key in ("tok", "lse", "logp")})
+        state[odd] = float("nan")
+    step.close()
+    keep = torch.ones(batch, dtype=torch.bool)
+    keep[odd] = False
+    for key in ("tok", "lse", "logp"):
+        assert torch.equal(tables[0][key][keep], tables[1][key][keep])
+    assert torch.isnan(tables[1]["lse"][odd]).all()
+    tok = tables[1]["tok"][odd]
+    assert (((tok >= 0) & (tok < V)) | (tok == 2**31 - 1)).all()
