@@ -32,7 +32,7 @@ __host__ __device__ inline size_t skinny_state_bytes(int R, int kt) {
 // be issued long before the states exist.
 template <int NS, int DEPTH, bool EXACT>
 __device__ __forceinline__ void skinny_prefetch(const HeadJob& p, int wg, int G, u32x4 (&a)[DEPTH][NS]) {
-  const int kt = p.kt;
+  const int kt = p.kt, slots = p.tile_slots;
   const int tid = opaque_tid(), lane = tid & 63, w = tid >> 6;
   const int spw = EXACT ? NS : (kt + kSkinnyWaves - 1) / kSkinnyWaves;
   const int s0 = min(w * spw, kt);
@@ -45,7 +45,7 @@ __device__ __forceinline__ void skinny_prefetch(const HeadJob& p, int wg, int G,
     const int tile = wg + d * G;
     if (tile < total) {
       const u32x4* base =
-          tile < p.vt_head ? wh + tile * packed_tile_slots(kt) : wp + (tile - p.vt_head) * packed_tile_slots(kt);
+          tile < p.vt_head ? wh + packed_tile_start(tile, slots) : wp + packed_tile_start(tile - p.vt_head, slots);
       const u32x4* ptr = base + (int64_t)s0 * 64 + lane;
 #pragma unroll
       for (int t = 0; t < NS; ++t)
@@ -142,7 +142,7 @@ __device__ __forceinline__ void fold_states(const HeadJob& p, u32x4* ldsB, float
 template <int NS, int DEPTH, bool EXACT>
 __device__ __forceinline__ void skinny_run(const HeadJob& p, int wg, int G, u32x4 (&a)[DEPTH][NS],
                                            unsigned char* smem) {
-  const int kt = p.kt, R = p.R;
+  const int kt = p.kt, R = p.R, slots = p.tile_slots;
   u32x4* ldsB = reinterpret_cast<u32x4*>(smem);  // [kt][4][R] slots of 8 bf16
   const size_t bytesB = ((size_t)kt * 4 * R * 16 + 255) & ~(size_t)255;
   f32x4* ldsP = reinterpret_cast<f32x4*>(smem + bytesB);  // [2][waves][64]
@@ -159,7 +159,7 @@ __device__ __forceinline__ void skinny_run(const HeadJob& p, int wg, int G, u32x
   const u32x4* wh = static_cast<const u32x4*>(p.w_head);
   const u32x4* wp = static_cast<const u32x4*>(p.w_proj);
   auto tile_ptr = [&](int tile) -> const u32x4* {
-    const u32x4* base = tile < p.vt_head ? wh + tile * packed_tile_slots(kt) : wp + (tile - p.vt_head) * packed_tile_slots(kt);
+    const u32x4* base = tile < p.vt_head ? wh + packed_tile_start(tile, slots) : wp + packed_tile_start(tile - p.vt_head, slots);
     return base + (int64_t)s0 * 64 + lane;
   };
 

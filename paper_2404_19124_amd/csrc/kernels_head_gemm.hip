@@ -205,6 +205,7 @@ struct GemmArgs {
   int k_top;
   Partials part;
   int nparts;
+  int tile_slots;
 };
 
 // Narrow blocks are bandwidth-bound: two workgroups per CU (two waves per
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(256, 2) void head_gemm_kernel(GemmArgs p) {
     for (int ni = 0; ni < NI; ++ni) {
       ntv[ni] = (ntile * 4 + wave) * NI + ni;
       const int ntc = min(ntv[ni], p.nt_total[mat] - 1);
-      wp[ni] = p.w[mat] + ntc * packed_tile_slots(kt) + (int64_t)slab0 * KS * 64 + lane;
+      wp[ni] = p.w[mat] + packed_tile_start(ntc, p.tile_slots) + (int64_t)slab0 * KS * 64 + lane;
     }
   };
 
@@ -647,7 +648,7 @@ __global__ __launch_bounds__(256, 1) void head_gemm32_kernel(GemmArgs p) {
     for (int nb = 0; nb < NB; ++nb) {
       ntv[nb] = ntile * ts + wave * NI + 2 * nb;  // first 16-row tile of the block
       const int ntc = min(ntv[nb] + (c32 >> 4), tend - 1);
-      wp[nb] = p.w[mat] + ntc * packed_tile_slots(kt) + (int64_t)slab0 * KS * 64 + half * 16 + (c32 & 15);
+      wp[nb] = p.w[mat] + packed_tile_start(ntc, p.tile_slots) + (int64_t)slab0 * KS * 64 + half * 16 + (c32 & 15);
     }
   };
 
@@ -1025,6 +1026,7 @@ hipError_t launch_head_gemm(const HeadJob& job, const GemmPlan& pl, hipStream_t 
   }
   if (nm == 0) return hipErrorInvalidValue;
   a.kt = job.kt;
+  a.tile_slots = job.tile_slots;
   a.b = static_cast<const u32x4*>(job.b_src);
   a.b_rowmajor = job.b_rowmajor;
   a.b_ld = job.b_ld;

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kS32Waves * 64) void head_skinny32_kernel(HeadJob p
   // and the weight ring it has no registers left, and it is touched once per tile of several thousand cycles
   uint64_t* ldsK = reinterpret_cast<uint64_t*>(smem + kS32LdsP);
   const int wg = blockIdx.x, G = gridDim.x;
-  const int kt = p.kt, R = p.R;
+  const int kt = p.kt, R = p.R, slots = p.tile_slots;
   const int tid = opaque_tid(), lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: tile addresses stay in scalar registers
 
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kS32Waves * 64) void head_skinny32_kernel(HeadJob p
   const u32x4* wp = static_cast<const u32x4*>(p.w_proj);
   auto tile_slice = [&](int tile) {
     const int t = min(tile, total - 1);
-    const u32x4* base = t < p.vt_head ? wh + t * packed_tile_slots(kt) : wp + (t - p.vt_head) * packed_tile_slots(kt);
+    const u32x4* base = t < p.vt_head ? wh + packed_tile_start(t, slots) : wp + packed_tile_start(t - p.vt_head, slots);
     return weight_buffer(base + (int64_t)s0 * 64, tile < total ? ns * 1024 : 0);
   };
 

@@ -37,7 +37,7 @@ typedef const __attribute__((address_space(3))) u32x4 lds_word;
 struct TileArgs {
   const u32x4* w;    // packed head weights
   const u32x4* b;    // packed states
-  int kt, nt_total, n_valid, mt_total, R;
+  int kt, tile_slots, nt_total, n_valid, mt_total, R;
   int m_tiles, n_tiles, n_ranges, chunk;
   int k_top, nparts;
   Partials part;
@@ -109,7 +109,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
   for (int i = 0; i < G::SP; ++i) s_off[i] = min(min(i * kWaves + wave, G::SF - 1), mt_last) * kt * 1024;
   // The cursor moves by whole groups of kSteps steps: scalar work at every step would leave the matrix cores waiting.
   int c_step = 0, c_tile = t0;   // first step of the group that is copied, and its tile
-  const int tile_bytes = (int)packed_tile_slots(kt) * 16;
+  const int tile_bytes = p.tile_slots * 16;
   auto group_bufs = [&](auto& w, auto& s) {
     const int last = min(kWF, p.nt_total - c_tile * kWF) - 1;
 #pragma unroll
@@ -418,6 +418,7 @@ hipError_t launch_head_tile(const HeadJob& job, const TilePlan& pl, hipStream_t 
   a.w = static_cast<const u32x4*>(job.w_head);
   a.b = static_cast<const u32x4*>(job.b_src);
   a.kt = job.kt;
+  a.tile_slots = job.tile_slots;
   a.nt_total = job.vt_head;
   a.n_valid = job.n_head;
   a.mt_total = (job.R + 15) / 16;

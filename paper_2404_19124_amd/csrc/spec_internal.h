@@ -25,11 +25,14 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 //     address (in 16-byte slots) = (nt * (K/32) + t) * 64 + lane
 // so that a wave reads one fragment as one fully coalesced 1 KiB access.  Rows
 // beyond N are zero (weights) or unspecified (states).
-// Weight tiles lie four fragments further apart than they are long: tile nt starts at slot nt * packed_tile_slots(K / 32).
-// At K = 4096 a tile is 128 KiB, and workgroups that walk K in step, or start their tiles together, would ask the same
-// few channels and cache sets.  Launches of 32000 rows x 4096, us, tiles end to end / 4 KiB apart / 8 KiB:  1 row (with
-// the projection) 47.0 / 46.1 / 45.7, 15 rows 43.5 / 42.2 / 42.4, 24 rows of 49152 67.4 / 66.4 / 66.7, 384 rows 102 / 101 / 98;
-// 1 KiB apart, off the 4 KiB page, 64 and 96 rows lose 4 %.
+// Weight tiles of K = 2048 and 4096 (64 and 128 KiB) lie four fragments further apart than they are long: tile nt starts at
+// slot nt * packed_tile_slots(K / 32).  End to end, workgroups that walk K in step, or start their tiles together, ask the
+// same few channels and cache sets.  Launches end to end / 4 KiB apart, medians of eight processes: up to 16 rows 1.048 times
+// as fast at K = 2048 and 1.018 at 4096 (1 row of 32000 + projection, K = 4096: 47.0 / 46.1 us), 17 to 32 rows 1.048 and
+// 1.005; 33 to 64 rows lose 0.5 and 2 % (64 rows of 49152, K = 4096: 67.3 / 69.4), larger ones nothing on average (384 rows of
+// 49152 159 / 167).  Steps at K = 4096: batch 1 165.6 / 163.1, batch 5 189.3 / 185.5, 13B batch 16 265.4 / 257.7, mixed trees
+// 220.3 / 222.3.  Other widths stay end to end: they gain nothing (3072: 0.995, 5120 and 8192: 0.99), their launches of 33 to
+// 64 rows lose 2 to 4 %, and a tile of K = 64 would take three times its length.
 // ---------------------------------------------------------------------------
 
 // Partial result of a head contraction for one (row, part): the running maximum
@@ -43,7 +46,9 @@ struct Partials {
   int32_t* idx;
 };
 
-constexpr int64_t packed_tile_slots(int kt) { return (int64_t)(kt + 4) * 64; }
+constexpr int packed_tile_slots(int kt) { return (kt == 64 || kt == 128 ? kt + 4 : kt) * 64; }
+// slots in front of tile nt (a product of 32 by 32 bits)
+constexpr int64_t packed_tile_start(int nt, int slots) { return (int64_t)nt * slots; }
 
 // ---- packing --------------------------------------------------------------
 // src row-major [n_rows][k] bf16 -> dst packed with ceil(n_rows/16) row tiles, as weights or as states.
@@ -88,6 +93,7 @@ struct HeadJob {
   int k_top;
   Partials part;
   int nparts;
+  int tile_slots;         // packed_tile_slots(kt)
   float* out_head;
   int64_t ld_head;
   // projection epilogue: out_proj[r * ld_proj + d]

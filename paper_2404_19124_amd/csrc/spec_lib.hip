@@ -427,6 +427,7 @@ extern "C" spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t 
   HeadJob job;
   memset(&job, 0, sizeof(job));
   job.kt = kt;
+  job.tile_slots = packed_tile_slots(kt);
   job.R = rows;
   job.k_top = n_head > 0 ? k_top : 0;
   job.n_head = n_head;
@@ -492,6 +493,7 @@ static HeadJob make_head_job(const spec_model* m, const Workspace& ws, int stage
   HeadJob job;
   memset(&job, 0, sizeof(job));
   job.kt = b_ld / 32;
+  job.tile_slots = packed_tile_slots(job.kt);
   job.b_src = b_src;
   job.b_rowmajor = b_rowmajor ? 1 : 0;
   job.b_ld = b_ld;
