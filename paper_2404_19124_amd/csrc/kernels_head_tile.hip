@@ -1,5 +1,5 @@
-// Vocabulary head alone against many state rows: the compute-bound launches of a batched draft (320 and 960 rows per
-// stage for 64 sequences with a 5/3/2 tree, 768 and 2304 for 32 sequences with a 6/4/3/2 tree).
+// Vocabulary head alone against many state rows: the compute-bound launches of a batched draft (960 rows of the last stage for
+// 64 sequences with a 5/3/2 tree; 192, 768 and 2304 per stage for 32 sequences with a 6/4/3/2 tree).
 //
 // Bound: the power the matrix cores may draw, then what a CU pulls through its L2.  So the tile is as tall as the
 // accumulators allow, and the cheaper matrix instruction is taken:
@@ -9,6 +9,11 @@
 //    often per product (the clock falls to 1.6 GHz), 1220 with 16x16x32 (1.8 GHz, matrix cores 76 % busy).  The dense kernel's
 //    1 x 4 split of a 160-row block reads an operand byte from LDS up to twice as often, and its epilogue (vector ALU)
 //    runs alone on its SIMD;
+//  * no instance uses scratch memory.  Blocks of 256 rows did (18 registers of a wave, 22 with lists of three): written in front
+//    of every K loop, read behind it, and a reload waits for every copy in flight.  So there the weight fragments are read in
+//    place, the lane index is asked for anew and the third entries of the lists wait in LDS.  960 rows x 32000, us, with scratch
+//    and now: K = 128 26.0 and 22.7, 512 42.1 and 39.2, 4096 190.0 and 189.3; 768 x 128256 x 3072 445.5 and 440.0; 2304 rows
+//    1270 and 1274; 4096 x 128256 x 8192, 6 ms, 1 to 3 % more;
 //  * both operands are copied from memory straight into LDS (buffer loads to LDS), kSteps K-steps ahead and across the tiles
 //    of a range, one barrier per K-step.  The fragments of the next step are read into registers while the matrix
 //    cores work on this one's, and the copies and reads are issued one by one between the matrix instructions.  The cursor of
@@ -72,7 +77,10 @@ struct TileGeo {
   static constexpr int WP = kWF / kWaves;                // weight / state fragments a wave copies per step
   static constexpr int SP = (SF + kWaves - 1) / kWaves;
   static constexpr int COPIES = WP + SP;
+  static constexpr int KEEP = MB == 4 ? 8 : 0;
 };
+
+constexpr bool tile_parks(int mb, int kt) { return mb == 4 && kt == 3; }
 
 // N = copies of this wave that may still be in flight; all LDS reads have returned.  Then the barrier.
 template <int N, bool LDS>
@@ -89,18 +97,22 @@ __device__ __forceinline__ void copies_landed_barrier() {
 template <int MB, int KT>
 __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, int mtile, int range,
                                            lds_byte* __restrict b0, lds_byte* __restrict b1, lds_byte* __restrict b2,
-                                           lds_byte* __restrict b3, unsigned char* smem) {
+                                           lds_byte* __restrict b3, lds_byte* park, unsigned char* smem) {
   using G = TileGeo<MB>;
   static_assert(kSteps == 4, "four buffers");
   lds_byte* const bufs[kSteps] = {b0, b1, b2, b3};
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave / kWM, wm = wave % kWM;
-  const int col = lane & 15, grp = lane >> 4;
+  // The lane is asked for anew where it is needed: held across the K loop it is what does not fit the registers.
+  auto lane_id = []() {
+    uint32_t none = 0;
+    asm volatile("" : "+s"(none));   // (or the first answer is kept)
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
+  };
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave / kWM, wm = wave % kWM;
   const int kt = p.kt;
 
-  // ---- copies: 1 KiB = one fragment of the packed layout per instruction; wave w takes fragments w, w + 4, ...
+  // ---- copies: 1 KiB = one fragment of the packed layout per instruction; wave w takes fragments w, w + 8, ...
   // A fragment past the matrix or the block repeats the last one (its results are masked).
-  const int lane16 = lane * 16;
+  const int lane16 = lane_id() * 16;
   const unsigned char* const wb = reinterpret_cast<const unsigned char*>(p.w);
   const int mt0 = mtile * G::SF, mt_last = min(G::SF, p.mt_total - mt0) - 1;
   const unsigned char* const sb = reinterpret_cast<const unsigned char*>(p.b) + (int64_t)mt0 * kt * 1024;
@@ -147,21 +159,21 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     for (int i = 0; i < G::COPIES; ++i) copy(i, u);
   next_group();
 
-  // ---- fragments of one K-step in registers: two sets of states; a weight fragment makes room for the next step's as soon
-  // as its matrix instructions are issued
+  // ---- fragments of one K-step in registers: two sets of the states and of the last weight fragments; each of the first
+  // G::KEEP weight fragments makes room for the next step's as soon as its matrix instructions are issued
   u32x4 aw[2][kNB], bf[2][MB];
   const int a_at = wn * kNB * 1024 + lane16, b_at = (kWF + wm * MB) * 1024 + lane16;
-  auto read_a = [&](u32x4(&aw)[kNB], int u) {
-#pragma unroll
-    for (int n = 0; n < kNB; ++n) aw[n] = *reinterpret_cast<lds_word*>(bufs[u] + a_at + n * 1024);
+  auto read_a = [&](int u, int n) {   // fragment n of step u
+    aw[n < G::KEEP ? 0 : u & 1][n] = *reinterpret_cast<lds_word*>(bufs[u % kSteps] + a_at + n * 1024);
   };
-  auto read_b = [&](u32x4(&b)[MB], int u) {
-#pragma unroll
-    for (int m = 0; m < MB; ++m) b[m] = *reinterpret_cast<lds_word*>(bufs[u] + b_at + m * 1024);
+  auto read_b = [&](int u, int m) {
+    bf[u & 1][m] = *reinterpret_cast<lds_word*>(bufs[u % kSteps] + b_at + m * 1024);
   };
   copies_landed_barrier<(kSteps - 1) * G::COPIES, false>();
-  read_a(aw[0], 0);
-  read_b(bf[0], 0);
+#pragma unroll
+  for (int n = 0; n < kNB; ++n) read_a(0, n);
+#pragma unroll
+  for (int m = 0; m < MB; ++m) read_b(0, m);
 
   // running state of this lane, per state row 16 * (wm * MB + m) + col of the block: its best logits so far, and the sum of
   // exponentials relative to the first of them
@@ -174,10 +186,20 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     for (int q = 0; q < KT; ++q) lk[m][q] = __hiloint2double(__float_as_int(SPEC_NEG_INF), kIdxNone);
   }
 
+  // The third entries of the lists wait in LDS while the K loop runs (blocks of 256 rows: 8 registers of 256).
+  constexpr bool PARK = tile_parks(MB, KT);
+  volatile __attribute__((address_space(3))) double* const parked =
+      (volatile __attribute__((address_space(3))) double*)(park + (wave * 64 + lane_id()) * (MB * 8));
+  auto put = [&]() {
+#pragma unroll
+    for (int m = 0; m < MB; ++m) parked[m] = lk[m][KT - 1];
+  };
+  if (PARK) put();
+
   for (int t = t0; t < t1; ++t) {
     f32x4 acc[MB][kNB];
     // (weight rows past the vocabulary start, and stay, at -inf: no mask in the epilogue)
-    const int v0 = t * 256 + wn * 128 + grp * 4;   // this lane's weight rows: v0 + 16 n + i
+    const int v0 = t * 256 + wn * 128 + (lane_id() >> 4) * 4;   // this lane's weight rows: v0 + 16 n + i
 #pragma unroll
     for (int n = 0; n < kNB; ++n) {
       f32x4 z;
@@ -194,16 +216,20 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
         // every wave has read step u's buffer, and step u + 1 has landed for all of them
         copies_landed_barrier<(kSteps - 2) * G::COPIES, true>();
         __builtin_amdgcn_sched_barrier(0);
-        read_a(aw[(u+1)&1], (u + 1) % kSteps);
-        read_b(bf[(u + 1) & 1], (u + 1) % kSteps);
+#pragma unroll
+        for (int m = 0; m < MB; ++m) read_b(u + 1, m);
+#pragma unroll
+        for (int n = G::KEEP; n < kNB; ++n) read_a(u + 1, n);
 #pragma unroll
         for (int i = 0; i < G::COPIES; ++i) copy(i, u);
 #pragma unroll
-        for (int n = 0; n < kNB; ++n)
+        for (int n = 0; n < kNB; ++n) {
 #pragma unroll
           for (int m = 0; m < MB; ++m)
-            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aw[u & 1][n]),
-                                                                __builtin_bit_cast(bf16x8, bf[u & 1][m]), acc[m][n], 0, 0, 0);
+            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, aw[n < G::KEEP ? 0 : u & 1][n]), __builtin_bit_cast(bf16x8, bf[u & 1][m]), acc[m][n], 0, 0, 0);
+          if (n < G::KEEP) read_a(u + 1, n);
+        }
         // a wave issues in order: the reads, then the copies, one by one between the matrix instructions
         constexpr int NM = MB * kNB, NR = MB + kNB, NT = NR + G::COPIES;
 #pragma unroll
@@ -221,6 +247,10 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     }
 
     pin_accumulators<MB>(acc);
+    if (PARK) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m) lk[m][KT - 1] = parked[m];
+    }
 
     // ---- epilogue: a row's 32 logits of this lane into its list, whose first entry is then the running maximum, and their
     // exponentials into its sum.  The MB rows are independent chains: one logit each in turn.  No branch: the
@@ -271,6 +301,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int m = 0; m < MB; ++m) sum[m] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[m][n][i], kLog2e, ml[m]));
+    if (PARK && t + 1 < t1) put();
   }
 
   // ---- merge the 8 lane lists of every row (4 lane groups x 2 waves) into the workgroup's partial, as the wide
@@ -281,6 +312,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
   uint64_t* sk = reinterpret_cast<uint64_t*>(smem);            // [ROWS][RS]
   float* sm = reinterpret_cast<float*>(sk + ROWS * RS);        // [ROWS][8]
   float* ss = sm + ROWS * 8;
+  const int lane = lane_id(), tid = wave * 64 + lane, col = lane & 15, grp = lane >> 4;
   {
     const int src = wn * 4 + grp;   // this lane's place among the 8 that hold a row
 #pragma unroll
@@ -353,7 +385,7 @@ __global__ __launch_bounds__(kWaves * 64) void head_tile_kernel(TileArgs p) {
   const int t0 = (int)((int64_t)range * p.n_tiles / p.n_ranges);
   const int t1 = (int)((int64_t)(range + 1) * p.n_tiles / p.n_ranges);
   lds_byte* l = (lds_byte*)smem;
-  tile_range<MB, KT>(p, t0, t1, mtile, range, l, l + G::STEP, l + 2 * G::STEP, l + 3 * G::STEP, smem);
+  tile_range<MB, KT>(p, t0, t1, mtile, range, l, l + G::STEP, l + 2 * G::STEP, l + 3 * G::STEP, l + 4 * G::STEP, smem);
 }
 
 template <int MB, int KT>
@@ -370,12 +402,18 @@ static hipError_t launch_tile_t(const TileArgs& a, size_t smem, hipStream_t st, 
 }
 
 // Which head launches come here: alone (no projection), more than 64 rows, lists of at most 4, K in whole groups of kSteps
-// steps, and cheaper than the dense kernel by its own estimate.  Both estimates count tile rounds of the longest range; the
-// unit is the dense kernel's 96-row tile, as in plan_gemm.  Launches of 4096 x 32000 (320, 384, 960 rows) and 3072 x 128256
-// (192, 768, 2304), us, dense kernel / blocks of 192, 256 rows here:  320: 91 / 94, 116;  384: 120 / 97, 121;  960: 229 / 239,
-// 216;  192: 192 / 162, -;  768: 551 / 473, 454;  2304: 1569 / 1383, 1299.  So a tile costs 1.55 and 1.95.  One round each, as at
-// 320 rows, is bound by the weights' way from memory in both, and the dense kernel keeps what is not 5 % better here; so it
-// does where it shortens its tiles to reach more CUs.  (256 rows with lists of 4 do not fit the registers.)
+// steps (the cursor of the copies moves by groups; other widths stay with the dense kernel), and cheaper than the dense
+// kernel by its own estimate.  Both estimates count tile rounds of the longest range; the unit is the dense kernel's 96-row
+// tile, as in plan_gemm.  Launches of 4096 x 32000 (320, 384, 960 rows) and 3072 x 128256 (192, 768, 2304), us, dense kernel /
+// blocks of 192, 256 rows here:  320: 91 / 94, 116;  384: 120 / 97, 121;  960: 229 / 239, 216;  192: 192 / 162, -;  768: 551 /
+// 473, 454;  2304: 1569 / 1383, 1299 (another card: dense 103, 210, 201, 543, 1551; here, the better block, 84, 189, 160, 440,
+// 1274).  So a tile costs 1.55 and 1.95.  The quotient holds for short K too: drafts of one stage, 272 shapes of 128 to 4096 rows,
+// K = 128 to 8192 and 8000 to 128256 weight rows, and 260 random ones up to 26000 rows, are 1.007 to 1.38 times as fast where
+// the rule comes here (960 rows x 32000: K = 128 58.8 / 55.7, 512 79.8 / 74.1, 1024 105.2 / 96.5); the least, 0.99 and 1.0, are
+// 17000 and 20000 rows x 8000, where row blocks nearly fill the CUs by themselves.  One round each, as at 320 rows, is bound by the
+// weights' way from memory in both, and the dense kernel keeps what is not 5 % better here; so it does where it shortens its
+// tiles to reach more CUs, and where its blocks outnumber the CUs, whose rounds its estimate does not count.  (256 rows with
+// lists of 4 do not fit the registers: 36 bytes of scratch a lane, parked entries and all.)
 TilePlan plan_tile(int R, int k_top, int n_head, int kt, int n_cu) {
   TilePlan best;
   memset(&best, 0, sizeof(best));
@@ -403,7 +441,8 @@ TilePlan plan_tile(int R, int k_top, int n_head, int kt, int n_cu) {
 }
 
 size_t tile_lds_bytes(const TilePlan& pl) {
-  const size_t steps = (size_t)kSteps * (kWF + 2 * pl.block) * 1024;
+  const size_t steps = (size_t)kSteps * (kWF + 2 * pl.block) * 1024 +
+                       (tile_parks(pl.block / 2, pl.kcap) ? (size_t)kWaves * 64 * (pl.block / 2) * 8 : 0);
   const size_t merge = (size_t)32 * pl.block * ((8 * pl.kcap + 1) * 8 + 8 * 8);
   return steps > merge ? steps : merge;
 }
