@@ -31,8 +31,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 // as fast at K = 2048 and 1.018 at 4096 (1 row of 32000 + projection, K = 4096: 47.0 / 46.1 us), 17 to 32 rows 1.048 and
 // 1.005; 33 to 64 rows lose 0.5 and 2 % (64 rows of 49152, K = 4096: 67.3 / 69.4), larger ones nothing on average (384 rows of
 // 49152 159 / 167).  Steps at K = 4096: batch 1 165.6 / 163.1, batch 5 189.3 / 185.5, 13B batch 16 265.4 / 257.7, mixed trees
-// 220.3 / 222.3.  Other widths stay end to end: they gain nothing (3072: 0.995, 5120 and 8192: 0.99), their launches of 33 to
-// 64 rows lose 2 to 4 %, and a tile of K = 64 would take three times its length.
+// 220.3 / 222.3.  Other widths stay end to end: they gain nothing (3072: 0.995; steps of K = 8192 0.95 to 1.02,
+// 12288 1.005) or lose (16384: 0.91 to 0.97), their launches of 33 to 64 rows lose 2 to 4 %, and a tile of K = 64 would take
+// three times its length.
 // ---------------------------------------------------------------------------
 
 // Partial result of a head contraction for one (row, part): the running maximum

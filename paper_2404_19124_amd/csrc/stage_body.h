@@ -69,8 +69,12 @@ __device__ __forceinline__ void stage_rows(const StageJob& j, int parent, int ra
 #pragma unroll
       for (int u = 0; u < (BF16 ? 1 : 2); ++u) raw[h][ci][u] = row[(at8[ci] >> 3) * (BF16 ? 1 : 2) + u];
   }
-  // a projection split along K: its other parts, added in order, four of them (long rows: two) on their way at a time
-  constexpr int PU = NCH > 2 ? 2 : 4;
+  // a projection split along K: its other parts, added in order.  All three there can be on their way at once; rows past 4096
+  // elements, whose threads hold two chunks: as many as leave the kernel below 129 registers, so that two workgroups share a
+  // CU.  (Four in both cases, 130 to 166 registers: D = 6144, 255 parents of 6 36.0 us, 255 rows of stage 0 9.9, and now 26.5 and
+  // 8.1; one chunk, D = 4096, 255 parents of 3 11.4, now 10.0.  Three siblings of 6144 together with two parts 18.4, with one 16.1.)
+  static_assert(kMaxKSplit == 4, "three other parts");
+  constexpr int PU = NCH == 1 ? 3 : NCH == 2 && KC == 3 ? 1 : 2;
   for (int q0 = 1; q0 < j.pz_parts; q0 += PU) {
     float pq[PU][NCH][8];
 #pragma unroll

@@ -1,0 +1,38 @@
+"""What kernels rely on of their registers (host-only: reads the metadata of the built library)."""
+import struct
+
+import pytest
+
+from paper_2404_19124_amd import binding as B
+
+msgpack = pytest.importorskip("msgpack")
+
+
+def kernels():
+    """(name, metadata) of every kernel of the library: the notes of its code objects."""
+    data = open(B.LIB_PATH, "rb").read()
+    at = data.find(b"AMDGPU\0\0")
+    while at >= 0:
+        name_size, size, kind = struct.unpack_from("<III", data, at - 12)
+        if (name_size, kind) == (7, 32):
+            for k in msgpack.unpackb(data[at + 8:at + 8 + size])["amdhsa.kernels"]:
+                yield k[".name"], k
+        at = data.find(b"AMDGPU\0\0", at + 8)
+
+
+def test_tile_kernel_without_scratch():
+    """A reload would wait for every copy in flight, and the spills of 256 persistent workgroups are traffic of their own."""
+    B.lib()
+    found = {name: k[".private_segment_fixed_size"] for name, k in kernels() if "head_tile_kernel" in name}
+    assert len(found) == 5 and not any(found.values()), found
+
+
+def test_stage_kernels_share_a_cu():
+    """Rows of up to 4096 elements one chunk per thread, up to 8192 two: of the latter two workgroups of 512 threads fit a CU's 512
+    registers per lane (four siblings at a time do not), of the former three."""
+    B.lib()
+    found = {name: k[".vgpr_count"] for name, k in kernels() if "stage_kernel" in name}
+    two = {name: n for name, n in found.items() if "ELi2ELi512EE" in name}
+    one = {name: n for name, n in found.items() if "ELi1ELi512EE" in name}
+    assert len(two) == 14 and max(two.values()) <= 128, two
+    assert len(one) == 14 and max(one.values()) <= 80, one
