@@ -153,10 +153,6 @@ __device__ __forceinline__ uint64_t row16_best_key(uint64_t key) {
   key = key_step<kDppHalfMirror>(key);
   return key_step<kDppMirror>(key);
 }
-// best (value, index) over each row of 16 lanes
-__device__ __forceinline__ void row16_best(float& v, int32_t& i) {
-  best_unkey(row16_best_key(best_key(v, i)), v, i);
-}
 
 __device__ __forceinline__ float wave_sum(float x) {
   x = row16_sum(x);

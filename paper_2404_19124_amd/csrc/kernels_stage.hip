@@ -131,14 +131,13 @@ __global__ __launch_bounds__(NT) void tree_kernel(TreeJob j) {
   __shared__ __align__(16) uint64_t sk[kMaxLeaves];
   __shared__ int s_k[kMaxStages], s_kw[kMaxStages];
   __shared__ int64_t s_off[kMaxStages], s_rbase[kMaxStages];
-  __shared__ __align__(16) float merge_lds[KWAVE ? kMergeLds * (NT / 256) : 1];
   __shared__ int32_t c_tok[KWAVE ? kMaxLeaves : 1];
   __shared__ float c_logp[KWAVE ? kMaxLeaves : 1];
   TreeArgs a;
   tree_args_for_sequence(j, blockIdx.x, a, s_k, s_off, s_rbase, s_kw);
-  // (no barrier here: a wave reads back only what it wrote itself until the merge in tree_body ends in one,
-  // so it starts its loads while the later waves of the workgroup are still being launched)
-  tree_body<NT, KWAVE>(a, blockIdx.x, s_k, s_off, s_rbase, s_kw, sk, merge_lds, c_tok, c_logp);
+  // (no barrier here: a wave reads back only what it wrote itself, so it starts its loads while the later waves
+  // of the workgroup are still being launched)
+  tree_body<NT, KWAVE>(a, blockIdx.x, s_k, s_off, s_rbase, s_kw, sk, c_tok, c_logp);
 }
 
 // The last head's tables ahead of the tree kernel, one row per wave and workgroup, over the whole chip.  Bound: latency, one trip

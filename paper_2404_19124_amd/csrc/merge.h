@@ -125,7 +125,7 @@ __device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t
   else wave_merge_partials_un<K, 4>(p, row, nparts, k, out_val, out_idx, lse);
 }
 
-// The same merge done by a group of 256 consecutive threads for ONE row: with at most
+// The same merge for the ONE row that a whole workgroup wants, by its first 256 threads: with at most
 // 256 parts every thread holds exactly one part's (already sorted) list, so nothing has
 // to be inserted.  Two levels, ONE exchange: every wave reduces its 64 parts to its own
 // (max, sum-exp, k best) with wave-wide reductions only, the four waves' results go
@@ -134,11 +134,11 @@ __device__ __forceinline__ void wave_merge_partials_k(const Partials& p, int64_t
 // - one barrier and one LDS exchange per result - took 0.65 us per round on the batch-1 chain; the four
 // lists merged in registers by every thread, K shifts of 4 K keys each, made the stage kernel take 7.5 us
 // for 5 rows (256 parts, top-5), 21.7 for 960 rows and 34.4 for 2304, against 6.8, 19.5 and 27.1.)
-// A workgroup of 256 * n threads runs n such groups side by side, each on its own row, or one for all (ONE, below):
-// the function contains workgroup barriers, so EVERY thread of the workgroup must call it, with the same k
-// and nparts.  Lane c < 4 K of every wave of the group receives candidate c (value, index, rank; the k
-// best have ranks 0 .. k - 1), the other lanes rank kNoRank; every thread receives lse.  `lds` is the
-// group's own scratch of kMergeLds words, 8-byte aligned.
+// The other threads of a larger workgroup wait at the barrier: they would only take issue slots, eight waves on four SIMDs
+// (stage kernel, 5 rows of top-5, 7.0 us with both groups of 256 merging, 6.0 with one; 96 rows of top-6 9.6 and 8.5; top-1 4.8
+// either way).  EVERY thread of the workgroup must call, with the same k and nparts.  Lane c < 4 K of every wave receives
+// candidate c (value, index, rank; the k best have ranks 0 .. k - 1), the other lanes rank kNoRank; every thread receives
+// lse.  `lds` is scratch of kMergeLds words, 8-byte aligned, that nobody has used before.
 constexpr int kMergeWave = 2 + 2 * kMaxTopK;   // words per wave: max, sum-exp, k keys
 constexpr int kMergeLds = 4 * kMergeWave;
 constexpr int kNoRank = 1 << 20;
@@ -162,17 +162,13 @@ __device__ __forceinline__ void group_merge_load(const Partials& p, int64_t row,
     x.i[j] = pi[jc];
   }
 }
-// ONE: the whole workgroup wants the same row, `lds` is the workgroup's and nobody has used it before: the first 256
-// threads merge, the others wait at the barrier (they would only take issue slots: eight waves on four SIMDs.  Stage
-// kernel, 5 rows of top-5, 7.0 us with both groups merging, 6.0 with one; 96 rows of top-6 9.6 and 8.5; top-1 4.8 either way).
-template <int K, bool ONE>
+template <int K>
 __device__ __forceinline__ void group_merge_loaded(const MergePart<K>& x, const Partials& p, int64_t row, int nparts, int k,
                                                  float& out_val, int32_t& out_idx, int& rank,
                                                  float& lse, float* lds) {
   const int tid = opaque_tid(), gt = tid & 255, lane = gt & 63, w = gt >> 6;
 
-  if (!ONE) __syncthreads();                          // scratch may still be read from an earlier call
-  if (!ONE || __builtin_amdgcn_readfirstlane(tid >> 8) == 0) {
+  if (__builtin_amdgcn_readfirstlane(tid >> 8) == 0) {
     uint64_t tk[K];   // the thread's list as keys (best_key)
     const bool ok = gt < nparts;
     float run_m = ok ? x.m : SPEC_NEG_INF, run_s = ok ? x.s : 0.f;
@@ -252,29 +248,6 @@ __device__ __forceinline__ void group_merge_loaded(const MergePart<K>& x, const 
   best_unkey(key, out_val, out_idx);
   if (out_idx > kIdxNone - 4 * kMaxTopK) out_idx = kIdxNone;   // (an empty entry: no token has such an index)
   rank = lane < 4 * K ? before_me : kNoRank;
-}
-
-template <int K>
-__device__ __forceinline__ void group_merge_partials_k(const Partials& p, int64_t row, int nparts, int k,
-                                                     float& out_val, int32_t& out_idx, int& rank,
-                                                     float& lse, float* lds) {
-  MergePart<K> x;
-  group_merge_load<K>(p, row, nparts, k, x);
-  group_merge_loaded<K, false>(x, p, row, nparts, k, out_val, out_idx, rank, lse, lds);
-}
-
-__device__ __forceinline__ void group_merge_partials(const Partials& p, int64_t row, int nparts, int k,
-                                                     float& out_val, int32_t& out_idx, int& rank,
-                                                     float& lse, float* lds) {
-  switch (k) {
-    case 1: group_merge_partials_k<1>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
-    case 2: group_merge_partials_k<2>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
-    case 3: group_merge_partials_k<3>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
-    case 4: group_merge_partials_k<4>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
-    case 5:
-    case 6: group_merge_partials_k<6>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
-    default: group_merge_partials_k<8>(p, row, nparts, k, out_val, out_idx, rank, lse, lds); break;
-  }
 }
 
 // k is uniform over the launch: pick the list size that just holds it, so that

@@ -50,7 +50,7 @@ __device__ __forceinline__ void stage_rows(const StageJob& j, int parent, int ra
 #pragma unroll
     for (int h = 0; h < KC; ++h) tok[h] = j.last_tok[parent];   // (uniform tree: parent == r)
   } else {
-    group_merge_loaded<K ? K : 1, true>(list, j.part, parent, j.nparts, j.k_prev, v, ix, at, lse, lds + 32 * KC);
+    group_merge_loaded<K ? K : 1>(list, j.part, parent, j.nparts, j.k_prev, v, ix, at, lse, lds + 32 * KC);
 #pragma unroll
     for (int h = 0; h < KC; ++h) {
       const int rank = h < live ? rank0 + h : rank0;
@@ -203,15 +203,14 @@ struct TreeArgs {
 // s_k / s_off / s_rbase / s_kw: per stage, in LDS (indexing kernel arguments with a run-time stage
 // number would make the compiler spill the argument block to scratch): this sequence's branching,
 // the table's element offset, this sequence's first row, the table's width.
-// sk: kMaxLeaves 64-bit words of LDS (the leaves' scores as keys, see best_key); merge_lds: (NT / 256) * kMergeLds words; c_tok / c_logp: kMaxLeaves words
+// sk: kMaxLeaves 64-bit words of LDS (the leaves' scores as keys, see best_key); c_tok / c_logp: kMaxLeaves words
 // each, the last stage's tables of this sequence for the leaf scores (the tables in memory are written all
 // the same: the debug outputs and the caller's next step read them).
-// KWAVE: widest kw_last merged one row per wave (register-hungry for wide lists: a wave
-// of a 1024-thread workgroup has 128 registers); wider ones are merged one row per
-// 256-thread group; 0: the tables of the last stage are there already.  Contains workgroup barriers.
+// KWAVE: widest kw_last there is (merged one row per wave: register-hungry for wide lists, a wave of a 1024-thread
+// workgroup has 128 registers); 0: the tables of the last stage are there already.  Contains workgroup barriers.
 template <int NT, int KWAVE>
 __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s_k, const int64_t* s_off,
-                                          const int64_t* s_rbase, const int* s_kw, uint64_t* sk, float* merge_lds,
+                                          const int64_t* s_rbase, const int* s_kw, uint64_t* sk,
                                           int32_t* c_tok, float* c_logp) {
   const int tid = opaque_tid(), lane = tid & 63, wave = tid >> 6;
   const int n = j.n, L = j.L, kw = j.kw_last;
@@ -257,8 +256,7 @@ __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s
     }
   }
 
-  if (KWAVE == 0) {
-  } else if (kw <= KWAVE) {
+  if (KWAVE > 0) {
     // (the first wave has just spent its time on the leaves' paths: it stays out of the merge when the
     // other waves cover the rows in one pass)
     const int w0 = (early && rows_last <= NT / 64 - 1) ? 1 : 0;
@@ -289,28 +287,6 @@ __device__ __forceinline__ void tree_body(const TreeArgs& j, int q, const int* s
         }
       if (lane == 0) j.lse[j.row_off_last + row] = lse;
     }
-  } else {
-    const int grp = tid >> 8, gl = tid & 255;
-    for (int r0 = 0; r0 < rows_last; r0 += NT / 256) {
-      const int rl = r0 + grp;
-      const bool live = rl < rows_last;
-      const int64_t row = j.rbase_last + (live ? rl : rows_last - 1);
-      float v, lse;
-      int32_t ix;
-      int at;
-      group_merge_partials(j.part, row, j.nparts, kw, v, ix, at, lse, merge_lds + grp * kMergeLds);
-      if (live && gl < 64 && at < kw) {
-        j.tok[j.off_last + row * kw + at] = ix;
-        j.logp[j.off_last + row * kw + at] = v - lse;
-        if (early) {
-          c_tok[rl * kw + at] = ix;
-          c_logp[rl * kw + at] = v - lse;
-        }
-      }
-      if (live && gl == 0) j.lse[j.row_off_last + row] = lse;
-    }
-  }
-  if (KWAVE > 0) {
     __threadfence_block();
     __syncthreads();
   }
