@@ -137,9 +137,11 @@ def _dtype_code(name: str) -> int:
 
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        # (a Stream object made only to ask it for its address costs 2 us, a sixth of what a verify takes on the host)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # (a Stream object made only to ask it for its address costs 2 us, a sixth of what a verify takes on the host; the
+        # lookup without one is not part of torch's public interface, so it may be missing)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None) if torch.cuda.is_initialized() else None
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
