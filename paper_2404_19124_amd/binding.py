@@ -135,13 +135,16 @@ def _dtype_code(name: str) -> int:
     return {"f32": SPEC_F32, "bf16": SPEC_BF16}[name]
 
 
+# The current stream's address without a Stream object made only to ask for it, which costs 2 us, a sixth of what a verify takes
+# on the host.  Neither is part of torch's public interface, so they may be missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
-        # (a Stream object made only to ask it for its address costs 2 us, a sixth of what a verify takes on the host; the
-        # lookup without one is not part of torch's public interface, so it may be missing)
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None) if torch.cuda.is_initialized() else None
-        if raw is not None:
-            return raw(torch.cuda.current_device())
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
