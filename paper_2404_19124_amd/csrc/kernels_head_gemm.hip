@@ -176,6 +176,7 @@ double dense_head_cost(int R, int k_top, int n_head, int kt, int n_cu) {
 // that is a little longer than a multiple of the ranges makes the launch one tile longer for a few ranges
 // (320 rows against 125 + 16 tiles: 128 ranges, 13 of them with two tiles).  Then two launches are cheaper:
 // the head alone in one even round, the projection alone split along K over the whole chip.
+// (The head alone is priced as the dense kernel's, also where the tile kernel would take it.)
 bool plan_projection_apart(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   if (R <= 64 || n_head <= 0 || n_proj <= 0) return false;   // wide kernel only
   const GemmPlan both = plan_gemm(R, k_top, n_head, n_proj, kt, n_cu);

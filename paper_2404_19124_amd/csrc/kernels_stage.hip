@@ -178,7 +178,11 @@ hipError_t launch_tree(const TreeJob& job, hipStream_t st) {
   const int rows_last = job.seq_desc ? kMaxLeaves : job.L / job.top_k[job.n - 1];
   // More rows per sequence than one pass of sixteen waves: a pass is 3 us and more of arithmetic on one CU while others
   // are idle, and the rows get a launch of their own.  Tree kernel alone, and both launches, us: 24 rows x 16 sequences
-  // 16.2 and 13.0, 72 x 32 19.8 and 13.4; in one pass 15 x 64 12.2 and 11.8, 15 x 5 10.3 and 10.5, 15 x 1 8.5 and 9.6.
+  // 16.2 and 13.0, 72 x 32 19.8 and 13.4; in one pass 15 x 64 12.2 and 11.8, 15 x 5 10.3 and 10.5, 15 x 1 8.5 and 9.6: the
+  // line goes by the rows of a sequence alone, and from some dozens of sequences of 15 rows on it leaves 0.4 us behind.
+  // The tree kernel then only scores and ranks: a leaf per thread up to 256, since small workgroups share a CU (256 leaves,
+  // 256 and 1024 threads, us: 600 sequences 10.0 and 21.3, 32 sequences 8.3 and 8.0, 1 sequence 7.3 and 7.1); with more
+  // leaves 1024 threads (320 leaves 15.3 and 9.1, 512 20.9 and 11.9).
   if (!job.seq_desc && rows_last > 16) {
     launch_merge_rows(job, st);
     hipError_t e = hipGetLastError();
