@@ -22,7 +22,7 @@ SPEC_OK, SPEC_EINVAL, SPEC_ESHAPE, SPEC_EDTYPE, SPEC_ENOMEM, SPEC_EHIP = 0, -1, 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libspecdraft.so")
 
 EXPORTS = ["spec_create", "spec_destroy", "spec_draft", "spec_draft_static", "spec_draft_dynamic", "spec_verify", "spec_verify_dynamic", "spec_head_logp", "spec_model_scalars",
-           "spec_profile_enable", "spec_profile_read", "spec_copy_probe", "spec_tree_metadata", "spec_advance", "spec_plan_contraction", "spec_plan_head", "spec_last_error", "spec_version"]
+           "spec_profile_enable", "spec_profile_read", "spec_copy_probe", "spec_tree_metadata", "spec_advance", "spec_plan_contraction", "spec_plan_head", "spec_plan_panel", "spec_last_error", "spec_version"]
 
 
 class SpecError(RuntimeError):
@@ -102,6 +102,8 @@ def lib() -> C.CDLL:
         l.spec_plan_contraction.argtypes = [C.c_int32] * 6 + [C.POINTER(spec_plan_t)]
         l.spec_plan_head.restype = C.c_int
         l.spec_plan_head.argtypes = [C.c_int32] * 5 + [C.POINTER(spec_plan_t)]
+        l.spec_plan_panel.restype = C.c_int
+        l.spec_plan_panel.argtypes = [C.c_int32] * 6 + [C.POINTER(spec_plan_t)]
         l.spec_tree_metadata.restype = C.c_int
         l.spec_tree_metadata.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32] + [C.c_void_p] * 7
         l.spec_advance.restype = C.c_int
@@ -474,6 +476,13 @@ def spec_plan_head(rows: int, k: int, n_head: int, k_top: int, n_cu: int = 256) 
     """The launch plan of a head that is launched alone for its top-k (host-only: needs no GPU)."""
     out = spec_plan_t()
     _check(lib().spec_plan_head(int(rows), int(k), int(n_head), int(k_top), int(n_cu), C.byref(out)))
+    return {name: int(getattr(out, name)) for name, _ in spec_plan_t._fields_}
+
+
+def spec_plan_panel(rows: int, k: int, n_head: int, k_top: int, n_proj: int, n_cu: int = 256) -> dict:
+    """The launch plan of a draft's head and the projection that rides with it (host-only: needs no GPU)."""
+    out = spec_plan_t()
+    _check(lib().spec_plan_panel(int(rows), int(k), int(n_head), int(k_top), int(n_proj), int(n_cu), C.byref(out)))
     return {name: int(getattr(out, name)) for name, _ in spec_plan_t._fields_}
 
 

@@ -27,6 +27,7 @@ SOURCES = [
     "kernels_head_skinny32.hip",
     "kernels_head_gemm.hip",
     "kernels_head_tile.hip",
+    "kernels_head_panel.hip",
     "kernels_tree_meta.hip",
 ]
 

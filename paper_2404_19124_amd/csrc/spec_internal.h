@@ -159,6 +159,19 @@ size_t tile_lds_bytes(const TilePlan& plan);
 hipError_t launch_head_tile(const HeadJob& job, const TilePlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
                             hipEvent_t ev_stop = nullptr);
 
+// A head (top-k partials), alone or with the next projection, against 17 to 128 rows: tiles of up to nine 16-row weight tiles
+// against all state rows.  block = 0: not for this kernel.
+struct PanelPlan {
+  int block, kcap;           // 16-row state fragments, capacity of the per-lane top-k lists
+  int ts;                    // 16-row weight tiles of a workgroup tile
+  int n_head, n_tiles;       // workgroup tiles of the head, of both matrices
+  int n_ranges, nparts;      // contiguous ranges of the tiles, one workgroup each; those that hold head tiles
+};
+PanelPlan plan_panel(int R, int k_top, int n_head, int n_proj, int kt, int n_cu);
+size_t panel_lds_bytes(const PanelPlan& plan);
+hipError_t launch_head_panel(const HeadJob& job, const PanelPlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
+                             hipEvent_t ev_stop = nullptr);
+
 // ---- contraction, float32 ----------------------------------------------------
 // out[r * ldo + v] = sum_k a[r * K + k] * w[v * K + k]
 hipError_t launch_store_f32(const float* a, const float* w, float* out, int64_t ldo, int R, int N, int K, hipStream_t st);

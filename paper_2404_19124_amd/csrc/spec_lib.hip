@@ -475,6 +475,26 @@ extern "C" spec_status_t spec_plan_head(int32_t rows, int32_t k, int32_t n_head,
   return SPEC_OK;
 }
 
+extern "C" spec_status_t spec_plan_panel(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_proj,
+                                         int32_t n_cu, spec_plan_t* out) {
+  spec_status_t s = spec_plan_contraction(rows, k, n_head, k_top, n_proj, n_cu, out);
+  if (s != SPEC_OK) return s;
+  const PanelPlan pp = plan_panel(rows, k_top, n_head, n_proj, k / 32, n_cu);
+  if (!pp.block) return SPEC_OK;
+  memset(out, 0, sizeof(*out));
+  out->kernel = 300 + 10 * pp.block + pp.kcap;
+  out->block_rows = 16 * pp.block;
+  out->tile_rows = 16 * pp.ts;
+  out->row_blocks = 1;
+  out->ranges = pp.n_ranges;
+  out->tiles = pp.n_tiles;
+  out->parts = pp.nparts;
+  out->k_split = 1;
+  out->workgroups = pp.n_ranges;
+  out->lds_bytes = (int32_t)panel_lds_bytes(pp);
+  return SPEC_OK;
+}
+
 extern "C" spec_status_t spec_copy_probe(const void* src, void* dst, int64_t bytes, void* hip_stream) {
   if (!src || !dst) return fail(SPEC_EINVAL, "a required pointer is NULL");
   if (bytes <= 0 || bytes % 16) return fail(SPEC_EINVAL, "bytes = %lld must be a positive multiple of 16", (long long)bytes);
@@ -531,6 +551,18 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
     const int slot = prof_slot(m, R <= 16 ? 0 : 2, R, job.n_head + job.n_proj, K);
     HIP_TRY((R <= 16 ? launch_head_skinny : launch_head_skinny32)(job, m->n_cu, st, EV0(slot), EV1(slot)));
     return SPEC_OK;
+  }
+  if (stage >= 0 && !out_head && !b_rowmajor) {
+    const PanelPlan pp = plan_panel(R, k_top, job.n_head, job.n_proj, job.kt, m->n_cu);
+    if (pp.block) {
+      job.nparts = pp.nparts;
+      *nparts = job.nparts;
+      if ((int64_t)R * job.nparts > ws.part_rows_parts)
+        return fail(SPEC_ESHAPE, "internal: partial workspace too small (%d rows x %d parts)", R, job.nparts);
+      const int slot = prof_slot(m, 300 + 10 * pp.block + pp.kcap, R, job.n_head + job.n_proj, K);
+      HIP_TRY(launch_head_panel(job, pp, st, EV0(slot), EV1(slot)));
+      return SPEC_OK;
+    }
   }
   if (stage >= 0 && proj_stage < 0 && !out_head && !b_rowmajor) {
     const TilePlan tp = plan_tile(R, k_top, job.n_head, job.kt, m->n_cu);
@@ -725,6 +757,7 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
       }
       const int proj_next = i + 1 < n ? i + 1 : -1;
       if (m->bf16 && proj_next >= 0 && !skinny_fits((int)R[i], D / 32) &&
+          !plan_panel((int)R[i], top_k[i], V, D, D / 32, m->n_cu).block &&
           plan_projection_apart((int)R[i], top_k[i], V, D, D / 32, m->n_cu)) {
         // the head in one even round of tiles, then the next projection on its own, split along K
         spec_status_t s = run_contraction(m, ws, i, -1, ws.states, false, D, (int)R[i], top_k[i], nullptr, nullptr,

@@ -1,0 +1,56 @@
+"""Host logic of the panel kernel's plan (no GPU): what it takes is covered whole, fits the CU's LDS and the partial-result
+workspace, and no range of the projection alone counts as a part; everything else keeps the general plan."""
+import random
+
+import pytest
+
+from paper_2404_19124_amd import binding as B
+
+
+def check(rows, k, n_head, k_top, n_proj, n_cu):
+    p = B.spec_plan_panel(rows, k, n_head, k_top, n_proj, n_cu)
+    what = "rows=%d k=%d n_head=%d k_top=%d n_proj=%d n_cu=%d -> %s" % (rows, k, n_head, k_top, n_proj, n_cu, p)
+    if not 300 <= p["kernel"] < 1000:
+        assert p == B.spec_plan_contraction(rows, k, n_head, k_top, n_proj, n_cu), what
+        return p
+    mf, kt = divmod(p["kernel"] - 300, 10)
+    assert 16 < rows <= 128 and mf in (2, 3, 4, 5, 6, 8) and kt in (2, 3, 4, 6, 8) and kt >= k_top, what
+    assert p["block_rows"] == 16 * mf >= rows and p["row_blocks"] == 1, what
+    head = -(-n_head // p["tile_rows"])
+    assert 16 <= p["tile_rows"] <= 144 and p["tiles"] == head + -(-n_proj // p["tile_rows"]), what
+    starts = [r * p["tiles"] // p["ranges"] for r in range(p["ranges"])]
+    assert p["workgroups"] == p["ranges"] <= min(n_cu, p["tiles"]) and len(set(starts)) == len(starts), what
+    assert p["parts"] == sum(s < head for s in starts) >= 1, what
+    assert rows * p["parts"] <= max(128, rows) * n_cu and 0 < p["lds_bytes"] <= 160 * 1024, what
+    return p
+
+
+def test_invariants_over_random_shapes():
+    rnd = random.Random(20241204)
+    taken = 0
+    for _ in range(4000):
+        n_head = rnd.choice([rnd.randint(1, 3000), rnd.randint(3000, 200000)])
+        p = check(rnd.choice([rnd.randint(1, 200), rnd.randint(17, 128)]), 64 * rnd.randint(1, 128), n_head, rnd.randint(1, 8),
+                  rnd.choice([0, 64 * rnd.randint(1, 128)]), rnd.choice([256, 256, 304, 128, 40, 7]))
+        taken += 300 <= p["kernel"] < 1000
+    assert taken > 200
+
+
+# the lines of the rule, and launches whose times it rests on: state fragments, or 0 where another kernel stays
+@pytest.mark.parametrize("args,block", [((64, 4096, 32000, 5, 4096), 4), ((96, 4096, 32000, 4, 4096), 6), ((75, 4096, 32000, 2, 0), 5),
+                                        ((33, 4096, 32000, 3, 4096), 3), ((128, 4096, 32000, 3, 0), 8), ((129, 4096, 32000, 3, 0), 0),
+                                        ((32, 3072, 128256, 6, 3072), 2), ((32, 4096, 32000, 5, 4096), 0), ((16, 4096, 32000, 5, 4096), 0),
+                                        ((33, 3072, 128256, 6, 3072), 0), ((48, 4096, 49152, 1, 0), 0), ((64, 4096, 16384, 2, 0), 0),
+                                        ((64, 4096, 16385, 2, 0), 4), ((64, 1024, 2000, 2, 0), 4), ((64, 1088, 2000, 2, 0), 0),
+                                        ((65, 4096, 2000, 2, 0), 5), ((64, 4096, 36864, 2, 0), 4), ((64, 4096, 36865, 2, 0), 0)])
+def test_who_takes_which_launch(args, block):
+    p = check(*args, 256)
+    assert (p["block_rows"] // 16 if 300 <= p["kernel"] < 1000 else 0) == block
+
+
+@pytest.mark.parametrize("args", [(0, 4096, 32000, 2, 0, 256), (64, 100, 32000, 2, 0, 256), (64, 4096, 32000, 9, 0, 256),
+                                  (64, 4096, 32000, 0, 0, 256), (64, 4096, 0, 0, 0, 256), (64, 4096, 32000, 2, 0, 0)])
+def test_bad_arguments(args):
+    with pytest.raises(B.SpecError) as e:
+        B.spec_plan_panel(*args)
+    assert e.value.status == B.SPEC_EINVAL
