@@ -118,6 +118,34 @@ def lib() -> C.CDLL:
     return _lib
 
 
+_fast = None   # the native half of the binding (csrc/call.cpp), once it is loaded
+
+
+def _native():
+    global _fast
+    if _fast is None:
+        l = lib()
+        try:
+            from . import _call
+        except ImportError as e:
+            raise RuntimeError("_call.so is missing or does not load: run `python -m paper_2404_19124_amd.build`; there is no "
+                               "fallback path") from e
+        at = [C.cast(f, C.c_void_p).value for f in (l.spec_verify, l.spec_verify_dynamic, l.spec_advance, l.spec_tree_metadata,
+                                                    l.spec_draft)]
+        _call.bind(*at, lambda stream: _stream_ptr(stream))
+        _fast = _call
+    return _fast
+
+
+def _done(status: Optional[int]) -> bool:
+    """What a native call answered: None = not the usual case, nothing has happened."""
+    if status is None:
+        return False
+    if status:
+        _check(status)
+    return True
+
+
 def spec_last_error() -> str:
     return lib().spec_last_error().decode()
 
@@ -254,6 +282,10 @@ def spec_draft(model: SpecModel, state: torch.Tensor, last_tok: torch.Tensor, to
                dbg: Optional[Dict[str, torch.Tensor]] = None, stream=None) -> None:
     """Enqueues one draft.  All tensors are caller-allocated device tensors."""
     cfg = model.cfg
+    if dbg is None and _CHECK_DEVICE and _done((_fast or _native()).draft(
+            model.handle.value if model.handle else None, cfg.n_predict, cfg.emb_dim, cfg.weight_dtype, state, last_tok, top_k, B,
+            cand_tokens, cand_scores, cand_leaf, stream)):
+        return
     n, D = cfg.n_predict, cfg.inner_dim
     wdt = _TORCH_DTYPE[cfg.weight_dtype]
     top_k = [int(k) for k in top_k]
@@ -373,6 +405,9 @@ def spec_verify_dynamic(base_logits: torch.Tensor, cand_tokens: torch.Tensor, n_
                         out_tokens: torch.Tensor, n_out: torch.Tensor, accept_all: Optional[torch.Tensor] = None,
                         stream=None) -> None:
     """Enqueues one verify in which sequence q has n_cand[q] candidates (0 = speculation off)."""
+    if n_cand is not None and _CHECK_DEVICE and _done((_fast or _native()).verify(
+            base_logits, cand_tokens, n_cand, greedy, accept_len, best_cand, out_tokens, n_out, accept_all, stream)):
+        return
     if not isinstance(base_logits, torch.Tensor) or base_logits.dim() != 4:
         raise ValueError("base_logits must be a [batch, B, n_predict + 1, vocab] tensor")
     b, B, n1, V = base_logits.shape
@@ -397,6 +432,9 @@ def spec_verify(base_logits: torch.Tensor, cand_tokens: torch.Tensor, greedy: to
                 best_cand: torch.Tensor, out_tokens: torch.Tensor, n_out: torch.Tensor,
                 accept_all: Optional[torch.Tensor] = None, stream=None) -> None:
     """Enqueues one verify.  base_logits [batch, B, n+1, V] float32 or bfloat16."""
+    if _CHECK_DEVICE and _done((_fast or _native()).verify(
+            base_logits, cand_tokens, None, greedy, accept_len, best_cand, out_tokens, n_out, accept_all, stream)):
+        return
     if not isinstance(base_logits, torch.Tensor) or base_logits.dim() != 4:
         raise ValueError("base_logits must be a [batch, B, n_predict + 1, vocab] tensor")
     b, B, n1, V = base_logits.shape
@@ -431,6 +469,9 @@ def spec_profile_read(model: SpecModel, cap: int = 65536):
 def spec_tree_metadata(cand_tokens: torch.Tensor, node_tok: torch.Tensor, node_parent: torch.Tensor,
                        node_depth: torch.Tensor, n_nodes: torch.Tensor, cand_node: torch.Tensor,
                        mask: Optional[torch.Tensor] = None, stream=None) -> None:
+    if _CHECK_DEVICE and _done((_fast or _native()).tree_metadata(cand_tokens, node_tok, node_parent, node_depth, n_nodes, cand_node,
+                                                                  mask, stream)):
+        return
     if not isinstance(cand_tokens, torch.Tensor) or cand_tokens.dim() != 3:
         raise ValueError("cand_tokens must be a [batch, B, n_predict] tensor")
     b, Bc, n = cand_tokens.shape
@@ -449,6 +490,8 @@ def spec_tree_metadata(cand_tokens: torch.Tensor, node_tok: torch.Tensor, node_p
 
 def spec_advance(hidden: torch.Tensor, best_cand: torch.Tensor, accept_len: torch.Tensor, out_tokens: torch.Tensor,
                  next_state: torch.Tensor, next_tok: torch.Tensor, stream=None) -> None:
+    if _CHECK_DEVICE and _done((_fast or _native()).advance(hidden, best_cand, accept_len, out_tokens, next_state, next_tok, stream)):
+        return
     if not isinstance(hidden, torch.Tensor) or hidden.dim() != 4:
         raise ValueError("hidden must be a [batch, B, n_predict + 1, emb_dim] tensor")
     b, Bc, n1, E = hidden.shape

@@ -11,12 +11,15 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspecdraft.so")
+
+CALL = os.path.join(HERE, "_call.so")   # the binding's native half (host code, against torch's headers)
 
 SOURCES = [
     "spec_lib.hip",
@@ -65,10 +68,28 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_call() -> None:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = os.path.join(root, "include")
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", inc,
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "call.cpp"), "-o", CALL,
+           # (loaded by `import torch` already: no search path of its own)
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for call.cpp:\n" + r.stderr)
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        call = ex.submit(_compile_call)
         objs = list(ex.map(_compile, SOURCES))
+        call.result()
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
