@@ -43,6 +43,8 @@ def kernel_name(kid: int) -> str:
     if kid >= 1000:
         mb, rest = divmod(kid - 1000, 100)
         return "head_gemm32_kernel<%d, 2, %d, %s>" % (mb, rest // 2, "true" if rest % 2 else "false")
+    if kid >= 400:
+        return "head_once_kernel<%d, %d>" % divmod(kid - 400, 10)
     if kid >= 300:
         return "head_panel_kernel<%d, %d>" % divmod(kid - 300, 10)
     if kid >= 100:

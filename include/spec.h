@@ -225,6 +225,7 @@ spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const void* states,
  *           100 + 20 * MB + KT = tile kernel of many rows, head_tile_kernel<MB,KT> (a head without a projection;
  *           64 * MB-row blocks, per-lane top-k lists of KT entries),
  *           300 + 10 * MF + KT = panel kernel of some dozens of rows, head_panel_kernel<MF,KT> (16 * MF state rows, lists of KT),
+ *           400 + 10 * MB + KT = head_once_kernel<MB,KT> (a head with a projection, 64 * MB state rows, one tile per CU),
  *           1000 + 100 * MB + 2 * KT + VT = wide dense kernel head_gemm32_kernel<MB,2,KT,VT>
  *           (32 * MB-row state blocks, per-lane top-k lists of KT entries, VT = 1 with short tiles)
  *   rows, weight_rows, k: the contraction is [rows, k] x [weight_rows, k]^T
@@ -312,7 +313,7 @@ spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t n_head, int
  * spec_plan_contraction's, which describes the other kernels only. */
 spec_status_t spec_plan_head(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_cu, spec_plan_t* out);
 /* The same for a head with (or, n_proj = 0, without) the next projection as a draft launches it for its top-k: where the panel
- * kernel takes it, that kernel's plan, ahead of both above; else spec_plan_contraction's. */
+ * kernel or head_once_kernel takes it, that kernel's plan, ahead of both above; else spec_plan_contraction's. */
 spec_status_t spec_plan_panel(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_proj, int32_t n_cu,
                               spec_plan_t* out);
 

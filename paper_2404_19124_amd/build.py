@@ -31,6 +31,7 @@ SOURCES = [
     "kernels_head_gemm.hip",
     "kernels_head_tile.hip",
     "kernels_head_panel.hip",
+    "kernels_head_once.hip",
     "kernels_tree_meta.hip",
 ]
 

@@ -1,0 +1,422 @@
+// Vocabulary head and the next stage's projection in one launch against 129 to 320 state rows, where every CU has at most one tile
+// of weight rows: the middle stages of a batched draft (320 rows of 64 sequences with a 5/3/2 tree).
+//
+// The two were two launches (head alone, one round of tiles; projection split along K, its four partial sums added by the stage
+// kernel) or one whose tile list was a little longer than a round.  160 weight rows to a tile put both into one round of a
+// launch whose blocks hold all state rows, so no weight is read twice.
+// Bound: the requests a CU may have outstanding.  Its L1 keeps about 90 lines of 128 bytes on their way whatever the kernel has
+// asked for (averages of the counters in these launches: 87 to 92, 640 to 950 cycles each), so a line from HBM costs a CU about
+// 700 / 90 cycles and one from L2 300 / 90, and the two add up: copies of the states alone take 42 us of the launch below, of the
+// weights alone 55, of both 95, with the matrix work 103, which alone would take 55.
+//  * Workgroup = 8 waves; tile = 160 weight rows x 64 * MB state rows, a wave 80 x 16 * MB of it (MB = 5: 100 accumulators of
+//    v_mfma_f32_16x16x32_bf16, two sets of fragments beside them).
+//  * Both operands are copied straight into LDS (buffer loads to LDS), the weights eight K-steps ahead, the states four, by
+//    different waves: a wave's copies land in order, and a wait for its states would be one for its youngest weights.
+//    One barrier per K-step; LDS reads and copies are issued one by one between the matrix instructions.
+// 320 rows x (32000 + 4096) x 4096: 89.5 + 24.4 us in two launches, 103 in one; 4096 + 32000 rows, drafts of two
+// stages against 130, 192, 256 rows 1.15, 1.19, 1.09 times as fast.
+#include <hip/hip_ext.h>
+
+#include <cstring>
+
+#include "device_utils.h"
+#include "spec_internal.h"
+
+namespace specdraft {
+
+constexpr int kOnceWaves = 8;      // two along the weight rows, four along the state rows
+constexpr int kOnceWM = 4;
+constexpr int kOnceCopyW = 2;      // waves that copy weights; the others copy states
+constexpr int kOnceDW = 8;         // K-steps (of 32) of weights in LDS
+constexpr int kOnceDS = 4;         // and of states
+constexpr int kOnceNB = 5;         // 16-row weight fragments of a wave
+constexpr int kOnceLds = 160 * 1024;
+
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef const __attribute__((address_space(3))) u32x4 lds_word;
+
+struct OnceArgs {
+  const u32x4* w[2];   // packed weights: head, projection
+  int n_frags[2];      // their 16-row tiles
+  int n_head;          // workgroup tiles of the head; the projection's follow
+  int n_valid, kt, tile_slots;
+  const u32x4* b;      // packed states
+  int mt_total, R;
+  float* out;          // projection
+  int64_t ldo;
+  int k_top, nparts;
+  Partials part;
+};
+
+// MB = state fragments of a wave.
+template <int MB>
+struct OnceGeo {
+  static constexpr int NB = kOnceNB, WF = 2 * NB, SF = kOnceWM * MB;       // fragments of a K-step
+  static constexpr int W_STEP = WF * 1024, S_STEP = SF * 1024;
+  static constexpr int WC = WF / kOnceCopyW;                 // copies of a wave per step
+  static constexpr int SC = (SF + kOnceWaves - kOnceCopyW - 1) / (kOnceWaves - kOnceCopyW);
+  static constexpr int S_AT = kOnceDW * W_STEP;
+  static constexpr int BYTES = S_AT + kOnceDS * S_STEP;
+  static_assert(BYTES <= kOnceLds, "a CU has no more");
+};
+constexpr size_t once_merge_bytes(int mb, int kt) { return (size_t)64 * mb * ((8 * kt + 1) * 8 + 8 * 8); }
+
+// ---- top-k lists: one float64 per entry (high word = the logit, low word breaks ties), as in the tile kernel ----
+__device__ __forceinline__ double once_key(float x, int32_t not_index) {
+  const int32_t b = __float_as_int(x);
+  return __hiloint2double(b, not_index ^ (b >> 31));
+}
+__device__ __forceinline__ float once_logit(double key) { return __int_as_float(__double2hiint(key)); }
+__device__ __forceinline__ int32_t once_index(double key) { return ~(__double2loint(key) ^ (__double2hiint(key) >> 31)); }
+__device__ __forceinline__ float once_reference(double best) { return fmaxf(-2e38f, once_logit(best)); }
+
+// N = copies of this wave that may still be in flight; all LDS reads have returned.  Then the barrier.
+template <int N, bool LDS>
+__device__ __forceinline__ void once_barrier() {
+  static_assert(N >= 0 && N < 64, "the counter has six bits");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (LDS ? 0 : 15 << 8));
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// WEIGHTS: what this wave copies.  The slots of that ring are distinct objects to the compiler (restrict): a read of one then waits
+// only for this wave's copies into that one, which the counted wait in front of the barrier has already seen land, and not for
+// every copy in flight.  The other ring, which this wave only reads, goes by the plain pointer: what it holds changes behind
+// every barrier.
+template <int MB, int KT, bool WEIGHTS>
+__device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_byte* __restrict c0, lds_byte* __restrict c1,
+                                          lds_byte* __restrict c2, lds_byte* __restrict c3, lds_byte* __restrict c4,
+                                          lds_byte* __restrict c5, lds_byte* __restrict c6, lds_byte* __restrict c7,
+                                          unsigned char* smem) {
+  using G = OnceGeo<MB>;
+  constexpr int NB = G::NB;
+  static_assert(kOnceDW == 8 && kOnceDS == 4, "the slots");
+  lds_byte* const mine[8] = {c0, c1, c2, c3, c4, c5, c6, c7};   // (four of them for the states)
+  constexpr int C = WEIGHTS ? G::WC : G::SC, DEPTH = WEIGHTS ? kOnceDW : kOnceDS;
+  const int lane = threadIdx.x & 63, lane16 = lane * 16;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave / kOnceWM, wm = wave % kOnceWM;
+  const int kt = p.kt, range = blockIdx.x;
+  const bool head = range < p.n_head;
+  const int mat = head ? 0 : 1, f0 = (range - (head ? 0 : p.n_head)) * G::WF;   // first fragment of the tile
+
+  // ---- copies: 1 KiB = one fragment of the packed layout.  A fragment past the matrix or the block repeats the last one.
+  const int tile_bytes = p.tile_slots * 16, w_last = min(G::WF, p.n_frags[mat] - f0) - 1, s_last = min(G::SF, p.mt_total) - 1;
+  const unsigned char* const src = WEIGHTS ? reinterpret_cast<const unsigned char*>(p.w[mat]) + (int64_t)f0 * tile_bytes
+                                           : reinterpret_cast<const unsigned char*>(p.b);
+  const int span = WEIGHTS ? (w_last + 1) * tile_bytes : (s_last + 1) * kt * 1024;
+  int from[C], to[C];
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+    const int f = WEIGHTS ? wave * G::WC + i : min((wave - kOnceCopyW) + i * (kOnceWaves - kOnceCopyW), G::SF - 1);
+    from[i] = WEIGHTS ? min(f, w_last) * tile_bytes : min(f, s_last) * kt * 1024;
+    to[i] = f * 1024;
+  }
+  auto group_buf = [&](int step) {   // from K-step `step` on
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src + step * 1024), 0, span - step * 1024, 0x00020000);
+  };
+  auto copy = [&](__amdgpu_buffer_rsrc_t buf, int i, int u, int at) {   // into slot u, from step `at` of the buffer's group
+    lds_byte* const dst = mine[u % DEPTH] + to[i];
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)dst, 16, lane16, from[i] + at * 1024, 0,
+                                             WEIGHTS ? 2 : 0);
+  };
+  __amdgpu_buffer_rsrc_t here = group_buf(0);
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u)
+#pragma unroll
+    for (int i = 0; i < C; ++i) copy(here, i, u, u);
+
+  // ---- fragments of two K-steps in registers
+  u32x4 aw[2][NB], bf[2][MB];
+  const int a_at = wn * NB * 1024 + lane16, b_at = wm * MB * 1024 + lane16;
+  auto read_a = [&](int u, int n) {
+    lds_byte* const slot = WEIGHTS ? mine[u % kOnceDW] : lds + (u % kOnceDW) * G::W_STEP;
+    aw[u & 1][n] = *reinterpret_cast<lds_word*>(slot + a_at + n * 1024);
+  };
+  auto read_b = [&](int u, int m) {
+    lds_byte* const slot = WEIGHTS ? lds + G::S_AT + (u % kOnceDS) * G::S_STEP : mine[u % kOnceDS];
+    bf[u & 1][m] = *reinterpret_cast<lds_word*>(slot + b_at + m * 1024);
+  };
+  once_barrier<(DEPTH - 1) * C, false>();
+#pragma unroll
+  for (int n = 0; n < NB; ++n) read_a(0, n);
+#pragma unroll
+  for (int m = 0; m < MB; ++m) read_b(0, m);
+
+  f32x4 acc[MB][NB];
+  // (weight rows past the vocabulary start, and stay, at -inf: no mask in the epilogue)
+  const int v0 = (f0 + wn * NB) * 16 + (lane >> 4) * 4;   // this lane's weight rows: v0 + 16 n + i
+  const int v_end = head ? p.n_valid : 0x7fffffff;
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    f32x4 z;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z[i] = v0 + n * 16 + i < v_end ? 0.f : SPEC_NEG_INF;
+#pragma unroll
+    for (int m = 0; m < MB; ++m) acc[m][n] = z;
+  }
+
+  for (int base = 0; base < kt; base += kOnceDW) {
+    // (past the last step the last group again: nobody reads it, and it is in the L2)
+    const auto next = group_buf(min(base + kOnceDW, kt - kOnceDW));
+#pragma unroll
+    for (int u = 0; u < kOnceDW; ++u) {
+      // every wave has read step u's slots, and step u + 1 has landed for all of them
+      once_barrier<(DEPTH - 2) * C, true>();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < MB; ++m) read_b(u + 1, m);
+#pragma unroll
+      for (int n = 0; n < NB; ++n) read_a(u + 1, n);
+#pragma unroll
+      for (int i = 0; i < C; ++i) {
+        if (WEIGHTS) copy(next, i, u, u);
+        else if (u < kOnceDS) copy(here, i, u, u + kOnceDS);
+        else copy(next, i, u, u - kOnceDS);
+      }
+#pragma unroll
+      for (int n = 0; n < NB; ++n)
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+          acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, aw[u & 1][n]),
+                                                              __builtin_bit_cast(bf16x8, bf[u & 1][m]), acc[m][n], 0, 0, 0);
+      // a wave issues in order: the reads, then the copies, one by one between the matrix instructions
+      constexpr int NM = MB * NB, NR = MB + NB, NT = NR + C;
+#pragma unroll
+      for (int i = 0; i < NM; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+#pragma unroll
+        for (int j = i * NT / NM; j < (i + 1) * NT / NM; ++j) {
+          if (j < NR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          else __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    here = next;
+  }
+
+  const int col = lane & 15, grp = lane >> 4;
+  if (!head) {
+    // ---- store: lane = state row lane % 16 of every state fragment, four consecutive columns of each weight fragment
+    once_barrier<0, true>();   // (LDS goes back with nothing on its way into it)
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+      if (f0 + wn * NB + n < p.n_frags[1]) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+          const int r = (wm * MB + m) * 16 + col;
+          if (r < p.R) *reinterpret_cast<f32x4*>(p.out + (int64_t)r * p.ldo + v0 + n * 16) = acc[m][n];
+        }
+      }
+    }
+    return;
+  }
+
+  // ---- epilogue: a row's 4 NB logits of this lane into its list, and their exponentials into its sum.  The MB rows are
+  // independent chains: one logit each in turn.
+  float sum[MB];
+  double lk[MB][KT];
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int q = 0; q < KT; ++q) lk[m][q] = __hiloint2double(__float_as_int(SPEC_NEG_INF), kIdxNone);
+  constexpr float kLog2e = 1.4426950408889634f;
+  // NaN counts as -inf in the lists: the median with the two infinities is the smaller of them then.  (In registers the
+  // optimiser cannot look through: it would take the median of x and known infinities for x.)
+  float lowest = SPEC_NEG_INF, highest = -SPEC_NEG_INF;
+  asm volatile("" : "+v"(lowest), "+v"(highest));
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int32_t not_index = ~(v0 + n * 16 + i);
+      asm volatile("" : "+v"(not_index));   // (one value for the MB rows)
+      double key[MB];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) key[m] = once_key(__builtin_amdgcn_fmed3f(acc[m][n][i], lowest, highest), not_index);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < KT; ++q) {   // down the lists, the smaller of each pair moves on
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+          const double old = lk[m][q];
+          lk[m][q] = __builtin_fmax(old, key[m]);
+          if (q + 1 < KT) key[m] = __builtin_fmin(old, key[m]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  float ml[MB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    sum[m] = 0.f;
+    ml[m] = -once_reference(lk[m][0]) * kLog2e;
+  }
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int m = 0; m < MB; ++m) sum[m] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[m][n][i], kLog2e, ml[m]));
+
+  // ---- merge the 8 lane lists of every row (4 lane groups x 2 waves) into the workgroup's partial.  LDS aliases the copies'
+  // buffers: all copies land first, for all waves.
+  once_barrier<0, true>();
+  constexpr int ROWS = 64 * MB, RS = 8 * KT + 1;
+  uint64_t* sk = reinterpret_cast<uint64_t*>(smem);            // [ROWS][RS]
+  float* sm = reinterpret_cast<float*>(sk + ROWS * RS);        // [ROWS][8]
+  float* ss = sm + ROWS * 8;
+  {
+    const int list = wn * 4 + grp;   // this lane's place among the 8 that hold a row
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      const int rl = (wm * MB + m) * 16 + col;
+#pragma unroll
+      for (int q = 0; q < KT; ++q) sk[rl * RS + list * KT + q] = best_key(once_logit(lk[m][q]), once_index(lk[m][q]));
+      sm[rl * 8 + list] = once_reference(lk[m][0]);
+      ss[rl * 8 + list] = sum[m];
+    }
+  }
+  __syncthreads();
+  const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
+#pragma unroll 1
+  for (int r0 = wave * 8; r0 < p.R; r0 += kOnceWaves * 8) {
+    const int r = min(r0 + (lane >> 3), p.R - 1), s8 = lane & 7;
+    const bool live = r0 + (lane >> 3) < p.R;
+    uint64_t hk[KT];
+#pragma unroll
+    for (int q = 0; q < KT; ++q) hk[q] = sk[r * RS + s8 * KT + q];
+    const float m = sm[r * 8 + s8], s = ss[r * 8 + s8];
+    float mx = fmaxf(m, dpp_f<kDppXor1>(m));
+    mx = fmaxf(mx, dpp_f<kDppXor2>(mx));
+    mx = fmaxf(mx, dpp_f<kDppHalfMirror>(mx));
+    float tot = s * __expf(m - mx);
+    tot += dpp_f<kDppXor1>(tot);
+    tot += dpp_f<kDppXor2>(tot);
+    tot += dpp_f<kDppHalfMirror>(tot);
+    const int64_t slot = (int64_t)r * p.nparts + range;
+    if (live && s8 == 0) {
+      p.part.m[slot] = mx;
+      p.part.s[slot] = tot;
+    }
+#pragma unroll
+    for (int j = 0; j < KT; ++j) {
+      if (j < p.k_top) {
+        uint64_t best = key_step<kDppXor1>(hk[0]);
+        best = key_step<kDppXor2>(best);
+        best = key_step<kDppHalfMirror>(best);
+        const bool won = hk[0] == best;   // the owner of the winner pops it
+#pragma unroll
+        for (int q = 0; q + 1 < KT; ++q) {
+          const uint64_t up = opaque_key(hk[q + 1]);
+          hk[q] = won ? up : hk[q];
+        }
+        hk[KT - 1] = won ? kEmpty : hk[KT - 1];
+        if (live && s8 == j) {
+          float bv;
+          int32_t bi;
+          best_unkey(best, bv, bi);
+          p.part.val[slot * p.k_top + j] = bv;
+          p.part.idx[slot * p.k_top + j] = bi;
+        }
+      }
+    }
+  }
+}
+
+template <int MB, int KT>
+__global__ __launch_bounds__(kOnceWaves * 64) void head_once_kernel(OnceArgs p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  using G = OnceGeo<MB>;
+  lds_byte* const l = (lds_byte*)smem;
+  lds_byte* const s = l + G::S_AT;
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < kOnceCopyW)
+    once_tile<MB, KT, true>(p, l, l, l + G::W_STEP, l + 2 * G::W_STEP, l + 3 * G::W_STEP, l + 4 * G::W_STEP, l + 5 * G::W_STEP,
+                                l + 6 * G::W_STEP, l + 7 * G::W_STEP, smem);
+  else
+    once_tile<MB, KT, false>(p, l, s, s + G::S_STEP, s + 2 * G::S_STEP, s + 3 * G::S_STEP, nullptr, nullptr, nullptr, nullptr,
+                                 smem);
+}
+
+static constexpr size_t once_lds(int mb, int kt) {
+  const size_t rings = (size_t)kOnceDW * 2 * kOnceNB * 1024 + (size_t)kOnceDS * kOnceWM * mb * 1024;
+  return once_merge_bytes(mb, kt) > rings ? once_merge_bytes(mb, kt) : rings;
+}
+
+template <int MB, int KT>
+static hipError_t launch_once_t(const OnceArgs& a, int grid, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  constexpr size_t smem = once_lds(MB, KT);
+  static_assert(smem <= kOnceLds && smem >= (size_t)OnceGeo<MB>::BYTES, "a CU has no more");
+  static bool attr_set = false;  // per instantiation
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_once_kernel<MB, KT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipExtLaunchKernelGGL((head_once_kernel<MB, KT>), dim3(grid), dim3(kOnceWaves * 64), smem, st, ev_start, ev_stop, 0, a);
+  return hipGetLastError();
+}
+
+// Which launches come here: a head with the next projection, lists of at most 4, K in whole groups of eight steps (the copies
+// move by groups; other widths stay with the dense kernels), more than 128 weight rows of the two per CU and all tiles in one
+// round.  Drafts of two stages of top-1 against 130, 192, 256, 320 rows, the kernels there were before / this one, us ratio:
+// 28000 + 6144 rows 1.11, 1.11, 1.09, 1.04;  32000 + 1024 1.06, 1.06, 1.05, 1.03;  + 3072 1.20, 1.21, 1.16, 1.08;  + 4096 1.15,
+// 1.19, 1.09, 1.05;  + 6144 1.11, 1.15, 1.06, 1.06;  + 2048 1.02, 1.01, 0.96, 0.96, hence the line at 192 rows for K = 2048.  384 rows 0.98
+// to 1.08.  Up to 128 rows per CU the head alone and the projection behind it are as fast or faster (28000 + 4096 1.11, 1.06,
+// 0.98, 0.94;  20000 + 4096 0.97 to 0.89), and so is a head without a projection on the tile kernel (32000: 0.98, 0.94, 0.88, 0.90).
+OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
+  OncePlan pl;
+  memset(&pl, 0, sizeof(pl));
+  const int64_t cus = n_cu > 0 ? n_cu : 256;
+  if (R <= 128 || R > (kt == 64 ? 192 : 320) || n_head <= 0 || n_proj <= 0 || k_top < 1 || k_top > 4 || kt % kOnceDW) return pl;
+  constexpr int kRows = 32 * kOnceNB;
+  const int64_t head = ((int64_t)n_head + kRows - 1) / kRows, tiles = head + ((int64_t)n_proj + kRows - 1) / kRows;
+  if ((int64_t)n_head + n_proj <= 128 * cus || tiles > cus) return pl;
+  pl.block = (R + 63) / 64;
+  pl.kcap = k_top < 2 ? 2 : k_top;
+  pl.n_head = (int)head;
+  pl.n_tiles = (int)tiles;
+  return pl;
+}
+
+size_t once_lds_bytes(const OncePlan& pl) { return once_lds(pl.block, pl.kcap); }
+
+hipError_t launch_head_once(const HeadJob& job, const OncePlan& pl, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (job.vt_head <= 0 || job.out_head || job.b_rowmajor || job.kt % kOnceDW || job.kt < kOnceDW || job.k_top > pl.kcap ||
+      job.nparts != pl.n_head || job.R > 64 * pl.block)
+    return hipErrorInvalidValue;
+  OnceArgs a;
+  memset(&a, 0, sizeof(a));
+  a.w[0] = static_cast<const u32x4*>(job.w_head);
+  a.w[1] = static_cast<const u32x4*>(job.w_proj);
+  a.n_frags[0] = job.vt_head;
+  a.n_frags[1] = job.vt_proj;
+  a.n_head = pl.n_head;
+  a.n_valid = job.n_head;
+  a.kt = job.kt;
+  a.tile_slots = job.tile_slots;
+  a.b = static_cast<const u32x4*>(job.b_src);
+  a.mt_total = (job.R + 15) / 16;
+  a.R = job.R;
+  a.out = job.out_proj;
+  a.ldo = job.ld_proj;
+  a.k_top = job.k_top;
+  a.nparts = job.nparts;
+  a.part = job.part;
+  switch (pl.block * 10 + pl.kcap) {
+    case 32: return launch_once_t<3, 2>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 33: return launch_once_t<3, 3>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 34: return launch_once_t<3, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 42: return launch_once_t<4, 2>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 43: return launch_once_t<4, 3>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 44: return launch_once_t<4, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 52: return launch_once_t<5, 2>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 53: return launch_once_t<5, 3>(a, pl.n_tiles, st, ev_start, ev_stop);
+    case 54: return launch_once_t<5, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace specdraft

@@ -172,6 +172,16 @@ size_t panel_lds_bytes(const PanelPlan& plan);
 hipError_t launch_head_panel(const HeadJob& job, const PanelPlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr);
 
+// A head with the next projection against 129 to 320 rows, all of both in one round of 160-weight-row tiles x all state rows.
+struct OncePlan {
+  int block, kcap;           // 64-row units of the state rows (0: not for this kernel), capacity of the per-lane top-k lists
+  int n_head, n_tiles;       // workgroup tiles of the head (= parts per row), of both matrices
+};
+OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu);
+size_t once_lds_bytes(const OncePlan& plan);
+hipError_t launch_head_once(const HeadJob& job, const OncePlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
+                            hipEvent_t ev_stop = nullptr);
+
 // ---- contraction, float32 ----------------------------------------------------
 // out[r * ldo + v] = sum_k a[r * K + k] * w[v * K + k]
 hipError_t launch_store_f32(const float* a, const float* w, float* out, int64_t ldo, int R, int N, int K, hipStream_t st);

@@ -480,6 +480,18 @@ extern "C" spec_status_t spec_plan_panel(int32_t rows, int32_t k, int32_t n_head
   spec_status_t s = spec_plan_contraction(rows, k, n_head, k_top, n_proj, n_cu, out);
   if (s != SPEC_OK) return s;
   const PanelPlan pp = plan_panel(rows, k_top, n_head, n_proj, k / 32, n_cu);
+  const OncePlan op = plan_once(rows, k_top, n_head, n_proj, k / 32, n_cu);
+  if (op.block) {
+    memset(out, 0, sizeof(*out));
+    out->kernel = 400 + 10 * op.block + op.kcap;
+    out->block_rows = 64 * op.block;
+    out->tile_rows = 160;
+    out->row_blocks = 1;
+    out->ranges = out->tiles = out->workgroups = op.n_tiles;
+    out->parts = op.n_head;
+    out->k_split = 1;
+    out->lds_bytes = (int32_t)once_lds_bytes(op);
+  }
   if (!pp.block) return SPEC_OK;
   memset(out, 0, sizeof(*out));
   out->kernel = 300 + 10 * pp.block + pp.kcap;
@@ -561,6 +573,16 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
         return fail(SPEC_ESHAPE, "internal: partial workspace too small (%d rows x %d parts)", R, job.nparts);
       const int slot = prof_slot(m, 300 + 10 * pp.block + pp.kcap, R, job.n_head + job.n_proj, K);
       HIP_TRY(launch_head_panel(job, pp, st, EV0(slot), EV1(slot)));
+      return SPEC_OK;
+    }
+    const OncePlan op = plan_once(R, k_top, job.n_head, job.n_proj, job.kt, m->n_cu);
+    if (op.block) {
+      job.nparts = op.n_head;
+      *nparts = job.nparts;
+      if ((int64_t)R * job.nparts > ws.part_rows_parts)
+        return fail(SPEC_ESHAPE, "internal: partial workspace too small (%d rows x %d parts)", R, job.nparts);
+      const int slot = prof_slot(m, 400 + 10 * op.block + op.kcap, R, job.n_head + job.n_proj, K);
+      HIP_TRY(launch_head_once(job, op, st, EV0(slot), EV1(slot)));
       return SPEC_OK;
     }
   }
@@ -758,6 +780,7 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
       const int proj_next = i + 1 < n ? i + 1 : -1;
       if (m->bf16 && proj_next >= 0 && !skinny_fits((int)R[i], D / 32) &&
           !plan_panel((int)R[i], top_k[i], V, D, D / 32, m->n_cu).block &&
+          !plan_once((int)R[i], top_k[i], V, D, D / 32, m->n_cu).block &&
           plan_projection_apart((int)R[i], top_k[i], V, D, D / 32, m->n_cu)) {
         // the head in one even round of tiles, then the next projection on its own, split along K
         spec_status_t s = run_contraction(m, ws, i, -1, ws.states, false, D, (int)R[i], top_k[i], nullptr, nullptr,

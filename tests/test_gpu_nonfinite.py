@@ -13,9 +13,10 @@ pytestmark = pytest.mark.gpu
 BIG = 3.0e38   # a head row of it: the logit of a state around 1 overflows
 
 
-def _first_stage(dtype, V, batch, k, edit):
-    """The tables of a one-stage draft, and its states and head."""
-    wl = W.Workload("nonfinite", 128, 128, V, 1, (k,), k, batch, dtype, "f32", 0.5, seed=43, emb_std=0.3)
+def _first_stage(dtype, V, batch, k, edit, D=128, stages=1):
+    """The tables of the first stage of a draft (by default its only one), and its states and head."""
+    top_k = (k,) + (1,) * (stages - 1)
+    wl = W.Workload("nonfinite", 128, D, V, stages, top_k, k, batch, dtype, "f32", 0.5, seed=43, emb_std=0.3)
     gen = W.make_generator(wl.seed)
     w = W.make_speculator(wl, gen)
     w["ln_beta"][0] += 1.0
@@ -173,3 +174,38 @@ def test_tile_kernel_rows_of_nan_only(batch, V, k, block):
     assert torch.isnan(tables[1]["lse"][odd]).all()
     tok = tables[1]["tok"][odd]
     assert (((tok >= 0) & (tok < V)) | (tok == 2**31 - 1)).all()
+
+
+# the panel kernel's ranges of one and of two tiles, and head and projection in one round: finite logits follow in the same tile
+PANELS = [(70, 3001, 3, 128, 1, 300), (17, 70001, 2, 128, 1, 300), (140, 33601, 2, 256, 2, 400)]
+
+
+@pytest.mark.parametrize("batch,V,k,D,stages,kernel", PANELS)
+def test_panel_kernel(batch, V, k, D, stages, kernel):
+    """Logits of -inf count nothing; one that is NaN, first or last of the vocabulary, shows in the sum and takes no place."""
+    assert kernel <= B.spec_plan_panel(batch, D, V, k, D if stages > 1 else 0)["kernel"] < kernel + 100
+    low = np.zeros(V, bool)
+    low[:V // 3] = True
+    low[V // 2::7] = True
+
+    def edit(head):
+        head[torch.from_numpy(low)] = -BIG
+
+    got, head = _first_stage("bf16", V, batch, k, edit, D, stages)
+    assert (got["states"].sum(1) > 2).all()
+    logits = O.head_logits(got["states"], head)
+    logits[:, low] = -np.inf
+    logp, lse = O.log_softmax(logits)
+    assert np.abs(got["lse"] - lse).max() < 1e-3
+    for r in range(batch):
+        assert np.array_equal(got["tok"][r], O.topk_desc(logits[r].astype(np.float32), k))
+    for at in (0, -1):
+        def nan(head):
+            head[at] = float("nan")
+
+        got, head = _first_stage("bf16", V, batch, k, nan, D, stages)
+        assert np.isnan(got["lse"]).all() and np.isnan(got["logp"]).all()
+        logits = O.head_logits(got["states"], head)
+        logits[:, at] = -np.inf
+        for r in range(batch):
+            assert np.array_equal(got["tok"][r], O.topk_desc(logits[r].astype(np.float32), k))

@@ -1,0 +1,26 @@
+"""Head and projection in one round of tiles, at the edges: one row past a wave's fragments and all of the last, a last tile of
+one row of the vocabulary, all CUs busy, one group of K-steps and several; against the oracle, the projection through the second
+stage's states."""
+import pytest
+
+from paper_2404_19124_amd import binding as B
+from paper_2404_19124_amd import workloads as W
+from tests.gpu_common import run_workload
+
+pytestmark = pytest.mark.gpu
+
+# D, V, top_k, batch, rows of a block
+CASES = [(256, 33601, (1, 1), 129, 192), (256, 40640, (4, 1), 192, 192), (768, 32161, (2, 1), 193, 256), (512, 40001, (3, 1), 256, 256),
+         (256, 32513, (2, 1), 257, 320), (1024, 39801, (3, 1), 320, 320)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)).replace(" ", "") for c in CASES])
+def test_drafts(case):
+    D, V, top_k, batch, block = case
+    plan = B.spec_plan_panel(batch, D, V, top_k[0], D)
+    assert 400 <= plan["kernel"] < 1000 and plan["block_rows"] == block
+    wl = W.Workload("once", 64, D, V, 2, top_k, top_k[0], batch, "bf16", "f32", 0.6, seed=63, emb_std=0.3)
+    seqs = sorted({0, 1, 15, 16, 79, 80, batch // 2, batch - 17, batch - 16, batch - 1})
+    rep, step, od, ov = run_workload(wl, ln_affine="random", gen_device="cpu", sample_seqs=seqs, check_verify=False)
+    assert rep.rows_checked + rep.rows_skipped_below_exempt == len(seqs) * (1 + top_k[0])
+    assert rep.rows_exempt <= 1

@@ -10,6 +10,13 @@ from paper_2404_19124_amd import binding as B
 def check(rows, k, n_head, k_top, n_proj, n_cu):
     p = B.spec_plan_panel(rows, k, n_head, k_top, n_proj, n_cu)
     what = "rows=%d k=%d n_head=%d k_top=%d n_proj=%d n_cu=%d -> %s" % (rows, k, n_head, k_top, n_proj, n_cu, p)
+    if 400 <= p["kernel"] < 1000:   # one round of tiles of both matrices, all state rows in a block
+        mb, kt = divmod(p["kernel"] - 400, 10)
+        assert mb in (3, 4, 5) and kt in (2, 3, 4) and kt >= k_top and n_proj > 0 and k % 256 == 0, what
+        assert p["block_rows"] == 64 * mb >= rows > 128 and p["row_blocks"] == 1, what
+        assert p["tiles"] == -(-n_head // 160) + -(-n_proj // 160) == p["workgroups"] <= n_cu, what
+        assert p["parts"] == -(-n_head // 160) and 0 < p["lds_bytes"] <= 160 * 1024, what
+        return p
     if not 300 <= p["kernel"] < 1000:
         assert p == B.spec_plan_contraction(rows, k, n_head, k_top, n_proj, n_cu), what
         return p
@@ -27,13 +34,18 @@ def check(rows, k, n_head, k_top, n_proj, n_cu):
 
 def test_invariants_over_random_shapes():
     rnd = random.Random(20241204)
-    taken = 0
+    taken = once = 0
+    for _ in range(500):   # around one round of tiles of both matrices
+        n_cu = rnd.choice([256, 304, 40])
+        k = 64 * rnd.randint(1, 64)
+        p = check(rnd.randint(100, 330), k, rnd.randint(120, 170) * n_cu - rnd.choice([k, 64]), rnd.randint(1, 5), rnd.choice([k, 64]), n_cu)
+        once += 400 <= p["kernel"] < 1000
     for _ in range(4000):
         n_head = rnd.choice([rnd.randint(1, 3000), rnd.randint(3000, 200000)])
-        p = check(rnd.choice([rnd.randint(1, 200), rnd.randint(17, 128)]), 64 * rnd.randint(1, 128), n_head, rnd.randint(1, 8),
+        p = check(rnd.choice([rnd.randint(1, 400), rnd.randint(17, 128)]), 64 * rnd.randint(1, 128), n_head, rnd.randint(1, 8),
                   rnd.choice([0, 64 * rnd.randint(1, 128)]), rnd.choice([256, 256, 304, 128, 40, 7]))
-        taken += 300 <= p["kernel"] < 1000
-    assert taken > 200
+        taken += 300 <= p["kernel"] < 400
+    assert taken > 200 and once > 10
 
 
 # the lines of the rule, and launches whose times it rests on: state fragments, or 0 where another kernel stays
@@ -45,7 +57,17 @@ def test_invariants_over_random_shapes():
                                         ((65, 4096, 2000, 2, 0), 5), ((64, 4096, 36864, 2, 0), 4), ((64, 4096, 36865, 2, 0), 0)])
 def test_who_takes_which_launch(args, block):
     p = check(*args, 256)
-    assert (p["block_rows"] // 16 if 300 <= p["kernel"] < 1000 else 0) == block
+    assert (p["block_rows"] // 16 if 300 <= p["kernel"] < 400 else 0) == block
+
+
+@pytest.mark.parametrize("args,block", [((320, 4096, 32000, 3, 4096), 320), ((321, 4096, 32000, 3, 4096), 0), ((129, 4096, 32000, 3, 4096), 192),
+                                        ((128, 4096, 32000, 3, 4096), 0), ((256, 4096, 28672, 3, 4096), 0), ((256, 4096, 28673, 3, 4096), 256),
+                                        ((200, 4096, 36800, 4, 4096), 256), ((200, 4096, 36801, 4, 4096), 0), ((200, 4096, 32000, 5, 4096), 0),
+                                        ((200, 4160, 32000, 3, 4160), 0), ((200, 4096, 32000, 3, 0), 0), ((192, 2048, 32000, 3, 2048), 192),
+                                        ((193, 2048, 32000, 3, 2048), 0)])
+def test_who_takes_one_round(args, block):
+    p = check(*args, 256)
+    assert (p["block_rows"] if 400 <= p["kernel"] < 1000 else 0) == block
 
 
 @pytest.mark.parametrize("args", [(0, 4096, 32000, 2, 0, 256), (64, 100, 32000, 2, 0, 256), (64, 4096, 32000, 9, 0, 256),
