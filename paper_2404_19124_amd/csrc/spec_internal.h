@@ -185,10 +185,6 @@ hipError_t launch_head_once(const HeadJob& job, const OncePlan& plan, hipStream_
 // ---- contraction, float32 ----------------------------------------------------
 // out[r * ldo + v] = sum_k a[r * K + k] * w[v * K + k]
 hipError_t launch_store_f32(const float* a, const float* w, float* out, int64_t ldo, int R, int N, int K, hipStream_t st);
-// head: at most max_parts partials per row (*nparts of them); n_proj > 0: the next projection in the same launch,
-// out_proj [R][n_proj]
-hipError_t launch_head_f32(const float* a, const float* w_head, int n_head, int k_top, Partials part, int max_parts,
-                           const float* w_proj, int n_proj, float* out_proj, int R, int K, int* nparts, hipStream_t st);
 // logp[r][v] = logits[r][v] - logsumexp(logits[r])   (in place allowed)
 hipError_t launch_row_log_softmax(const float* logits, float* logp, int64_t ld, int R, int V, hipStream_t st);
 
@@ -226,6 +222,14 @@ struct StageJob {
   const int32_t* row_rank;
 };
 hipError_t launch_stage(const StageJob& job, hipStream_t st);
+
+// ---- float32: head, at most max_parts partials per row (*nparts of them); n_proj > 0: the next projection in the same launch,
+// out_proj [R][n_proj].  fold: the states are not read from `a`, every workgroup computes the stage's rows itself.
+hipError_t launch_head_f32(const float* a, const float* w_head, int n_head, int k_top, Partials part, int max_parts,
+                           const float* w_proj, int n_proj, float* out_proj, int R, int K, int* nparts, hipStream_t st,
+                           const StageJob* fold = nullptr);
+// whether that may be asked of a stage whose parents' heads left nparts partials; half: (row, part) slots of one head
+bool f32_fold_fits(int R, int D, int V, int nparts, int max_parts, int64_t half);
 
 // ---- per-sequence trees: n words of `maps` (pinned host memory, device address) to dev, the `batch` words behind them
 // to n_cand

@@ -679,6 +679,19 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
     }
   }
 
+  // Partial results of head i.  A float32 stage computed inside head i's launch reads those of head i - 1 there, so heads of few
+  // rows take turns with the halves of the buffer.
+  const int64_t half = ws.part_rows_parts / 2;
+  auto part_of = [&](int i) {
+    Partials q = ws.part;
+    if (!m->bf16 && (i & 1) && R[i] <= 16) {
+      q.m += half;
+      q.s += half;
+      q.val += half * kMaxTopK;
+      q.idx += half * kMaxTopK;
+    }
+    return q;
+  };
   auto stage_job = [&](int i, int nparts) {
     StageJob sj;
     memset(&sj, 0, sizeof(sj));
@@ -688,7 +701,7 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
     sj.xcd_rows = (m->bf16 && R[i] > 16) ? 1 : 0;   // more than one tile of packed states
     sj.D = D;
     sj.bf16 = m->bf16 ? 1 : 0;
-    sj.part = ws.part;
+    sj.part = part_of(i > 0 ? i - 1 : 0);
     sj.nparts = nparts;
     sj.V = V;
     if (i > 0) {
@@ -730,7 +743,7 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
       tj.row_off[i] = row_off[i];
     }
     for (int i = n; i < kMaxStages; ++i) tj.top_k[i] = 1;
-    tj.part = ws.part;
+    tj.part = part_of(n - 1);
     tj.nparts = nparts;
     tj.rows_last = (int)R[n - 1];
     tj.tok = ws.tok;
@@ -774,9 +787,10 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
         fold.tok = last_tok;
         fold.emb = sj.emb; fold.gamma = sj.gamma; fold.beta = sj.beta;
         fold.w_s = sj.w_s; fold.w_e = sj.w_e; fold.eps = sj.eps;
-      } else {
-        HIP_TRY(launch_stage(sj, st));
       }
+      const int max_parts = m->n_cu > 0 ? m->n_cu : 256;
+      const bool folded_f32 = !m->bf16 && !dbg && f32_fold_fits((int)R[i], D, V, i > 0 ? nparts : 1, max_parts, half);
+      if (!folded && !folded_f32) HIP_TRY(launch_stage(sj, st));
       const int proj_next = i + 1 < n ? i + 1 : -1;
       if (m->bf16 && proj_next >= 0 && !skinny_fits((int)R[i], D / 32) &&
           !plan_panel((int)R[i], top_k[i], V, D, D / 32, m->n_cu).block &&
@@ -797,9 +811,9 @@ static spec_status_t draft_impl(spec_model_t* m, const Workspace& ws, const void
         if (s != SPEC_OK) return s;
       } else {
         HIP_TRY(launch_head_f32(static_cast<const float*>(ws.states), static_cast<const float*>(m->head[i]), V, top_k[i],
-                                ws.part, m->n_cu > 0 ? m->n_cu : 256,
-                                proj_next >= 0 ? static_cast<const float*>(m->proj[proj_next]) : nullptr,
-                                proj_next >= 0 ? D : 0, ws.pz[(i + 1) & 1], (int)R[i], D, &nparts, st));
+                                part_of(i), max_parts, proj_next >= 0 ? static_cast<const float*>(m->proj[proj_next]) : nullptr,
+                                proj_next >= 0 ? D : 0, ws.pz[(i + 1) & 1], (int)R[i], D, &nparts, st,
+                                folded_f32 ? &sj : nullptr));
       }
     }
     HIP_TRY(launch_tree(tree_job(nparts), st));

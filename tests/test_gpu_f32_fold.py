@@ -1,0 +1,55 @@
+"""float32 stages computed inside the head's launch (a call with debug outputs does not) are the stage kernel's, bit for bit: on
+both sides of 16 rows, one and two chunks per lane and one too many, 64 parts and one more, with trees per sequence as well."""
+import math
+
+import pytest
+import torch
+
+from paper_2404_19124_amd import binding as B
+from paper_2404_19124_amd import workloads as W
+from paper_2404_19124_amd.runner import Step
+
+pytestmark = pytest.mark.gpu
+
+# E, D, V, tree, batch
+CASES = [(8, 8, 9, (8, 2), 1), (33, 264, 700, (4, 4, 1), 1), (64, 512, 4096, (1, 1, 1), 16), (64, 520, 4097, (2, 1, 2), 8),
+         (64, 1024, 1000, (5, 3, 2), 1), (64, 1032, 300, (2, 2), 3), (64, 256, 2000, (6, 1, 1, 1), 3), (130, 72, 65, (7, 1), 2)]
+
+
+def _steps(case, seed=19):
+    E, D, V, tree, batch = case
+    wl = W.Workload("fold32", E, D, V, len(tree), tree, min(2, math.prod(tree)), batch, "f32", "f32", 0.5, seed=seed,
+                    emb_std=1.0)
+    gen = W.make_generator(seed, "cuda")
+    w = W.make_speculator(wl, gen, device="cuda", ln_affine="random")
+    return wl, [Step(wl, w, debug=debug) for debug in (True, False)], gen
+
+
+@pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)).replace(" ", "") for c in CASES])
+def test_with_and_without_debug_outputs(case):
+    wl, steps, gen = _steps(case)
+    for _ in range(4):   # (each pass finds what the one before left in the workspace)
+        state, last = W.make_draft_inputs(wl, gen, device="cuda")
+        for step in steps:
+            step.draft(state, last)
+        torch.cuda.synchronize()
+        for what in ("cand_tokens", "cand_leaf", "cand_scores"):
+            assert torch.equal(getattr(steps[0], what), getattr(steps[1], what)), what
+    for step in steps:
+        step.close()
+
+
+def test_trees_per_sequence():
+    wl, steps, gen = _steps((64, 256, 1500, (4, 2, 2), 6))
+    trees, counts = [[4, 2, 2], [1, 1, 1], [1, 1, 1], [3, 1, 2], [2, 2, 1], [1, 1, 1]], [8, 0, 1, 6, 4, 1]
+    state, last = W.make_draft_inputs(wl, gen, device="cuda")
+    got = []
+    for step in steps:
+        out = [torch.zeros((6, 8, 3), dtype=torch.int32, device="cuda"), torch.zeros((6, 8), device="cuda"),
+               torch.zeros((6, 8), dtype=torch.int32, device="cuda"), torch.zeros((6,), dtype=torch.int32, device="cuda")]
+        B.spec_draft_dynamic(step.model, state, last, trees, counts, *out, dbg=step.dbg)
+        torch.cuda.synchronize()
+        got.append(out)
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    for step in steps:
+        step.close()
