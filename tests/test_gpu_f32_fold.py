@@ -43,11 +43,13 @@ def test_trees_per_sequence():
     wl, steps, gen = _steps((64, 256, 1500, (4, 2, 2), 6))
     trees, counts = [[4, 2, 2], [1, 1, 1], [1, 1, 1], [3, 1, 2], [2, 2, 1], [1, 1, 1]], [8, 0, 1, 6, 4, 1]
     state, last = W.make_draft_inputs(wl, gen, device="cuda")
+    rows, kw, _ = B.dynamic_rows(trees, counts)
+    lse = torch.zeros((sum(rows),), device="cuda")
     got = []
-    for step in steps:
+    for step, dbg in zip(steps, ({"row_lse": lse}, None)):
         out = [torch.zeros((6, 8, 3), dtype=torch.int32, device="cuda"), torch.zeros((6, 8), device="cuda"),
                torch.zeros((6, 8), dtype=torch.int32, device="cuda"), torch.zeros((6,), dtype=torch.int32, device="cuda")]
-        B.spec_draft_dynamic(step.model, state, last, trees, counts, *out, dbg=step.dbg)
+        B.spec_draft_dynamic(step.model, state, last, trees, counts, *out, dbg=dbg)
         torch.cuda.synchronize()
         got.append(out)
     assert all(torch.equal(a, b) for a, b in zip(*got))
