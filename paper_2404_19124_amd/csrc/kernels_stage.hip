@@ -102,18 +102,25 @@ hipError_t launch_stage(const StageJob& job, hipStream_t st) {
 
 // Row maps of a call with per-sequence trees: a few KB straight from pinned host memory, every word requested at
 // once (one trip over PCIe), and the candidate counts to the caller's array.  Two copies by the runtime in its place
-// delayed the draft's first kernel by 15 us.
-__global__ __launch_bounds__(256) void fetch_maps_kernel(const int32_t* __restrict__ maps, int32_t* __restrict__ dev,
-                                                         int n, int32_t* __restrict__ n_cand, int batch) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= n + batch) return;
-  const int32_t v = maps[i];
-  if (i < n) dev[i] = v;
-  else n_cand[i - n] = v;
+// delayed the draft's first kernel by 15 us.  A workgroup that has read its words says so in pinned memory (`read`, one word
+// each): an event behind the launch, or its own, made the draft's first kernel wait 6 or 5 us for its release to the host.
+__global__ __launch_bounds__(kFetchWords) void fetch_maps_kernel(const int32_t* __restrict__ maps, int32_t* __restrict__ dev,
+                                                                 int n, int32_t* __restrict__ n_cand, int batch, uint32_t* read,
+                                                                 uint32_t ticket) {
+  const int i = blockIdx.x * kFetchWords + threadIdx.x;
+  if (i < n + batch) {
+    const int32_t v = maps[i];
+    if (i < n) dev[i] = v;
+    else n_cand[i - n] = v;
+  }
+  __syncthreads();   // (a word has arrived where it has been stored)
+  if (threadIdx.x == 0) __hip_atomic_store(read + blockIdx.x, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, hipStream_t st) {
-  hipLaunchKernelGGL(fetch_maps_kernel, dim3((n + batch + 255) / 256), dim3(256), 0, st, maps, dev, n, n_cand, batch);
+hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, uint32_t* read,
+                             uint32_t ticket, hipStream_t st) {
+  hipLaunchKernelGGL(fetch_maps_kernel, dim3(fetch_groups(n + batch)), dim3(kFetchWords), 0, st, maps, dev, n, n_cand, batch, read,
+                     ticket);
   return hipGetLastError();
 }
 

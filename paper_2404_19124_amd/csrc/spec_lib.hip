@@ -5,12 +5,14 @@
 
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "spec_internal.h"
@@ -73,14 +75,16 @@ struct spec_model {
   Workspace ws;
   // per-sequence trees (spec_draft_dynamic): row maps and sequence descriptors are built on the host in
   // one of kDynSlots pinned buffers and fetched into dyn_dev on the caller's stream; a slot is reused only
-  // after the event recorded behind the fetch has completed
+  // after every workgroup of the fetch has said that it has read its words: behind the dyn_ints words of a slot stands
+  // one word per workgroup, the ticket of the call it last read
   static constexpr int kDynSlots = 4;
   int64_t dyn_ints = 0;
   int32_t* dyn_dev = nullptr;
   int32_t* dyn_host[kDynSlots] = {};
   int32_t* dyn_host_dev[kDynSlots] = {};   // the same memory as the device addresses it
-  hipEvent_t dyn_ev[kDynSlots] = {};
-  bool dyn_busy[kDynSlots] = {};
+  int dyn_groups[kDynSlots] = {};          // workgroups of the slot's last fetch, 0: none yet
+  uint32_t dyn_ticket[kDynSlots] = {};     // and its ticket
+  uint32_t dyn_calls = 0;
   int dyn_next = 0;
   std::vector<void*> owned;
   // live timing of contraction launches
@@ -97,7 +101,6 @@ static void free_model(spec_model* m) {
     if (p) (void)hipFree(p);
   for (int q = 0; q < spec_model::kDynSlots; ++q) {
     if (m->dyn_host[q]) (void)hipHostFree(m->dyn_host[q]);
-    if (m->dyn_ev[q]) (void)hipEventDestroy(m->dyn_ev[q]);
   }
   delete m;
 }
@@ -328,10 +331,11 @@ extern "C" spec_status_t spec_create(const spec_config_t* cfg, const spec_weight
   for (int q = 0; q < spec_model::kDynSlots; ++q) {
     // coherent: a kernel reads the slot, and what an earlier call's kernel left of it in a cache must not be found there
     // (without the flag that is the environment's choice)
-    HIP_TRY_FREE(hipHostMalloc(reinterpret_cast<void**>(&m->dyn_host[q]), (size_t)m->dyn_ints * 4,
+    HIP_TRY_FREE(hipHostMalloc(reinterpret_cast<void**>(&m->dyn_host[q]),
+                               (size_t)(m->dyn_ints + fetch_groups(m->dyn_ints)) * 4,
                                hipHostMallocMapped | hipHostMallocCoherent));
     HIP_TRY_FREE(hipHostGetDevicePointer(reinterpret_cast<void**>(&m->dyn_host_dev[q]), m->dyn_host[q], 0));
-    HIP_TRY_FREE(hipEventCreateWithFlags(&m->dyn_ev[q], hipEventDisableTiming));
+    memset(m->dyn_host[q] + m->dyn_ints, 0, (size_t)fetch_groups(m->dyn_ints) * 4);
   }
 
   HIP_TRY_FREE(hipStreamSynchronize(stream));
@@ -837,6 +841,25 @@ extern "C" spec_status_t spec_draft(spec_model_t* m, const void* state, const in
                     hip_stream);
 }
 
+// The slot's last fetch has read it.  Usually long so (four calls ago); a caller that runs further ahead waits here, and after a
+// second the device is asked whether anything is wrong with it.
+static spec_status_t wait_until_read(spec_model* m, int slot) {
+  const uint32_t* read = reinterpret_cast<const uint32_t*>(m->dyn_host[slot] + m->dyn_ints);
+  auto all = [&]() {
+    for (int g = 0; g < m->dyn_groups[slot]; ++g)
+      if (__atomic_load_n(read + g, __ATOMIC_ACQUIRE) != m->dyn_ticket[slot]) return false;
+    return true;
+  };
+  for (int tries = 0; !all(); ++tries) {
+    if (tries < 1000) continue;
+    std::this_thread::sleep_for(std::chrono::microseconds(10));
+    if (tries < 1000 + 20000) continue;
+    HIP_TRY(hipDeviceSynchronize());
+    if (!all()) return fail(SPEC_EHIP, "the row maps of an earlier spec_draft_dynamic were never read");
+  }
+  return SPEC_OK;
+}
+
 // ---- spec_draft_dynamic: own tree and candidate count per sequence -------------------------------
 extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, const int32_t* last_tok, int32_t batch,
                                             const int32_t* top_k_seq, const int32_t* B_seq, int32_t B_pad,
@@ -879,7 +902,10 @@ extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, 
   // a free pinned slot (the fetch from it may still be pending on the caller's stream)
   const int slot = m->dyn_next;
   m->dyn_next = (slot + 1) % spec_model::kDynSlots;
-  if (m->dyn_busy[slot]) HIP_TRY(hipEventSynchronize(m->dyn_ev[slot]));
+  {
+    spec_status_t s = wait_until_read(m, slot);
+    if (s != SPEC_OK) return s;
+  }
   int32_t* h = m->dyn_host[slot];
   // layout: per stage parent[R_i], rank[R_i]; then the sequence descriptors; then B_seq (for n_cand)
   int64_t at = 0, p_at[kMaxStages], r_at[kMaxStages];
@@ -917,10 +943,12 @@ extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, 
   int32_t* hb = h + ints;
   if (ints + batch > m->dyn_ints) return fail(SPEC_ESHAPE, "internal: row maps exceed the model's buffer");
   for (int q = 0; q < batch; ++q) hb[q] = B_seq[q];
+  const uint32_t ticket = ++m->dyn_calls;
   // (one small kernel that reads the pinned slot: two copies by the runtime stood 15 us in front of the draft)
-  HIP_TRY(launch_fetch_maps(m->dyn_host_dev[slot], m->dyn_dev, (int)ints, n_cand, batch, st));
-  HIP_TRY(hipEventRecord(m->dyn_ev[slot], st));
-  m->dyn_busy[slot] = true;
+  HIP_TRY(launch_fetch_maps(m->dyn_host_dev[slot], m->dyn_dev, (int)ints, n_cand, batch,
+                            reinterpret_cast<uint32_t*>(m->dyn_host_dev[slot] + m->dyn_ints), ticket, st));
+  m->dyn_groups[slot] = fetch_groups(ints + batch);
+  m->dyn_ticket[slot] = ticket;
   for (int i = 0; i < n; ++i) {
     dp.kw[i] = kw[i];
     dp.parent[i] = m->dyn_dev + p_at[i];
