@@ -114,7 +114,7 @@ __global__ __launch_bounds__(kFetchWords) void fetch_maps_kernel(const int32_t* 
     else n_cand[i - n] = v;
   }
   __syncthreads();   // (a word has arrived where it has been stored)
-  if (threadIdx.x == 0) __hip_atomic_store(read + blockIdx.x, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (read && threadIdx.x == 0) __hip_atomic_store(read + blockIdx.x, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, uint32_t* read,

@@ -944,10 +944,18 @@ extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, 
   if (ints + batch > m->dyn_ints) return fail(SPEC_ESHAPE, "internal: row maps exceed the model's buffer");
   for (int q = 0; q < batch; ++q) hb[q] = B_seq[q];
   const uint32_t ticket = ++m->dyn_calls;
+  // A call that is being captured reports nothing: it runs at no time or many times, and a later call must neither wait for it
+  // nor find its ticket over its own.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) {   // (the legacy stream beside a capture: the launch says so)
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusNone;
+  }
+  const bool reports = capture == hipStreamCaptureStatusNone;
   // (one small kernel that reads the pinned slot: two copies by the runtime stood 15 us in front of the draft)
   HIP_TRY(launch_fetch_maps(m->dyn_host_dev[slot], m->dyn_dev, (int)ints, n_cand, batch,
-                            reinterpret_cast<uint32_t*>(m->dyn_host_dev[slot] + m->dyn_ints), ticket, st));
-  m->dyn_groups[slot] = fetch_groups(ints + batch);
+                            reports ? reinterpret_cast<uint32_t*>(m->dyn_host_dev[slot] + m->dyn_ints) : nullptr, ticket, st));
+  m->dyn_groups[slot] = reports ? fetch_groups(ints + batch) : 0;
   m->dyn_ticket[slot] = ticket;
   for (int i = 0; i < n; ++i) {
     dp.kw[i] = kw[i];

@@ -35,3 +35,43 @@ def test_a_caller_that_runs_ahead(batch):
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, want))
     step.close()
+
+
+def test_a_captured_call_is_waited_for_by_nobody():
+    """Eager calls between the replays of a captured one, and after a capture that was never replayed, are their own."""
+    wl = W.Workload("captured", 64, 64, 300, 2, (3, 2), 4, 3, "bf16", "f32", 0.6, seed=61, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    state, last = (t.cuda() for t in W.make_draft_inputs(wl, gen))
+    step = Step(wl, {k: [t.cuda() for t in v] for k, v in w.items()}, max_batch=3, max_top_k=wl.top_k)
+    calls = [([[3, 2], [1, 1], [2, 1]], [4, 0, 2]), ([[1, 2], [3, 2], [2, 2]], [1, 4, 3]), ([[1, 1], [1, 1], [3, 1]], [1, 1, 0])]
+    i32 = dict(dtype=torch.int32, device="cuda")
+
+    def buffers():
+        return [torch.empty((3, 4, 2), **i32), torch.empty((3, 4), device="cuda"), torch.empty((3, 4), **i32),
+                torch.empty((3,), **i32)]
+
+    def run(call, out, stream=None):
+        B.spec_draft_dynamic(step.model, state, last, *call, *out, stream=stream)
+        return out
+
+    want = [run(c, buffers()) for c in calls]
+    torch.cuda.synchronize()
+    captured, eager = buffers(), buffers()
+    for replays in (3, 0):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run(calls[0], captured)
+        for rep in range(replays):   # (the graph reads the slot it was captured with: three more calls have others)
+            for t in captured:
+                t.fill_(-7)
+            graph.replay()
+            run(calls[1 + rep % 2], eager)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(captured, want[0])), rep
+            assert all(torch.equal(a, b) for a, b in zip(eager, want[1 + rep % 2])), rep
+        for n in range(9):
+            run(calls[n % 3], eager)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(eager, want[n % 3])), (replays, n)
+    step.close()
