@@ -44,7 +44,8 @@ def kernel_name(kid: int) -> str:
         mb, rest = divmod(kid - 1000, 100)
         return "head_gemm32_kernel<%d, 2, %d, %s>" % (mb, rest // 2, "true" if rest % 2 else "false")
     if kid >= 400:
-        return "head_once_kernel<%d, %d>" % divmod(kid - 400, 10)
+        nb, rest = (4, kid - 500) if kid >= 500 else (5, kid - 400)
+        return "head_once_kernel<%d, %d, %d>" % ((nb,) + divmod(rest, 10))
     if kid >= 300:
         return "head_panel_kernel<%d, %d>" % divmod(kid - 300, 10)
     if kid >= 100:

@@ -225,7 +225,8 @@ spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const void* states,
  *           100 + 20 * MB + KT = tile kernel of many rows, head_tile_kernel<MB,KT> (a head without a projection;
  *           64 * MB-row blocks, per-lane top-k lists of KT entries),
  *           300 + 10 * MF + KT = panel kernel of some dozens of rows, head_panel_kernel<MF,KT> (16 * MF state rows, lists of KT),
- *           400 + 10 * MB + KT = head_once_kernel<MB,KT> (a head with a projection, 64 * MB state rows, one tile per CU),
+ *           400 + 10 * MB + KT = head_once_kernel<5,MB,KT> (64 * MB state rows, one tile of 160 weight rows per CU),
+ *           500 + 10 * MB + KT = head_once_kernel<4,MB,KT> (the same with tiles of 128 weight rows),
  *           1000 + 100 * MB + 2 * KT + VT = wide dense kernel head_gemm32_kernel<MB,2,KT,VT>
  *           (32 * MB-row state blocks, per-lane top-k lists of KT entries, VT = 1 with short tiles)
  *   rows, weight_rows, k: the contraction is [rows, k] x [weight_rows, k]^T

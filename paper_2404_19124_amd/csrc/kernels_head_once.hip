@@ -1,5 +1,5 @@
-// Vocabulary head and the next stage's projection in one launch against 129 to 320 state rows, where every CU has at most one tile
-// of weight rows: the middle stages of a batched draft (320 rows of 64 sequences with a 5/3/2 tree).
+// Vocabulary head, alone or with the next stage's projection, against 129 to 320 state rows, where every CU has at most one tile
+// of weight rows: the middle stages of a batched draft (320 rows of 64 sequences with a 5/3/2 tree), the last of a small batch.
 //
 // The two were two launches (head alone, one round of tiles; projection split along K, its four partial sums added by the stage
 // kernel) or one whose tile list was a little longer than a round.  160 weight rows to a tile put both into one round of a
@@ -8,8 +8,9 @@
 // asked for (averages of the counters in these launches: 87 to 92, 640 to 950 cycles each), so a line from HBM costs a CU about
 // 700 / 90 cycles and one from L2 300 / 90, and the two add up: copies of the states alone take 42 us of the launch below, of the
 // weights alone 55, of both 95, with the matrix work 103, which alone would take 55.
-//  * Workgroup = 8 waves; tile = 160 weight rows x 64 * MB state rows, a wave 80 x 16 * MB of it (MB = 5: 100 accumulators of
-//    v_mfma_f32_16x16x32_bf16, two sets of fragments beside them).
+//  * Workgroup = 8 waves; tile = 160 (NB = 5) weight rows x 64 * MB state rows, a wave 80 x 16 * MB of it (MB = 5: 100 accumulators
+//    of v_mfma_f32_16x16x32_bf16, two sets of fragments beside them).  Tiles of 128 weight rows (NB = 4) where they too are one
+//    round: a launch lasts as long as a tile, and 32000 rows are 200 tiles of 160 for 256 CUs.
 //  * Both operands are copied straight into LDS (buffer loads to LDS), the weights eight K-steps ahead, the states four, by
 //    different waves: a wave's copies land in order, and a wait for its states would be one for its youngest weights.
 //    One barrier per K-step; LDS reads and copies are issued one by one between the matrix instructions.
@@ -29,7 +30,6 @@ constexpr int kOnceWM = 4;
 constexpr int kOnceCopyW = 2;      // waves that copy weights; the others copy states
 constexpr int kOnceDW = 8;         // K-steps (of 32) of weights in LDS
 constexpr int kOnceDS = 4;         // and of states
-constexpr int kOnceNB = 5;         // 16-row weight fragments of a wave
 constexpr int kOnceLds = 160 * 1024;
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
@@ -48,10 +48,10 @@ struct OnceArgs {
   Partials part;
 };
 
-// MB = state fragments of a wave.
-template <int MB>
+// NB = 16-row weight fragments of a wave, MB = its state fragments.
+template <int NB, int MB>
 struct OnceGeo {
-  static constexpr int NB = kOnceNB, WF = 2 * NB, SF = kOnceWM * MB;       // fragments of a K-step
+  static constexpr int WF = 2 * NB, SF = kOnceWM * MB;       // fragments of a K-step
   static constexpr int W_STEP = WF * 1024, S_STEP = SF * 1024;
   static constexpr int WC = WF / kOnceCopyW;                 // copies of a wave per step
   static constexpr int SC = (SF + kOnceWaves - kOnceCopyW - 1) / (kOnceWaves - kOnceCopyW);
@@ -84,13 +84,12 @@ __device__ __forceinline__ void once_barrier() {
 // only for this wave's copies into that one, which the counted wait in front of the barrier has already seen land, and not for
 // every copy in flight.  The other ring, which this wave only reads, goes by the plain pointer: what it holds changes behind
 // every barrier.
-template <int MB, int KT, bool WEIGHTS>
+template <int NB, int MB, int KT, bool WEIGHTS>
 __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_byte* __restrict c0, lds_byte* __restrict c1,
                                           lds_byte* __restrict c2, lds_byte* __restrict c3, lds_byte* __restrict c4,
                                           lds_byte* __restrict c5, lds_byte* __restrict c6, lds_byte* __restrict c7,
                                           unsigned char* smem) {
-  using G = OnceGeo<MB>;
-  constexpr int NB = G::NB;
+  using G = OnceGeo<NB, MB>;
   static_assert(kOnceDW == 8 && kOnceDS == 4, "the slots");
   lds_byte* const mine[8] = {c0, c1, c2, c3, c4, c5, c6, c7};   // (four of them for the states)
   constexpr int C = WEIGHTS ? G::WC : G::SC, DEPTH = WEIGHTS ? kOnceDW : kOnceDS;
@@ -325,63 +324,77 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
   }
 }
 
-template <int MB, int KT>
+template <int NB, int MB, int KT>
 __global__ __launch_bounds__(kOnceWaves * 64) void head_once_kernel(OnceArgs p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  using G = OnceGeo<MB>;
+  using G = OnceGeo<NB, MB>;
   lds_byte* const l = (lds_byte*)smem;
   lds_byte* const s = l + G::S_AT;
   if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < kOnceCopyW)
-    once_tile<MB, KT, true>(p, l, l, l + G::W_STEP, l + 2 * G::W_STEP, l + 3 * G::W_STEP, l + 4 * G::W_STEP, l + 5 * G::W_STEP,
+    once_tile<NB, MB, KT, true>(p, l, l, l + G::W_STEP, l + 2 * G::W_STEP, l + 3 * G::W_STEP, l + 4 * G::W_STEP, l + 5 * G::W_STEP,
                                 l + 6 * G::W_STEP, l + 7 * G::W_STEP, smem);
   else
-    once_tile<MB, KT, false>(p, l, s, s + G::S_STEP, s + 2 * G::S_STEP, s + 3 * G::S_STEP, nullptr, nullptr, nullptr, nullptr,
+    once_tile<NB, MB, KT, false>(p, l, s, s + G::S_STEP, s + 2 * G::S_STEP, s + 3 * G::S_STEP, nullptr, nullptr, nullptr, nullptr,
                                  smem);
 }
 
-static constexpr size_t once_lds(int mb, int kt) {
-  const size_t rings = (size_t)kOnceDW * 2 * kOnceNB * 1024 + (size_t)kOnceDS * kOnceWM * mb * 1024;
+static constexpr size_t once_lds(int nb, int mb, int kt) {
+  const size_t rings = (size_t)kOnceDW * 2 * nb * 1024 + (size_t)kOnceDS * kOnceWM * mb * 1024;
   return once_merge_bytes(mb, kt) > rings ? once_merge_bytes(mb, kt) : rings;
 }
 
-template <int MB, int KT>
+template <int NB, int MB, int KT>
 static hipError_t launch_once_t(const OnceArgs& a, int grid, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  constexpr size_t smem = once_lds(MB, KT);
-  static_assert(smem <= kOnceLds && smem >= (size_t)OnceGeo<MB>::BYTES, "a CU has no more");
+  constexpr size_t smem = once_lds(NB, MB, KT);
+  static_assert(smem <= kOnceLds && smem >= (size_t)OnceGeo<NB, MB>::BYTES, "a CU has no more");
   static bool attr_set = false;  // per instantiation
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_once_kernel<MB, KT>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(head_once_kernel<NB, MB, KT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipExtLaunchKernelGGL((head_once_kernel<MB, KT>), dim3(grid), dim3(kOnceWaves * 64), smem, st, ev_start, ev_stop, 0, a);
+  hipExtLaunchKernelGGL((head_once_kernel<NB, MB, KT>), dim3(grid), dim3(kOnceWaves * 64), smem, st, ev_start, ev_stop, 0, a);
   return hipGetLastError();
 }
 
-// Which launches come here: a head with the next projection, lists of at most 4, K in whole groups of eight steps (the copies
-// move by groups; other widths stay with the dense kernels), more than 128 weight rows of the two per CU and all tiles in one
-// round.  Drafts of two stages of top-1 against 130, 192, 256, 320 rows, the kernels there were before / this one, us ratio:
-// 28000 + 6144 rows 1.11, 1.11, 1.09, 1.04;  32000 + 1024 1.06, 1.06, 1.05, 1.03;  + 3072 1.20, 1.21, 1.16, 1.08;  + 4096 1.15,
-// 1.19, 1.09, 1.05;  + 6144 1.11, 1.15, 1.06, 1.06;  + 2048 1.02, 1.01, 0.96, 0.96, hence the line at 192 rows for K = 2048.  384 rows 0.98
-// to 1.08.  Up to 128 rows per CU the head alone and the projection behind it are as fast or faster (28000 + 4096 1.11, 1.06,
-// 0.98, 0.94;  20000 + 4096 0.97 to 0.89), and so is a head without a projection on the tile kernel (32000: 0.98, 0.94, 0.88, 0.90).
+// Which launches come here: lists of at most 4, K in whole groups of eight steps (the copies move by groups; other widths stay
+// with the dense kernels), all tiles in one round.  Tiles of 128 weight rows where that is one round, else of 160.  Drafts of
+// one stage of top-2 (a head alone) and of two of top-1, weights of 800 MB in turn so that none stay in the memory-side cache,
+// the kernels there were before / this one, times as fast against 130, 192, 256, 320 rows:
+//  * 160-row tiles, head alone: 38000 x 1024 1.18, 1.14, 1.21, 1.17;  x 2048 1.15, 1.17, 1.17, 1.13;  x 3072 1.19, 1.21, 1.28, 1.21;
+//    40000 x 4096 1.19, 1.24, 1.22, 1.18;  x 8192 1.11, 1.21, 1.15, 1.17.  With the projection, its launches by difference: 32000 +
+//    1024 31 / 25, 39 / 28, 42 / 30, 44 / 36 us;  + 2048 45 / 40, 61 / 47, 64 / 54, 66 / 59;  + 3072 63 / 54, 82 / 59, 85 / 67, 92 / 74.
+//  * 128-row tiles, head alone: 32000 x 1024 1.04, 1.03, 1.02, 0.99;  x 2048 1.14, 1.09, 1.02, 0.98;  x 4096 1.18, 1.12, 1.02, 0.96;
+//    x 6144 1.15, 1.07, 1.00, 0.97;  28000 x 4096 1.13, 1.08, 1.00, 0.96;  24000 1.05, 1.03, 0.97, 0.95;  20000 1.02, 1.01, 0.93,
+//    0.88: up to 192 rows from 96 weight rows per CU on, up to 256 from 120.
+//  * 128-row tiles with the projection, by difference: 28000 + 4096 76 / 63, 74 / 67, 84 / 78, 93 / 91 us;  20000 + 4096 63 / 59, 68 /
+//    65, 77 / 74, 87 / 87;  18000 + 6144 89 / 80, 93 / 82, 106 / 96, 123 / 119;  28000 + 2048 39 / 35, 45 / 44, 48 / 49, 51 / 55;  18000 +
+//    8192 112 / 107, 132 / 129, 142 / 146, 159 / 163: up to 192 rows, up to 256 for K = 3072 to 6144, from 84 weight rows per CU on.
 OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   OncePlan pl;
   memset(&pl, 0, sizeof(pl));
   const int64_t cus = n_cu > 0 ? n_cu : 256;
-  if (R <= 128 || R > (kt == 64 ? 192 : 320) || n_head <= 0 || n_proj <= 0 || k_top < 1 || k_top > 4 || kt % kOnceDW) return pl;
-  constexpr int kRows = 32 * kOnceNB;
-  const int64_t head = ((int64_t)n_head + kRows - 1) / kRows, tiles = head + ((int64_t)n_proj + kRows - 1) / kRows;
-  if ((int64_t)n_head + n_proj <= 128 * cus || tiles > cus) return pl;
+  if (R <= 128 || R > 320 || n_head <= 0 || k_top < 1 || k_top > 4 || kt % kOnceDW) return pl;
+  auto head_tiles = [&](int nb) { return ((int64_t)n_head + 32 * nb - 1) / (32 * nb); };
+  auto all_tiles = [&](int nb) { return head_tiles(nb) + (n_proj > 0 ? ((int64_t)n_proj + 32 * nb - 1) / (32 * nb) : 0); };
+  const int nb = all_tiles(4) <= cus ? 4 : 5;
+  if (all_tiles(nb) > cus) return pl;
+  if (nb == 4) {
+    const int64_t weight_rows = (int64_t)n_head + (n_proj > 0 ? n_proj : 0);
+    if (n_proj > 0 ? R > (kt >= 96 && kt <= 192 ? 256 : 192) || weight_rows <= 84 * cus
+                   : R > 256 || weight_rows <= (R > 192 ? 120 : 96) * cus)
+      return pl;
+  }
+  pl.nb = nb;
   pl.block = (R + 63) / 64;
   pl.kcap = k_top < 2 ? 2 : k_top;
-  pl.n_head = (int)head;
-  pl.n_tiles = (int)tiles;
+  pl.n_head = (int)head_tiles(nb);
+  pl.n_tiles = (int)all_tiles(nb);
   return pl;
 }
 
-size_t once_lds_bytes(const OncePlan& pl) { return once_lds(pl.block, pl.kcap); }
+size_t once_lds_bytes(const OncePlan& pl) { return once_lds(pl.nb, pl.block, pl.kcap); }
 
 hipError_t launch_head_once(const HeadJob& job, const OncePlan& pl, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (job.vt_head <= 0 || job.out_head || job.b_rowmajor || job.kt % kOnceDW || job.kt < kOnceDW || job.k_top > pl.kcap ||
@@ -405,16 +418,13 @@ hipError_t launch_head_once(const HeadJob& job, const OncePlan& pl, hipStream_t 
   a.k_top = job.k_top;
   a.nparts = job.nparts;
   a.part = job.part;
-  switch (pl.block * 10 + pl.kcap) {
-    case 32: return launch_once_t<3, 2>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 33: return launch_once_t<3, 3>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 34: return launch_once_t<3, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 42: return launch_once_t<4, 2>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 43: return launch_once_t<4, 3>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 44: return launch_once_t<4, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 52: return launch_once_t<5, 2>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 53: return launch_once_t<5, 3>(a, pl.n_tiles, st, ev_start, ev_stop);
-    case 54: return launch_once_t<5, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
+  switch (pl.nb * 100 + pl.block * 10 + pl.kcap) {
+#define ONCE(NB_, MB_)                                                                             \
+  case (NB_) * 100 + (MB_) * 10 + 2: return launch_once_t<NB_, MB_, 2>(a, pl.n_tiles, st, ev_start, ev_stop); \
+  case (NB_) * 100 + (MB_) * 10 + 3: return launch_once_t<NB_, MB_, 3>(a, pl.n_tiles, st, ev_start, ev_stop); \
+  case (NB_) * 100 + (MB_) * 10 + 4: return launch_once_t<NB_, MB_, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
+    ONCE(4, 3) ONCE(4, 4) ONCE(4, 5) ONCE(5, 3) ONCE(5, 4) ONCE(5, 5)
+#undef ONCE
     default: return hipErrorInvalidValue;
   }
 }

@@ -174,6 +174,7 @@ hipError_t launch_head_panel(const HeadJob& job, const PanelPlan& plan, hipStrea
 
 // A head with the next projection against 129 to 320 rows, all of both in one round of 160-weight-row tiles x all state rows.
 struct OncePlan {
+  int nb;                    // 32-row units of a tile's weight rows
   int block, kcap;           // 64-row units of the state rows (0: not for this kernel), capacity of the per-lane top-k lists
   int n_head, n_tiles;       // workgroup tiles of the head (= parts per row), of both matrices
 };

@@ -479,6 +479,8 @@ extern "C" spec_status_t spec_plan_head(int32_t rows, int32_t k, int32_t n_head,
   return SPEC_OK;
 }
 
+static int once_id(const OncePlan& op) { return (op.nb == 4 ? 500 : 400) + 10 * op.block + op.kcap; }
+
 extern "C" spec_status_t spec_plan_panel(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_proj,
                                          int32_t n_cu, spec_plan_t* out) {
   spec_status_t s = spec_plan_contraction(rows, k, n_head, k_top, n_proj, n_cu, out);
@@ -487,9 +489,9 @@ extern "C" spec_status_t spec_plan_panel(int32_t rows, int32_t k, int32_t n_head
   const OncePlan op = plan_once(rows, k_top, n_head, n_proj, k / 32, n_cu);
   if (op.block) {
     memset(out, 0, sizeof(*out));
-    out->kernel = 400 + 10 * op.block + op.kcap;
+    out->kernel = once_id(op);
     out->block_rows = 64 * op.block;
-    out->tile_rows = 160;
+    out->tile_rows = 32 * op.nb;
     out->row_blocks = 1;
     out->ranges = out->tiles = out->workgroups = op.n_tiles;
     out->parts = op.n_head;
@@ -585,7 +587,7 @@ static spec_status_t run_contraction(spec_model* m, const Workspace& ws, int sta
       *nparts = job.nparts;
       if ((int64_t)R * job.nparts > ws.part_rows_parts)
         return fail(SPEC_ESHAPE, "internal: partial workspace too small (%d rows x %d parts)", R, job.nparts);
-      const int slot = prof_slot(m, 400 + 10 * op.block + op.kcap, R, job.n_head + job.n_proj, K);
+      const int slot = prof_slot(m, once_id(op), R, job.n_head + job.n_proj, K);
       HIP_TRY(launch_head_once(job, op, st, EV0(slot), EV1(slot)));
       return SPEC_OK;
     }

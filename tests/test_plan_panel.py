@@ -11,11 +11,12 @@ def check(rows, k, n_head, k_top, n_proj, n_cu):
     p = B.spec_plan_panel(rows, k, n_head, k_top, n_proj, n_cu)
     what = "rows=%d k=%d n_head=%d k_top=%d n_proj=%d n_cu=%d -> %s" % (rows, k, n_head, k_top, n_proj, n_cu, p)
     if 400 <= p["kernel"] < 1000:   # one round of tiles of both matrices, all state rows in a block
-        mb, kt = divmod(p["kernel"] - 400, 10)
-        assert mb in (3, 4, 5) and kt in (2, 3, 4) and kt >= k_top and n_proj > 0 and k % 256 == 0, what
-        assert p["block_rows"] == 64 * mb >= rows > 128 and p["row_blocks"] == 1, what
-        assert p["tiles"] == -(-n_head // 160) + -(-n_proj // 160) == p["workgroups"] <= n_cu, what
-        assert p["parts"] == -(-n_head // 160) and 0 < p["lds_bytes"] <= 160 * 1024, what
+        tile = 128 if p["kernel"] >= 500 else 160
+        mb, kt = divmod(p["kernel"] % 100, 10)
+        assert mb in (3, 4, 5) and kt in (2, 3, 4) and kt >= k_top and k % 256 == 0, what
+        assert p["block_rows"] == 64 * mb >= rows > 128 and p["row_blocks"] == 1 and p["tile_rows"] == tile, what
+        assert p["tiles"] == -(-n_head // tile) + -(-n_proj // tile) == p["workgroups"] <= n_cu, what
+        assert p["parts"] == -(-n_head // tile) and 0 < p["lds_bytes"] <= 160 * 1024, what
         return p
     if not 300 <= p["kernel"] < 1000:
         assert p == B.spec_plan_contraction(rows, k, n_head, k_top, n_proj, n_cu), what
@@ -38,7 +39,8 @@ def test_invariants_over_random_shapes():
     for _ in range(500):   # around one round of tiles of both matrices
         n_cu = rnd.choice([256, 304, 40])
         k = 64 * rnd.randint(1, 64)
-        p = check(rnd.randint(100, 330), k, rnd.randint(120, 170) * n_cu - rnd.choice([k, 64]), rnd.randint(1, 5), rnd.choice([k, 64]), n_cu)
+        p = check(rnd.randint(100, 330), k, max(1, rnd.randint(80, 170) * n_cu - rnd.choice([k, 64])), rnd.randint(1, 5),
+                  rnd.choice([k, 64, 0]), n_cu)
         once += 400 <= p["kernel"] < 1000
     for _ in range(4000):
         n_head = rnd.choice([rnd.randint(1, 3000), rnd.randint(3000, 200000)])
@@ -60,14 +62,23 @@ def test_who_takes_which_launch(args, block):
     assert (p["block_rows"] // 16 if 300 <= p["kernel"] < 400 else 0) == block
 
 
-@pytest.mark.parametrize("args,block", [((320, 4096, 32000, 3, 4096), 320), ((321, 4096, 32000, 3, 4096), 0), ((129, 4096, 32000, 3, 4096), 192),
-                                        ((128, 4096, 32000, 3, 4096), 0), ((256, 4096, 28672, 3, 4096), 0), ((256, 4096, 28673, 3, 4096), 256),
-                                        ((200, 4096, 36800, 4, 4096), 256), ((200, 4096, 36801, 4, 4096), 0), ((200, 4096, 32000, 5, 4096), 0),
-                                        ((200, 4160, 32000, 3, 4160), 0), ((200, 4096, 32000, 3, 0), 0), ((192, 2048, 32000, 3, 2048), 192),
-                                        ((193, 2048, 32000, 3, 2048), 0)])
+# the lines of the rule: (state rows of a block, weight rows of a tile), or None where another kernel stays
+@pytest.mark.parametrize("args,block", [((320, 4096, 32000, 3, 4096), (320, 160)), ((321, 4096, 32000, 3, 4096), None),
+                                        ((129, 4096, 32000, 3, 4096), (192, 160)), ((128, 4096, 32000, 3, 4096), None),
+                                        ((256, 4096, 28672, 3, 4096), (256, 128)), ((257, 4096, 28672, 3, 4096), None),
+                                        ((257, 4096, 28673, 3, 4096), (320, 160)), ((200, 4096, 36800, 4, 4096), (256, 160)),
+                                        ((200, 4096, 36801, 4, 4096), None), ((200, 4096, 32000, 5, 4096), None),
+                                        ((200, 4160, 32000, 3, 4160), None), ((320, 2048, 32000, 3, 2048), (320, 160)),
+                                        ((192, 2048, 30720, 3, 2048), (192, 128)), ((193, 2048, 30720, 3, 2048), None),
+                                        ((192, 8192, 18000, 3, 8192), (192, 128)), ((193, 8192, 18000, 3, 8192), None),
+                                        ((160, 4096, 17408, 2, 4096), None), ((160, 4096, 17409, 2, 4096), (192, 128)),
+                                        ((192, 4096, 24576, 3, 0), None), ((192, 4096, 24577, 3, 0), (192, 128)),
+                                        ((193, 4096, 30720, 3, 0), None), ((256, 4096, 30721, 3, 0), (256, 128)),
+                                        ((257, 4096, 32768, 3, 0), None), ((257, 4096, 32769, 3, 0), (320, 160)),
+                                        ((320, 4096, 40960, 3, 0), (320, 160)), ((320, 4096, 40961, 3, 0), None)])
 def test_who_takes_one_round(args, block):
     p = check(*args, 256)
-    assert (p["block_rows"] if 400 <= p["kernel"] < 1000 else 0) == block
+    assert ((p["block_rows"], p["tile_rows"]) if 400 <= p["kernel"] < 1000 else None) == block
 
 
 @pytest.mark.parametrize("args", [(0, 4096, 32000, 2, 0, 256), (64, 100, 32000, 2, 0, 256), (64, 4096, 32000, 9, 0, 256),
