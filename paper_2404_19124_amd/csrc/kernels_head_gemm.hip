@@ -174,8 +174,8 @@ double dense_head_cost(int R, int k_top, int n_head, int kt, int n_cu) {
 
 // Head and next projection in ONE launch share the state reads, but their tiles form one list, and a list
 // that is a little longer than a multiple of the ranges makes the launch one tile longer for a few ranges
-// (320 rows against 125 + 16 tiles: 128 ranges, 13 of them with two tiles).  Then two launches are cheaper:
-// the head alone in one even round, the projection alone split along K over the whole chip.
+// (768 rows against 501 + 12 tiles).  Then two launches are cheaper: the head alone in even rounds, the projection
+// alone split along K over the whole chip.  (What head_once_kernel takes, one round of both, does not come here.)
 // (The head alone is priced as the dense kernel's, also where the tile kernel would take it.)
 bool plan_projection_apart(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   if (R <= 64 || n_head <= 0 || n_proj <= 0) return false;   // wide kernel only

@@ -401,7 +401,7 @@ static hipError_t launch_tile_t(const TileArgs& a, size_t smem, hipStream_t st, 
   return hipGetLastError();
 }
 
-// Which head launches come here: alone (no projection), more than 64 rows, lists of at most 4, K in whole groups of kSteps
+// Which head launches come here, of those that the panel kernel and head_once_kernel leave: alone (no projection), more than 64 rows, lists of at most 4, K in whole groups of kSteps
 // steps (the cursor of the copies moves by groups; other widths stay with the dense kernel), and cheaper than the dense
 // kernel by its own estimate.  Both estimates count tile rounds of the longest range; the unit is the dense kernel's 96-row
 // tile, as in plan_gemm.  Launches of 4096 x 32000 (320, 384, 960 rows) and 3072 x 128256 (192, 768, 2304), us, dense kernel /

@@ -172,7 +172,8 @@ size_t panel_lds_bytes(const PanelPlan& plan);
 hipError_t launch_head_panel(const HeadJob& job, const PanelPlan& plan, hipStream_t st, hipEvent_t ev_start = nullptr,
                              hipEvent_t ev_stop = nullptr);
 
-// A head with the next projection against 129 to 320 rows, all of both in one round of 160-weight-row tiles x all state rows.
+// A head, alone or with the next projection, against 129 to 320 rows, all of both in one round of tiles of 160 or 128 weight rows
+// x all state rows.
 struct OncePlan {
   int nb;                    // 32-row units of a tile's weight rows
   int block, kcap;           // 64-row units of the state rows (0: not for this kernel), capacity of the per-lane top-k lists
