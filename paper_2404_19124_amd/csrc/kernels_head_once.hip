@@ -19,6 +19,7 @@
 #include <hip/hip_ext.h>
 
 #include <cstring>
+#include <type_traits>
 
 #include "device_utils.h"
 #include "spec_internal.h"
@@ -103,7 +104,7 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
   const int tile_bytes = p.tile_slots * 16, w_last = min(G::WF, p.n_frags[mat] - f0) - 1, s_last = min(G::SF, p.mt_total) - 1;
   const unsigned char* const src = WEIGHTS ? reinterpret_cast<const unsigned char*>(p.w[mat]) + (int64_t)f0 * tile_bytes
                                            : reinterpret_cast<const unsigned char*>(p.b);
-  const int span = WEIGHTS ? (w_last + 1) * tile_bytes : (s_last + 1) * kt * 1024;
+  const int span = WEIGHTS ? w_last * tile_bytes + kt * 1024 : (s_last + 1) * kt * 1024;
   int from[C], to[C];
 #pragma unroll
   for (int i = 0; i < C; ++i) {
@@ -155,11 +156,15 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
     for (int m = 0; m < MB; ++m) acc[m][n] = z;
   }
 
-  for (int base = 0; base < kt; base += kOnceDW) {
-    // (past the last step the last group again: nobody reads it, and it is in the L2)
-    const auto next = group_buf(min(base + kOnceDW, kt - kOnceDW));
+  // FULL: all steps of the group count.  Else those before kt, K not being a multiple of 32 * 8; what is copied and read past them
+  // lies in the matrices or past their end (zeros) and is not multiplied.
+  auto group = [&](auto full, int base) {
+    constexpr bool FULL = decltype(full)::value;
+    // (past the last group that one again: nobody reads it, and it is in the L2)
+    const auto next = group_buf(min(base + kOnceDW, (kt - 1) / kOnceDW * kOnceDW));
 #pragma unroll
     for (int u = 0; u < kOnceDW; ++u) {
+      if (!FULL && base + u >= kt) break;
       // every wave has read step u's slots, and step u + 1 has landed for all of them
       once_barrier<(DEPTH - 2) * C, true>();
       __builtin_amdgcn_sched_barrier(0);
@@ -193,7 +198,10 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
       __builtin_amdgcn_sched_barrier(0);
     }
     here = next;
-  }
+  };
+  int base = 0;
+  for (; base + kOnceDW <= kt; base += kOnceDW) group(std::true_type{}, base);
+  if (base < kt) group(std::false_type{}, base);
 
   const int col = lane & 15, grp = lane >> 4;
   if (!head) {
@@ -358,8 +366,7 @@ static hipError_t launch_once_t(const OnceArgs& a, int grid, hipStream_t st, hip
   return hipGetLastError();
 }
 
-// Which launches come here: lists of at most 4, K in whole groups of eight steps (the copies move by groups; other widths stay
-// with the dense kernels), all tiles in one round.  Tiles of 128 weight rows where that is one round, else of 160.  Drafts of
+// Which launches come here: lists of at most 4, K of one group of eight steps and more, all tiles in one round.  Tiles of 128 weight rows where that is one round, else of 160.  Drafts of
 // one stage of top-2 (a head alone) and of two of top-1, weights of 800 MB in turn so that none stay in the memory-side cache,
 // the kernels there were before / this one, times as fast against 130, 192, 256, 320 rows:
 //  * 160-row tiles, head alone: 38000 x 1024 1.18, 1.14, 1.21, 1.17;  x 2048 1.15, 1.17, 1.17, 1.13;  x 3072 1.19, 1.21, 1.28, 1.21;
@@ -371,11 +378,14 @@ static hipError_t launch_once_t(const OnceArgs& a, int grid, hipStream_t st, hip
 //  * 128-row tiles with the projection, by difference: 28000 + 4096 76 / 63, 74 / 67, 84 / 78, 93 / 91 us;  20000 + 4096 63 / 59, 68 /
 //    65, 77 / 74, 87 / 87;  18000 + 6144 89 / 80, 93 / 82, 106 / 96, 123 / 119;  28000 + 2048 39 / 35, 45 / 44, 48 / 49, 51 / 55;  18000 +
 //    8192 112 / 107, 132 / 129, 142 / 146, 159 / 163: up to 192 rows, up to 256 for K = 3072 to 6144, from 84 weight rows per CU on.
+//  * K that ends within a group, times as fast, head alone and two stages: 33000 x 3136 1.22, 1.45, 1.27, 1.24 and 1.28, 1.53, 1.32, 1.28;
+//    38000 x 2496 1.24, 1.43, 1.21, 1.19 and 1.25, 1.48, 1.25, 1.21;  28000 x 1600 1.15, 1.11, - and 1.15, 1.11, -;  30000 x 4160
+//    1.19, 1.14, - and 1.19, 1.23, 1.11, 1.12.
 OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   OncePlan pl;
   memset(&pl, 0, sizeof(pl));
   const int64_t cus = n_cu > 0 ? n_cu : 256;
-  if (R <= 128 || R > 320 || n_head <= 0 || k_top < 1 || k_top > 4 || kt % kOnceDW) return pl;
+  if (R <= 128 || R > 320 || n_head <= 0 || k_top < 1 || k_top > 4 || kt < kOnceDW) return pl;
   auto head_tiles = [&](int nb) { return ((int64_t)n_head + 32 * nb - 1) / (32 * nb); };
   auto all_tiles = [&](int nb) { return head_tiles(nb) + (n_proj > 0 ? ((int64_t)n_proj + 32 * nb - 1) / (32 * nb) : 0); };
   const int nb = all_tiles(4) <= cus ? 4 : 5;
@@ -397,7 +407,7 @@ OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
 size_t once_lds_bytes(const OncePlan& pl) { return once_lds(pl.nb, pl.block, pl.kcap); }
 
 hipError_t launch_head_once(const HeadJob& job, const OncePlan& pl, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (job.vt_head <= 0 || job.out_head || job.b_rowmajor || job.kt % kOnceDW || job.kt < kOnceDW || job.k_top > pl.kcap ||
+  if (job.vt_head <= 0 || job.out_head || job.b_rowmajor || job.kt < kOnceDW || job.k_top > pl.kcap ||
       job.nparts != pl.n_head || job.R > 64 * pl.block)
     return hipErrorInvalidValue;
   OnceArgs a;

@@ -27,6 +27,13 @@ def test_tile_kernel_without_scratch():
     assert len(found) == 5 and not any(found.values()), found
 
 
+def test_one_round_kernel_without_scratch():
+    """Its counted waits are for copies: a spill's loads and stores would count with them."""
+    B.lib()
+    found = {name: k[".private_segment_fixed_size"] for name, k in kernels() if "head_once_kernel" in name}
+    assert len(found) == 18 and not any(found.values()), found
+
+
 def test_stage_kernels_share_a_cu():
     """Rows of up to 4096 elements one chunk per thread, up to 8192 two: of the latter two workgroups of 512 threads fit a CU's 512
     registers per lane (four siblings at a time do not), of the former three."""
