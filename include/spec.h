@@ -151,7 +151,10 @@ spec_status_t spec_draft(spec_model_t* m, const void* state, const int32_t* last
  *              every table of stage i as wide as the widest top_k_seq[.][i] of the call
  * The host arrays are consumed before the call returns.  Unlike spec_draft this call copies a few KB
  * of row maps from host memory to the device on hip_stream (a kernel reads them from pinned memory; it may
- * wait for that kernel of the call four calls earlier). */
+ * wait for that kernel of the call four calls earlier).
+ * Recorded into a graph (hip_stream is capturing), the call neither waits nor uses that memory: the graph holds
+ * the maps itself, and each replay is that call again, with its trees and counts, however many calls the
+ * model has seen since.  As with every call of a model, a replay must not overlap another call of it in time. */
 spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, const int32_t* last_tok, int32_t batch,
                                  const int32_t* top_k_seq, const int32_t* B_seq, int32_t B_pad, int32_t* cand_tokens,
                                  float* cand_scores, int32_t* cand_leaf, int32_t* n_cand, const spec_debug_t* dbg,

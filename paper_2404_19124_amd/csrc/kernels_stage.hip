@@ -4,6 +4,8 @@
 // partial results are merged here (which saves a separate launch on the latency-critical batch-1 chain).
 #include "stage_body.h"
 
+#include <cstring>
+
 namespace specdraft {
 
 // Parents from which siblings share a workgroup: one for every CU.  With fewer, what a CU saves others do not lend (a child is
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(kFetchWords) void fetch_maps_kernel(const int32_t* 
     else n_cand[i - n] = v;
   }
   __syncthreads();   // (a word has arrived where it has been stored)
-  if (read && threadIdx.x == 0) __hip_atomic_store(read + blockIdx.x, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) __hip_atomic_store(read + blockIdx.x, ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, uint32_t* read,
@@ -122,6 +124,32 @@ hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* 
   hipLaunchKernelGGL(fetch_maps_kernel, dim3(fetch_groups(n + batch)), dim3(kFetchWords), 0, st, maps, dev, n, n_cand, batch, read,
                      ticket);
   return hipGetLastError();
+}
+
+// The same for a call that is being recorded into a graph: the words travel in the arguments of the launches, which the graph keeps,
+// so every replay finds those of its call, whatever later calls have put into the pinned memory.  One workgroup per launch and
+// a launch per kMapWords words (3840 bytes of arguments): 24 sequences of a 5/3/2 tree are two.
+struct MapWords {
+  int32_t w[kMapWords];
+};
+__global__ __launch_bounds__(kMapWords) void store_maps_kernel(MapWords words, int count, int at, int32_t* __restrict__ dev, int n,
+                                                               int32_t* __restrict__ n_cand) {
+  const int i = threadIdx.x;
+  if (i >= count) return;
+  if (at + i < n) dev[at + i] = words.w[i];
+  else n_cand[at + i - n] = words.w[i];
+}
+
+hipError_t launch_store_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, hipStream_t st) {
+  for (int at = 0; at < n + batch; at += kMapWords) {
+    MapWords words = {};
+    const int count = n + batch - at < kMapWords ? n + batch - at : kMapWords;
+    memcpy(words.w, maps + at, (size_t)count * 4);
+    hipLaunchKernelGGL(store_maps_kernel, dim3(1), dim3(kMapWords), 0, st, words, count, at, dev, n, n_cand);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // ---------------------------------------------------------------------------

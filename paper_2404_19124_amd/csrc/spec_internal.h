@@ -235,11 +235,13 @@ bool f32_fold_fits(int R, int D, int V, int nparts, int max_parts, int64_t half)
 
 // ---- per-sequence trees: n words of `maps` (pinned host memory, device address) to dev, the `batch` words behind them
 // to n_cand; workgroup g of fetch_groups(n + batch) stores `ticket` to read[g] (pinned as well) once it has its words
-// (read = nullptr: not)
 constexpr int kFetchWords = 256;
 constexpr int fetch_groups(int64_t words) { return (int)((words + kFetchWords - 1) / kFetchWords); }
 hipError_t launch_fetch_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, uint32_t* read,
                              uint32_t ticket, hipStream_t st);
+// the same from any host memory, which is read before the call returns (launches that a graph may keep)
+constexpr int kMapWords = 960;
+hipError_t launch_store_maps(const int32_t* maps, int32_t* dev, int n, int32_t* n_cand, int batch, hipStream_t st);
 
 // ---- tree: merge of the last head + leaf scores + top-B ----------------------
 struct TreeJob {

@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -898,18 +899,33 @@ extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, 
   }
   int64_t ints = (int64_t)batch * (2 * n + 1);
   for (int i = 0; i < n; ++i) ints += 2 * dp.R[i];
-  if (ints > m->dyn_ints) return fail(SPEC_ESHAPE, "internal: row maps of %lld words exceed the model's %lld", (long long)ints, (long long)m->dyn_ints);
+  const int64_t words = ints + batch;   // B_seq (for n_cand) behind the maps
+  if (words > m->dyn_ints) return fail(SPEC_ESHAPE, "internal: row maps of %lld words exceed the model's %lld", (long long)words, (long long)m->dyn_ints);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-  // a free pinned slot (the fetch from it may still be pending on the caller's stream)
-  const int slot = m->dyn_next;
-  m->dyn_next = (slot + 1) % spec_model::kDynSlots;
-  {
+  // A call that is being recorded into a graph runs at no time or many times, and at any time later: it takes no slot and waits for
+  // none, its maps go into the graph.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) {   // (the legacy stream beside a capture: the launch says so)
+    (void)hipGetLastError();
+    capture = hipStreamCaptureStatusNone;
+  }
+  const bool recorded = capture != hipStreamCaptureStatusNone;
+  std::unique_ptr<int32_t[]> own;
+  int slot = -1;
+  int32_t* h;
+  if (recorded) {
+    own.reset(new (std::nothrow) int32_t[words]);
+    if (!own) return fail(SPEC_ENOMEM, "host allocation failed");
+    h = own.get();
+  } else {   // a free pinned slot (the fetch from it may still be pending on the caller's stream)
+    slot = m->dyn_next;
+    m->dyn_next = (slot + 1) % spec_model::kDynSlots;
     spec_status_t s = wait_until_read(m, slot);
     if (s != SPEC_OK) return s;
+    h = m->dyn_host[slot];
   }
-  int32_t* h = m->dyn_host[slot];
-  // layout: per stage parent[R_i], rank[R_i]; then the sequence descriptors; then B_seq (for n_cand)
+  // layout: per stage parent[R_i], rank[R_i]; then the sequence descriptors; then B_seq
   int64_t at = 0, p_at[kMaxStages], r_at[kMaxStages];
   for (int i = 0; i < n; ++i) {
     p_at[i] = at;
@@ -941,24 +957,18 @@ extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, 
       }
     }
   }
-  // n_cand for the verify side: the B_seq values, from the same pinned slot
-  int32_t* hb = h + ints;
-  if (ints + batch > m->dyn_ints) return fail(SPEC_ESHAPE, "internal: row maps exceed the model's buffer");
-  for (int q = 0; q < batch; ++q) hb[q] = B_seq[q];
-  const uint32_t ticket = ++m->dyn_calls;
-  // A call that is being captured reports nothing: it runs at no time or many times, and a later call must neither wait for it
-  // nor find its ticket over its own.
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &capture) != hipSuccess) {   // (the legacy stream beside a capture: the launch says so)
-    (void)hipGetLastError();
-    capture = hipStreamCaptureStatusNone;
+  // n_cand for the verify side: the B_seq values
+  for (int q = 0; q < batch; ++q) h[ints + q] = B_seq[q];
+  if (recorded) {
+    HIP_TRY(launch_store_maps(h, m->dyn_dev, (int)ints, n_cand, batch, st));
+  } else {
+    // (one small kernel that reads the pinned slot: two copies by the runtime stood 15 us in front of the draft)
+    const uint32_t ticket = ++m->dyn_calls;
+    HIP_TRY(launch_fetch_maps(m->dyn_host_dev[slot], m->dyn_dev, (int)ints, n_cand, batch,
+                              reinterpret_cast<uint32_t*>(m->dyn_host_dev[slot] + m->dyn_ints), ticket, st));
+    m->dyn_groups[slot] = fetch_groups(words);
+    m->dyn_ticket[slot] = ticket;
   }
-  const bool reports = capture == hipStreamCaptureStatusNone;
-  // (one small kernel that reads the pinned slot: two copies by the runtime stood 15 us in front of the draft)
-  HIP_TRY(launch_fetch_maps(m->dyn_host_dev[slot], m->dyn_dev, (int)ints, n_cand, batch,
-                            reports ? reinterpret_cast<uint32_t*>(m->dyn_host_dev[slot] + m->dyn_ints) : nullptr, ticket, st));
-  m->dyn_groups[slot] = reports ? fetch_groups(ints + batch) : 0;
-  m->dyn_ticket[slot] = ticket;
   for (int i = 0; i < n; ++i) {
     dp.kw[i] = kw[i];
     dp.parent[i] = m->dyn_dev + p_at[i];

@@ -1,5 +1,6 @@
 """Drafts with trees per sequence enqueued behind work that holds the stream: the fifth call waits until the first one's row maps
-have been read, and every call's candidates are its own; 300 sequences: several workgroups fetch."""
+have been read, and every call's candidates are its own; 300 sequences: several workgroups fetch.  Recorded into a graph, every
+call keeps its trees."""
 import pytest
 import torch
 
@@ -62,7 +63,7 @@ def test_a_captured_call_is_waited_for_by_nobody():
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
             run(calls[0], captured)
-        for rep in range(replays):   # (the graph reads the slot it was captured with: three more calls have others)
+        for rep in range(replays):   # (the graph holds its maps itself)
             for t in captured:
                 t.fill_(-7)
             graph.replay()
@@ -74,4 +75,45 @@ def test_a_captured_call_is_waited_for_by_nobody():
             run(calls[n % 3], eager)
             torch.cuda.synchronize()
             assert all(torch.equal(a, b) for a, b in zip(eager, want[n % 3])), (replays, n)
+    step.close()
+
+
+# 300 sequences: the maps of a call are several launches
+@pytest.mark.parametrize("batch", [3, 300])
+def test_more_recorded_calls_than_slots(batch):
+    """Six calls in one graph, replayed after and between eager calls that have used every slot several times: each its own."""
+    wl = W.Workload("recorded", 64, 64, 300, 2, (3, 2), 4, batch, "bf16", "f32", 0.6, seed=67, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    state, last = (t.cuda() for t in W.make_draft_inputs(wl, gen))
+    step = Step(wl, {k: [t.cuda() for t in v] for k, v in w.items()}, max_batch=batch, max_top_k=wl.top_k)
+    calls = [([[1 + (c + q) % 3, 1 + (c * q) % 2] for q in range(batch)], [(c + q) % 2 for q in range(batch)]) for c in range(9)]
+
+    def buffers():
+        i32 = dict(dtype=torch.int32, device="cuda")
+        return [torch.empty((batch, 4, 2), **i32), torch.empty((batch, 4), device="cuda"), torch.empty((batch, 4), **i32),
+                torch.empty((batch,), **i32)]
+
+    def run(call, out):
+        B.spec_draft_dynamic(step.model, state, last, *call, *out)
+        return out
+
+    want = [run(c, buffers()) for c in calls]
+    torch.cuda.synchronize()
+    recorded, eager = [buffers() for _ in range(6)], buffers()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for call, out in zip(calls, recorded):
+            run(call, out)
+    for rep in range(3):
+        for n in range(9):
+            run(calls[(n + rep) % 9], eager)
+            assert all(torch.equal(a, b) for a, b in zip(eager, want[(n + rep) % 9])), (rep, n)
+        for out in recorded:
+            for t in out:
+                t.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        for c, out in enumerate(recorded):
+            assert all(torch.equal(a, b) for a, b in zip(out, want[c])), (rep, c)
     step.close()
