@@ -5,7 +5,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -13,10 +12,10 @@
 #include <memory>
 #include <mutex>
 #include <new>
-#include <thread>
 #include <vector>
 
 #include "spec_internal.h"
+#include "tickets.h"
 
 using namespace specdraft;
 
@@ -844,22 +843,18 @@ extern "C" spec_status_t spec_draft(spec_model_t* m, const void* state, const in
                     hip_stream);
 }
 
-// The slot's last fetch has read it.  Usually long so (four calls ago); a caller that runs further ahead waits here, and after a
-// second the device is asked whether anything is wrong with it.
-static spec_status_t wait_until_read(spec_model* m, int slot) {
-  const uint32_t* read = reinterpret_cast<const uint32_t*>(m->dyn_host[slot] + m->dyn_ints);
-  auto all = [&]() {
-    for (int g = 0; g < m->dyn_groups[slot]; ++g)
-      if (__atomic_load_n(read + g, __ATOMIC_ACQUIRE) != m->dyn_ticket[slot]) return false;
-    return true;
+// The slot's last fetch has read it.  Usually long so (four calls ago); a caller that runs further ahead waits here, for that fetch
+// alone: what else the device has to do, on other streams, may take as long as it likes.
+static spec_status_t wait_until_read(spec_model* m, int slot, hipStream_t st) {
+  hipError_t e = hipSuccess;
+  auto ask = [&]() -> int {   // the caller's stream, whose answer shows a device that is lost
+    e = hipStreamQuery(st);
+    if (e == hipSuccess) return 0;
+    (void)hipGetLastError();
+    return e == hipErrorNotReady ? 0 : 1;
   };
-  for (int tries = 0; !all(); ++tries) {
-    if (tries < 1000) continue;
-    std::this_thread::sleep_for(std::chrono::microseconds(10));
-    if (tries < 1000 + 20000) continue;
-    HIP_TRY(hipDeviceSynchronize());
-    if (!all()) return fail(SPEC_EHIP, "the row maps of an earlier spec_draft_dynamic were never read");
-  }
+  if (wait_for_tickets(reinterpret_cast<const uint32_t*>(m->dyn_host[slot] + m->dyn_ints), m->dyn_groups[slot], m->dyn_ticket[slot], ask))
+    return hip_fail(e, "waiting for the row maps of an earlier spec_draft_dynamic to be read");
   return SPEC_OK;
 }
 
@@ -921,7 +916,7 @@ extern "C" spec_status_t spec_draft_dynamic(spec_model_t* m, const void* state, 
   } else {   // a free pinned slot (the fetch from it may still be pending on the caller's stream)
     slot = m->dyn_next;
     m->dyn_next = (slot + 1) % spec_model::kDynSlots;
-    spec_status_t s = wait_until_read(m, slot);
+    spec_status_t s = wait_until_read(m, slot, st);
     if (s != SPEC_OK) return s;
     h = m->dyn_host[slot];
   }

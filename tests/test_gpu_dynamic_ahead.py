@@ -117,3 +117,37 @@ def test_more_recorded_calls_than_slots(batch):
         for c, out in enumerate(recorded):
             assert all(torch.equal(a, b) for a, b in zip(out, want[c])), (rep, c)
     step.close()
+
+
+def test_a_caller_that_runs_ahead_waits_for_its_own_stream():
+    """The fifth call behind 2 s of work on its stream comes back when that is done, not 5 s of another stream's work."""
+    wl = W.Workload("ahead", 64, 64, 300, 2, (3, 2), 4, 2, "bf16", "f32", 0.6, seed=71, emb_std=0.3)
+    gen = W.make_generator(wl.seed)
+    w = W.make_speculator(wl, gen)
+    state, last = (t.cuda() for t in W.make_draft_inputs(wl, gen))
+    step = Step(wl, {k: [t.cuda() for t in v] for k, v in w.items()}, max_batch=2, max_top_k=wl.top_k)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    outs = [[torch.empty((2, 4, 2), **i32), torch.empty((2, 4), device="cuda"), torch.empty((2, 4), **i32),
+             torch.empty((2,), **i32)] for _ in range(5)]
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def busy(stream, cycles):
+        with torch.cuda.stream(stream):
+            torch.cuda._sleep(cycles)
+
+    t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    busy(own, 1000)
+    t0.record(own)
+    busy(own, 10_000_000)
+    t1.record(own)
+    torch.cuda.synchronize()
+    second = int(1e10 / t0.elapsed_time(t1))   # of _sleep's cycles
+    busy(own, 2 * second)
+    busy(other, 5 * second)
+    for out in outs:   # the fifth takes the first one's slot
+        B.spec_draft_dynamic(step.model, state, last, [[3, 2], [2, 1]], [4, 2], *out, stream=own)
+    assert not other.query()
+    torch.cuda.synchronize()
+    for out in outs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out, outs[0]))
+    step.close()
