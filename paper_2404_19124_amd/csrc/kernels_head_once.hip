@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "device_utils.h"
+#include "once_steps.h"
 #include "spec_internal.h"
 
 namespace specdraft {
@@ -29,8 +30,6 @@ namespace specdraft {
 constexpr int kOnceWaves = 8;      // two along the weight rows, four along the state rows
 constexpr int kOnceWM = 4;
 constexpr int kOnceCopyW = 2;      // waves that copy weights; the others copy states
-constexpr int kOnceDW = 8;         // K-steps (of 32) of weights in LDS
-constexpr int kOnceDS = 4;         // and of states
 constexpr int kOnceLds = 160 * 1024;
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
@@ -112,19 +111,16 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
     from[i] = WEIGHTS ? min(f, w_last) * tile_bytes : min(f, s_last) * kt * 1024;
     to[i] = f * 1024;
   }
-  auto group_buf = [&](int step) {   // from K-step `step` on
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(src + step * 1024), 0, span - step * 1024, 0x00020000);
-  };
-  auto copy = [&](__amdgpu_buffer_rsrc_t buf, int i, int u, int at) {   // into slot u, from step `at` of the buffer's group
+  const auto buf = weight_buffer(src, span);   // (the scalar offset is not part of its check: no copy reaches past it)
+  auto copy = [&](int i, int u, int step) {   // K-step `step` into slot u
     lds_byte* const dst = mine[u % DEPTH] + to[i];
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)dst, 16, lane16, from[i] + at * 1024, 0,
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)dst, 16, lane16, from[i] + step * 1024, 0,
                                              WEIGHTS ? 2 : 0);
   };
-  __amdgpu_buffer_rsrc_t here = group_buf(0);
 #pragma unroll
   for (int u = 0; u < DEPTH; ++u)
 #pragma unroll
-    for (int i = 0; i < C; ++i) copy(here, i, u, u);
+    for (int i = 0; i < C; ++i) copy(i, u, u);
 
   // ---- fragments of two K-steps in registers
   u32x4 aw[2][NB], bf[2][MB];
@@ -156,12 +152,9 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
     for (int m = 0; m < MB; ++m) acc[m][n] = z;
   }
 
-  // FULL: all steps of the group count.  Else those before kt, K not being a multiple of 32 * 8; what is copied and read past them
-  // lies in the matrices or past their end (zeros) and is not multiplied.
+  // FULL: all steps of the group count.  Else those before kt, K not being a multiple of 32 * 8.
   auto group = [&](auto full, int base) {
     constexpr bool FULL = decltype(full)::value;
-    // (past the last group that one again: nobody reads it, and it is in the L2)
-    const auto next = group_buf(min(base + kOnceDW, (kt - 1) / kOnceDW * kOnceDW));
 #pragma unroll
     for (int u = 0; u < kOnceDW; ++u) {
       if (!FULL && base + u >= kt) break;
@@ -173,11 +166,7 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
 #pragma unroll
       for (int n = 0; n < NB; ++n) read_a(u + 1, n);
 #pragma unroll
-      for (int i = 0; i < C; ++i) {
-        if (WEIGHTS) copy(next, i, u, u);
-        else if (u < kOnceDS) copy(here, i, u, u + kOnceDS);
-        else copy(next, i, u, u - kOnceDS);
-      }
+      for (int i = 0; i < C; ++i) copy(i, u, once_next_step(base + u, DEPTH, kt));
 #pragma unroll
       for (int n = 0; n < NB; ++n)
 #pragma unroll
@@ -197,7 +186,6 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    here = next;
   };
   int base = 0;
   for (; base + kOnceDW <= kt; base += kOnceDW) group(std::true_type{}, base);

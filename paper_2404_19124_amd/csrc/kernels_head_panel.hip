@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kPanelWaves * 64) void head_panel_kernel(PanelArgs 
     const auto buf = tile_buf(t0);
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      a[d] = __builtin_amdgcn_raw_buffer_load_b128(buf, lane16, d * 1024, 2);
+      a[d] = load_weight(buf, lane16 + d * 1024);
       __builtin_amdgcn_sched_barrier(0);   // (in this order: the K loop then waits for one at a time)
     }
   }
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kPanelWaves * 64) void head_panel_kernel(PanelArgs 
           if (d % KS != KS - 1) bf[m] = read(m, d + 1);
         }
       }
-      a[d] = __builtin_amdgcn_raw_buffer_load_b128(src, lane16, off + d * 1024, 2);
+      a[d] = load_weight(src, lane16 + off + d * 1024);
       __builtin_amdgcn_sched_barrier(0);
       if (d % KS == KS - 1) slab_at ^= G::SLAB;
     };

@@ -27,3 +27,12 @@ def test_assembly_that_reads_matrix_results_stands_behind_a_wait():
             assert len(reads) == 1 and len(waits) == 1 and max(products) < waits[0] < reads[0]
             # two s_nop of 16 and 8 states: 16 passes of the instruction and 4 more are needed
             assert text.count('"s_nop 15\\n\\ts_nop 7"') == 4
+
+
+def test_loads_that_rely_on_a_buffers_end_are_checked_whole():
+    """A buffer's range check leaves the scalar offset out: a load that may lie past the end carries all of its position in the
+    offset of the lanes.  (Copies into LDS go by scalar offsets, and none of them relies on the check.)"""
+    calls = [(name, m) for name, text in _sources() for m in re.findall(r"raw_buffer_load_b128\(([^;]*)\);", text)]
+    assert calls
+    for name, args in calls:
+        assert re.fullmatch(r"\w+, \w+, 0, 2", args), (name, args)
