@@ -55,3 +55,45 @@ def test_trees_per_sequence():
     assert all(torch.equal(a, b) for a, b in zip(*got))
     for step in steps:
         step.close()
+
+
+# what a head holds: rows whose logits overflow to -inf (most of a part, all but two of the vocabulary, all of it), or are NaN
+@pytest.mark.parametrize("what", ["part", "all_but_two", "all", "nan_first", "nan_last", "nan_state"])
+@pytest.mark.parametrize("case", [(64, 64, 9, (8, 1, 1), 2), (64, 264, 700, (4, 2, 2), 2), (128, 1024, 4093, (2, 2, 1), 3)],
+                         ids=["V9", "V700", "V4093"])
+def test_logits_that_are_not_finite(case, what):
+    """The folded stage takes its parents' partial results as the stage kernel does: same candidates, same scores, NaN where that
+    has NaN; in every stage, so that the next one's fold reads them, and with tokens that name no row of the embedding."""
+    E, D, V, tree, batch = case
+    wl = W.Workload("fold32", E, D, V, len(tree), tree, min(4, math.prod(tree)), batch, "f32", "f32", 0.5, seed=23, emb_std=1.0)
+    gen = W.make_generator(23, "cuda")
+    w = W.make_speculator(wl, gen, device="cuda", ln_affine="random")
+    for i in range(len(tree)):
+        w["ln_beta"][i] += 1.0   # the sum of a state is far above 0: a head row of -3e38 gives -inf
+        head = w["head"][i]
+        if what == "part":
+            head[:V // 2] = -3.0e38
+        elif what == "all_but_two":
+            head[:V // 3] = -3.0e38
+            head[V // 3 + 2:] = -3.0e38
+        elif what == "all":
+            head[:] = -3.0e38
+        elif what != "nan_state":
+            head[0 if what == "nan_first" else -1] = float("nan")
+    steps = [Step(wl, w, debug=debug) for debug in (True, False)]
+    state, last = W.make_draft_inputs(wl, gen, device="cuda")
+    if what == "nan_state":
+        state[1] = float("nan")
+    for _ in range(2):   # (the second pass finds what the first left in the workspace)
+        for step in steps:
+            step.draft(state, last)
+        torch.cuda.synchronize()
+        t = steps[0].debug_tables()
+        lse = torch.cat([x.reshape(-1) for x in t["lse"]])
+        assert bool(torch.isnan(lse).any()) == what.startswith("nan")
+        assert bool(torch.isinf(lse).any()) == (what == "all")
+        a, b = steps[0].cand_scores, steps[1].cand_scores
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(a[~torch.isnan(a)], b[~torch.isnan(b)])
+        assert torch.equal(steps[0].cand_tokens, steps[1].cand_tokens) and torch.equal(steps[0].cand_leaf, steps[1].cand_leaf)
+    for step in steps:
+        step.close()
