@@ -57,3 +57,17 @@ def test_ranges_of_several_tiles(rows, D, V, k):
     assert tok.min() >= 0 and tok.max() < V and all(len(set(r)) == k for r in tok)
     best = -np.sort(-want_logp, axis=1)[:, :k]
     assert np.abs(want_logp[at, tok] - best).max() < 1e-3   # in order, up to ties within that
+
+
+# D, V, top_k, rows; head tiles and tiles of the range that holds both matrices
+@pytest.mark.parametrize("D,V,top_k,rows,mixed", [(320, 70001, (3, 1), 20, (1, 1)), (448, 75001, (6, 1), 31, (2, 1))])
+def test_ranges_of_head_and_projection(D, V, top_k, rows, mixed):
+    """One range closes its last head tiles and then stores tiles of the projection, which the second stage's states show."""
+    plan = B.spec_plan_panel(rows, D, V, top_k[0], D)
+    assert 300 <= plan["kernel"] < 400 and plan["tiles"] > plan["ranges"]
+    head, at = -(-V // plan["tile_rows"]), [r * plan["tiles"] // plan["ranges"] for r in range(plan["ranges"] + 1)]
+    assert [(head - a, b - head) for a, b in zip(at, at[1:]) if a < head < b] == [mixed]
+    wl = W.Workload("mixed", 64, D, V, 2, top_k, top_k[0], rows, "bf16", "f32", 0.6, seed=73, emb_std=0.3)
+    rep, step, od, ov = run_workload(wl, ln_affine="random", gen_device="cpu", check_verify=False)
+    assert rep.rows_checked + rep.rows_skipped_below_exempt == sum(wl.rows())
+    assert rep.rows_exempt <= 1
