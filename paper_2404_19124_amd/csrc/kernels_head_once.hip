@@ -354,9 +354,10 @@ static hipError_t launch_once_t(const OnceArgs& a, int grid, hipStream_t st, hip
   return hipGetLastError();
 }
 
-// Which launches come here: lists of at most 4, K of one group of eight steps and more, all tiles in one round.  Tiles of 128 weight rows where that is one round, else of 160.  Drafts of
-// one stage of top-2 (a head alone) and of two of top-1, weights of 800 MB in turn so that none stay in the memory-side cache,
-// the kernels there were before / this one, times as fast against 130, 192, 256, 320 rows:
+// Which launches come here: lists of at most 4, K of one group of eight steps and more, all tiles in one round.  Tiles of 128 weight
+// rows where that is one round, else of 160.  Drafts of one stage of top-2 (a head alone) and of two of top-1, weights of 800 MB in
+// turn so that none stay in the memory-side cache, the kernels there were before / this one, times as fast against 130, 192, 256,
+// 320 rows:
 //  * 160-row tiles, head alone: 38000 x 1024 1.18, 1.14, 1.21, 1.17;  x 2048 1.15, 1.17, 1.17, 1.13;  x 3072 1.19, 1.21, 1.28, 1.21;
 //    40000 x 4096 1.19, 1.24, 1.22, 1.18;  x 8192 1.11, 1.21, 1.15, 1.17.  With the projection, its launches by difference: 32000 +
 //    1024 31 / 25, 39 / 28, 42 / 30, 44 / 36 us;  + 2048 45 / 40, 61 / 47, 64 / 54, 66 / 59;  + 3072 63 / 54, 82 / 59, 85 / 67, 92 / 74.
@@ -365,7 +366,14 @@ static hipError_t launch_once_t(const OnceArgs& a, int grid, hipStream_t st, hip
 //    0.88: up to 192 rows from 96 weight rows per CU on, up to 256 from 120.
 //  * 128-row tiles with the projection, by difference: 28000 + 4096 76 / 63, 74 / 67, 84 / 78, 93 / 91 us;  20000 + 4096 63 / 59, 68 /
 //    65, 77 / 74, 87 / 87;  18000 + 6144 89 / 80, 93 / 82, 106 / 96, 123 / 119;  28000 + 2048 39 / 35, 45 / 44, 48 / 49, 51 / 55;  18000 +
-//    8192 112 / 107, 132 / 129, 142 / 146, 159 / 163: up to 192 rows, up to 256 for K = 3072 to 6144, from 84 weight rows per CU on.
+//    8192 112 / 107, 132 / 129, 142 / 146, 159 / 163: up to 192 rows, from 84 weight rows per CU on.
+//  * The same against 193 and 256 rows, two stages, us: K = 1536 92.2 / 92.5, 96.6 / 97.5;  1792 106.0 / 105.6, 112.1 / 112.3;  2048
+//    114.2 / 112.9, 119.5 / 120.0;  2112 116.4 / 114.7, 123.8 / 121.8;  2560 132.1 / 129.2, 140.1 / 138.1;  3072 133.6 / 127.1, 140.3 /
+//    135.2;  4096 167.0 / 163.0, 176.5 / 176.9;  6080 231.0 / 224.4, 245.3 / 240.7;  6144 232.2 / 234.1, 247.6 / 252.4;  6208 235.4 /
+//    230.4, 250.7 / 246.7;  7168 268.2 / 263.7, 286.5 / 281.5;  8128 313.6 / 309.1, 334.7 / 330.7;  8192 304.6 / 306.5, 324.7 / 329.6;  8704
+//    321.3 / 313.8, 343.1 / 338.0;  10240 367.0 / 370.0, 392.5 / 402.5;  12288 467 / 472, 509 / 519.  It gains above K = 2048, and
+//    loses where weight tiles lie a whole number of 64 KiB apart (6144, 8192, ..; those of 2048 and 4096 lie 4 KiB further): the
+//    eight fragments of a K-step then ask the same channels at once.  So up to 256 rows for the K above 2048 without that.
 //  * K that ends within a group, times as fast, head alone and two stages: 33000 x 3136 1.22, 1.45, 1.27, 1.24 and 1.28, 1.53, 1.32, 1.28;
 //    38000 x 2496 1.24, 1.43, 1.21, 1.19 and 1.25, 1.48, 1.25, 1.21;  28000 x 1600 1.15, 1.11, - and 1.15, 1.11, -;  30000 x 4160
 //    1.19, 1.14, - and 1.19, 1.23, 1.11, 1.12.
@@ -373,6 +381,7 @@ OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   OncePlan pl;
   memset(&pl, 0, sizeof(pl));
   const int64_t cus = n_cu > 0 ? n_cu : 256;
+  constexpr int kSlots64K = 65536 / 16;
   if (R <= 128 || R > 320 || n_head <= 0 || k_top < 1 || k_top > 4 || kt < kOnceDW) return pl;
   auto head_tiles = [&](int nb) { return ((int64_t)n_head + 32 * nb - 1) / (32 * nb); };
   auto all_tiles = [&](int nb) { return head_tiles(nb) + (n_proj > 0 ? ((int64_t)n_proj + 32 * nb - 1) / (32 * nb) : 0); };
@@ -380,7 +389,7 @@ OncePlan plan_once(int R, int k_top, int n_head, int n_proj, int kt, int n_cu) {
   if (all_tiles(nb) > cus) return pl;
   if (nb == 4) {
     const int64_t weight_rows = (int64_t)n_head + (n_proj > 0 ? n_proj : 0);
-    if (n_proj > 0 ? R > (kt >= 96 && kt <= 192 ? 256 : 192) || weight_rows <= 84 * cus
+    if (n_proj > 0 ? R > (kt > 64 && packed_tile_slots(kt) % kSlots64K ? 256 : 192) || weight_rows <= 84 * cus
                    : R > 256 || weight_rows <= (R > 192 ? 120 : 96) * cus)
       return pl;
   }

@@ -15,7 +15,8 @@ CASES = [(256, 33601, (1, 1), 129, 192, 160), (256, 40640, (4, 1), 192, 192, 160
          (256, 21249, (2, 1), 129, 192, 128), (512, 32256, (4, 1), 192, 192, 128), (3072, 18433, (3, 1), 256, 256, 128),
          (256, 24577, (2,), 129, 192, 128), (512, 25001, (3,), 192, 192, 128), (256, 32768, (4,), 256, 256, 128),
          (256, 32769, (3,), 193, 256, 160), (320, 33001, (1, 1), 320, 320, 160), (448, 40000, (2, 1), 200, 256, 160),
-         (704, 24577, (3,), 150, 192, 128), (832, 31001, (2,), 256, 256, 128), (256, 40960, (4,), 320, 320, 160)]
+         (704, 24577, (3,), 150, 192, 128), (832, 31001, (2,), 256, 256, 128), (256, 40960, (4,), 320, 320, 160),
+         (2112, 20001, (2, 1), 200, 256, 128)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=["x".join(map(str, c)).replace(" ", "") for c in CASES])

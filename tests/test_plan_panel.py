@@ -81,6 +81,16 @@ def test_who_takes_one_round(args, block):
     assert ((p["block_rows"], p["tile_rows"]) if 400 <= p["kernel"] < 1000 else None) == block
 
 
+# 193 to 256 rows beside a projection: above K = 2048, where weight tiles do not lie a whole number of 64 KiB apart
+@pytest.mark.parametrize("k,taken", [(1536, False), (2048, False), (2112, True), (2560, True), (3072, True), (4096, True), (6080, True),
+                                     (6144, False), (6208, True), (7168, True), (8128, True), (8192, False), (10240, False)])
+@pytest.mark.parametrize("rows", [193, 256])
+def test_tiles_of_128_rows_beside_a_projection(rows, k, taken):
+    p = check(rows, k, 30000 - k, 2, k, 256)
+    assert (500 <= p["kernel"] < 1000) == taken
+    assert 500 <= check(192, k, 30000 - k, 2, k, 256)["kernel"] < 1000
+
+
 @pytest.mark.parametrize("args", [(0, 4096, 32000, 2, 0, 256), (64, 100, 32000, 2, 0, 256), (64, 4096, 32000, 9, 0, 256),
                                   (64, 4096, 32000, 0, 0, 256), (64, 4096, 0, 0, 0, 256), (64, 4096, 32000, 2, 0, 0)])
 def test_bad_arguments(args):
