@@ -430,7 +430,7 @@ hipError_t launch_head_once(const HeadJob& job, const OncePlan& pl, hipStream_t 
   case (NB_) * 100 + (MB_) * 10 + 2: return launch_once_t<NB_, MB_, 2>(a, pl.n_tiles, st, ev_start, ev_stop); \
   case (NB_) * 100 + (MB_) * 10 + 3: return launch_once_t<NB_, MB_, 3>(a, pl.n_tiles, st, ev_start, ev_stop); \
   case (NB_) * 100 + (MB_) * 10 + 4: return launch_once_t<NB_, MB_, 4>(a, pl.n_tiles, st, ev_start, ev_stop);
-    ONCE(4, 3) ONCE(4, 4) ONCE(4, 5) ONCE(5, 3) ONCE(5, 4) ONCE(5, 5)
+    ONCE(4, 3) ONCE(4, 4) ONCE(5, 3) ONCE(5, 4) ONCE(5, 5)
 #undef ONCE
     default: return hipErrorInvalidValue;
   }
