@@ -21,9 +21,8 @@
 #include <cstring>
 #include <type_traits>
 
-#include "device_utils.h"
+#include "lane_lists.h"
 #include "once_steps.h"
-#include "spec_internal.h"
 
 namespace specdraft {
 
@@ -31,9 +30,6 @@ constexpr int kOnceWaves = 8;      // two along the weight rows, four along the 
 constexpr int kOnceWM = 4;
 constexpr int kOnceCopyW = 2;      // waves that copy weights; the others copy states
 constexpr int kOnceLds = 160 * 1024;
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef const __attribute__((address_space(3))) u32x4 lds_word;
 
 struct OnceArgs {
   const u32x4* w[2];   // packed weights: head, projection
@@ -59,36 +55,16 @@ struct OnceGeo {
   static constexpr int BYTES = S_AT + kOnceDS * S_STEP;
   static_assert(BYTES <= kOnceLds, "a CU has no more");
 };
-constexpr size_t once_merge_bytes(int mb, int kt) { return (size_t)64 * mb * ((8 * kt + 1) * 8 + 8 * 8); }
-
-// ---- top-k lists: one float64 per entry (high word = the logit, low word breaks ties), as in the tile kernel ----
-__device__ __forceinline__ double once_key(float x, int32_t not_index) {
-  const int32_t b = __float_as_int(x);
-  return __hiloint2double(b, not_index ^ (b >> 31));
-}
-__device__ __forceinline__ float once_logit(double key) { return __int_as_float(__double2hiint(key)); }
-__device__ __forceinline__ int32_t once_index(double key) { return ~(__double2loint(key) ^ (__double2hiint(key) >> 31)); }
-__device__ __forceinline__ float once_reference(double best) { return fmaxf(-2e38f, once_logit(best)); }
-
-// N = copies of this wave that may still be in flight; all LDS reads have returned.  Then the barrier.
-template <int N, bool LDS>
-__device__ __forceinline__ void once_barrier() {
-  static_assert(N >= 0 && N < 64, "the counter has six bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (LDS ? 0 : 15 << 8));
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // WEIGHTS: what this wave copies.  The slots of that ring are distinct objects to the compiler (restrict): a read of one then waits
 // only for this wave's copies into that one, which the counted wait in front of the barrier has already seen land, and not for
 // every copy in flight.  The other ring, which this wave only reads, goes by the plain pointer: what it holds changes behind
-// every barrier.
+// every barrier.  Nothing else is kept in that memory before this returns.
 template <int NB, int MB, int KT, bool WEIGHTS>
-__device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_byte* __restrict c0, lds_byte* __restrict c1,
-                                          lds_byte* __restrict c2, lds_byte* __restrict c3, lds_byte* __restrict c4,
-                                          lds_byte* __restrict c5, lds_byte* __restrict c6, lds_byte* __restrict c7,
-                                          unsigned char* smem) {
+__device__ __forceinline__ void once_contract(const OnceArgs& p, lds_byte* lds, lds_byte* __restrict c0, lds_byte* __restrict c1,
+                                              lds_byte* __restrict c2, lds_byte* __restrict c3, lds_byte* __restrict c4,
+                                              lds_byte* __restrict c5, lds_byte* __restrict c6, lds_byte* __restrict c7,
+                                              f32x4 (&acc)[MB][NB]) {
   using G = OnceGeo<NB, MB>;
   static_assert(kOnceDW == 8 && kOnceDS == 4, "the slots");
   lds_byte* const mine[8] = {c0, c1, c2, c3, c4, c5, c6, c7};   // (four of them for the states)
@@ -133,13 +109,12 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
     lds_byte* const slot = WEIGHTS ? lds + G::S_AT + (u % kOnceDS) * G::S_STEP : mine[u % kOnceDS];
     bf[u & 1][m] = *reinterpret_cast<lds_word*>(slot + b_at + m * 1024);
   };
-  once_barrier<(DEPTH - 1) * C, false>();
+  copies_landed_barrier<(DEPTH - 1) * C, false>();
 #pragma unroll
   for (int n = 0; n < NB; ++n) read_a(0, n);
 #pragma unroll
   for (int m = 0; m < MB; ++m) read_b(0, m);
 
-  f32x4 acc[MB][NB];
   // (weight rows past the vocabulary start, and stay, at -inf: no mask in the epilogue)
   const int v0 = (f0 + wn * NB) * 16 + (lane >> 4) * 4;   // this lane's weight rows: v0 + 16 n + i
   const int v_end = head ? p.n_valid : 0x7fffffff;
@@ -159,7 +134,7 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
     for (int u = 0; u < kOnceDW; ++u) {
       if (!FULL && base + u >= kt) break;
       // every wave has read step u's slots, and step u + 1 has landed for all of them
-      once_barrier<(DEPTH - 2) * C, true>();
+      copies_landed_barrier<(DEPTH - 2) * C, true>();
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int m = 0; m < MB; ++m) read_b(u + 1, m);
@@ -190,11 +165,20 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
   int base = 0;
   for (; base + kOnceDW <= kt; base += kOnceDW) group(std::true_type{}, base);
   if (base < kt) group(std::false_type{}, base);
+}
 
-  const int col = lane & 15, grp = lane >> 4;
+// What becomes of a tile's products: a projection's are stored, a head's closed.
+template <int NB, int MB, int KT>
+__device__ __forceinline__ void once_close(const OnceArgs& p, const f32x4 (&acc)[MB][NB], unsigned char* smem) {
+  using G = OnceGeo<NB, MB>;
+  const int lane = threadIdx.x & 63, col = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave / kOnceWM, wm = wave % kOnceWM;
+  const int range = blockIdx.x;
+  const bool head = range < p.n_head;
+  const int f0 = (range - (head ? 0 : p.n_head)) * G::WF, v0 = (f0 + wn * NB) * 16 + (lane >> 4) * 4;
   if (!head) {
     // ---- store: lane = state row lane % 16 of every state fragment, four consecutive columns of each weight fragment
-    once_barrier<0, true>();   // (LDS goes back with nothing on its way into it)
+    copies_landed_barrier<0, true>();   // (LDS goes back with nothing on its way into it)
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
       if (f0 + wn * NB + n < p.n_frags[1]) {
@@ -229,7 +213,7 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
       asm volatile("" : "+v"(not_index));   // (one value for the MB rows)
       double key[MB];
 #pragma unroll
-      for (int m = 0; m < MB; ++m) key[m] = once_key(__builtin_amdgcn_fmed3f(acc[m][n][i], lowest, highest), not_index);
+      for (int m = 0; m < MB; ++m) key[m] = list_key(__builtin_amdgcn_fmed3f(acc[m][n][i], lowest, highest), not_index);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < KT; ++q) {   // down the lists, the smaller of each pair moves on
@@ -246,7 +230,7 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
     sum[m] = 0.f;
-    ml[m] = -once_reference(lk[m][0]) * kLog2e;
+    ml[m] = -list_reference(lk[m][0]) * kLog2e;
   }
 #pragma unroll
   for (int n = 0; n < NB; ++n)
@@ -255,69 +239,8 @@ __device__ __forceinline__ void once_tile(const OnceArgs& p, lds_byte* lds, lds_
 #pragma unroll
       for (int m = 0; m < MB; ++m) sum[m] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[m][n][i], kLog2e, ml[m]));
 
-  // ---- merge the 8 lane lists of every row (4 lane groups x 2 waves) into the workgroup's partial.  LDS aliases the copies'
-  // buffers: all copies land first, for all waves.
-  once_barrier<0, true>();
-  constexpr int ROWS = 64 * MB, RS = 8 * KT + 1;
-  uint64_t* sk = reinterpret_cast<uint64_t*>(smem);            // [ROWS][RS]
-  float* sm = reinterpret_cast<float*>(sk + ROWS * RS);        // [ROWS][8]
-  float* ss = sm + ROWS * 8;
-  {
-    const int list = wn * 4 + grp;   // this lane's place among the 8 that hold a row
-#pragma unroll
-    for (int m = 0; m < MB; ++m) {
-      const int rl = (wm * MB + m) * 16 + col;
-#pragma unroll
-      for (int q = 0; q < KT; ++q) sk[rl * RS + list * KT + q] = best_key(once_logit(lk[m][q]), once_index(lk[m][q]));
-      sm[rl * 8 + list] = once_reference(lk[m][0]);
-      ss[rl * 8 + list] = sum[m];
-    }
-  }
-  __syncthreads();
-  const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
-#pragma unroll 1
-  for (int r0 = wave * 8; r0 < p.R; r0 += kOnceWaves * 8) {
-    const int r = min(r0 + (lane >> 3), p.R - 1), s8 = lane & 7;
-    const bool live = r0 + (lane >> 3) < p.R;
-    uint64_t hk[KT];
-#pragma unroll
-    for (int q = 0; q < KT; ++q) hk[q] = sk[r * RS + s8 * KT + q];
-    const float m = sm[r * 8 + s8], s = ss[r * 8 + s8];
-    float mx = fmaxf(m, dpp_f<kDppXor1>(m));
-    mx = fmaxf(mx, dpp_f<kDppXor2>(mx));
-    mx = fmaxf(mx, dpp_f<kDppHalfMirror>(mx));
-    float tot = s * __expf(m - mx);
-    tot += dpp_f<kDppXor1>(tot);
-    tot += dpp_f<kDppXor2>(tot);
-    tot += dpp_f<kDppHalfMirror>(tot);
-    const int64_t slot = (int64_t)r * p.nparts + range;
-    if (live && s8 == 0) {
-      p.part.m[slot] = mx;
-      p.part.s[slot] = tot;
-    }
-#pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      if (j < p.k_top) {
-        uint64_t best = key_step<kDppXor1>(hk[0]);
-        best = key_step<kDppXor2>(best);
-        best = key_step<kDppHalfMirror>(best);
-        const bool won = hk[0] == best;   // the owner of the winner pops it
-#pragma unroll
-        for (int q = 0; q + 1 < KT; ++q) {
-          const uint64_t up = opaque_key(hk[q + 1]);
-          hk[q] = won ? up : hk[q];
-        }
-        hk[KT - 1] = won ? kEmpty : hk[KT - 1];
-        if (live && s8 == j) {
-          float bv;
-          int32_t bi;
-          best_unkey(best, bv, bi);
-          p.part.val[slot * p.k_top + j] = bv;
-          p.part.idx[slot * p.k_top + j] = bi;
-        }
-      }
-    }
-  }
+  copies_landed_barrier<0, true>();   // nothing is on its way into LDS any more, for all waves
+  merge_lane_lists<MB, KT>(smem, lk, sum, wave, lane, 0, p.R, p.part, p.k_top, p.nparts, range);
 }
 
 template <int NB, int MB, int KT>
@@ -326,17 +249,21 @@ __global__ __launch_bounds__(kOnceWaves * 64) void head_once_kernel(OnceArgs p) 
   using G = OnceGeo<NB, MB>;
   lds_byte* const l = (lds_byte*)smem;
   lds_byte* const s = l + G::S_AT;
-  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < kOnceCopyW)
-    once_tile<NB, MB, KT, true>(p, l, l, l + G::W_STEP, l + 2 * G::W_STEP, l + 3 * G::W_STEP, l + 4 * G::W_STEP, l + 5 * G::W_STEP,
-                                l + 6 * G::W_STEP, l + 7 * G::W_STEP, smem);
-  else
-    once_tile<NB, MB, KT, false>(p, l, s, s + G::S_STEP, s + 2 * G::S_STEP, s + 3 * G::S_STEP, nullptr, nullptr, nullptr, nullptr,
-                                 smem);
+  f32x4 acc[MB][NB];
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < kOnceCopyW) {
+    once_contract<NB, MB, KT, true>(p, l, l, l + G::W_STEP, l + 2 * G::W_STEP, l + 3 * G::W_STEP, l + 4 * G::W_STEP,
+                                    l + 5 * G::W_STEP, l + 6 * G::W_STEP, l + 7 * G::W_STEP, acc);
+    once_close<NB, MB, KT>(p, acc, smem);
+  } else {
+    once_contract<NB, MB, KT, false>(p, l, s, s + G::S_STEP, s + 2 * G::S_STEP, s + 3 * G::S_STEP, nullptr, nullptr, nullptr,
+                                     nullptr, acc);
+    once_close<NB, MB, KT>(p, acc, smem);
+  }
 }
 
 static constexpr size_t once_lds(int nb, int mb, int kt) {
   const size_t rings = (size_t)kOnceDW * 2 * nb * 1024 + (size_t)kOnceDS * kOnceWM * mb * 1024;
-  return once_merge_bytes(mb, kt) > rings ? once_merge_bytes(mb, kt) : rings;
+  return list_merge_bytes(mb, kt) > rings ? list_merge_bytes(mb, kt) : rings;
 }
 
 template <int NB, int MB, int KT>

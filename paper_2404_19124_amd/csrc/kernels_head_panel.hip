@@ -21,8 +21,7 @@
 
 #include <cstring>
 
-#include "device_utils.h"
-#include "spec_internal.h"
+#include "lane_lists.h"
 
 namespace specdraft {
 
@@ -32,9 +31,6 @@ constexpr int kPanelCopy = kPanelWaves - kPanelFrags;   // waves that copy state
 constexpr int kPanelCols = 16 * kPanelFrags;
 constexpr int kPanelLd = kPanelCols + 8;                // floats between two rows of logits in LDS: eight rows of eight lanes, 64 banks
 constexpr size_t kPanelLds = 160 * 1024;
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef const __attribute__((address_space(3))) u32x4 lds_word;
 
 struct PanelArgs {
   const u32x4* w[2];   // packed weights: head, projection
@@ -62,27 +58,6 @@ struct PanelGeo {
   static constexpr int BYTES = LOGITS_AT + 16 * MF * kPanelLd * 4;
   static_assert(D % KS == 0 && BYTES <= (int)kPanelLds && CP < 64, "");
 };
-
-// ---- top-k lists: one float64 per entry (high word = the logit, low word breaks ties), as in the tile kernel ----
-__device__ __forceinline__ double panel_key(float x, int32_t not_index) {
-  const int32_t b = __float_as_int(x);
-  return __hiloint2double(b, not_index ^ (b >> 31));
-}
-__device__ __forceinline__ uint64_t panel_best_key(double key) {
-  const int32_t hi = __double2hiint(key);
-  return best_key(__int_as_float(hi), ~(__double2loint(key) ^ (hi >> 31)));
-}
-
-__device__ __forceinline__ float row8_max(float x) {   // over eight neighbouring lanes
-  x = fmaxf(x, dpp_f<kDppXor1>(x));
-  x = fmaxf(x, dpp_f<kDppXor2>(x));
-  return fmaxf(x, dpp_f<kDppHalfMirror>(x));
-}
-__device__ __forceinline__ float row8_sum(float x) {
-  x += dpp_f<kDppXor1>(x);
-  x += dpp_f<kDppXor2>(x);
-  return x + dpp_f<kDppHalfMirror>(x);
-}
 
 __device__ __forceinline__ void wait_copies() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }   // vmcnt(0)
 __device__ __forceinline__ void wave_barrier() {   // every LDS access of this wave has returned
@@ -175,7 +150,7 @@ __global__ __launch_bounds__(kPanelWaves * 64) void head_panel_kernel(PanelArgs 
       for (int e = 0; e < KT; ++e) lk[e] = __hiloint2double(__float_as_int(SPEC_NEG_INF), kIdxNone);
 #pragma unroll
       for (int i = 0; i < NX; ++i) {
-        double key = panel_key(__builtin_amdgcn_fmed3f(x[i], lowest, highest), ~(v0 + 8 * i + j));
+        double key = list_key(__builtin_amdgcn_fmed3f(x[i], lowest, highest), ~(v0 + 8 * i + j));
 #pragma unroll
         for (int e = 0; e < KT; ++e) {   // down the list, the smaller of each pair moves on
           const double old = lk[e];
@@ -185,7 +160,7 @@ __global__ __launch_bounds__(kPanelWaves * 64) void head_panel_kernel(PanelArgs 
       }
       uint64_t hk[KT + 1];   // with the one carried along
 #pragma unroll
-      for (int e = 0; e < KT; ++e) hk[e] = panel_best_key(lk[e]);
+      for (int e = 0; e < KT; ++e) hk[e] = list_best_key(lk[e]);
       uint64_t c = run_key[q];
 #pragma unroll
       for (int e = 0; e < KT; ++e) {
@@ -199,9 +174,7 @@ __global__ __launch_bounds__(kPanelWaves * 64) void head_panel_kernel(PanelArgs 
 #pragma unroll
       for (int e = 0; e < KT; ++e) {
         if (e < p.k_top) {
-          uint64_t best = key_step<kDppXor1>(hk[0]);
-          best = key_step<kDppXor2>(best);
-          best = key_step<kDppHalfMirror>(best);
+          const uint64_t best = row8_best_key(hk[0]);
           const bool won = hk[0] == best;   // the owner of the winner pops it
 #pragma unroll
           for (int u = 0; u < KT; ++u) {

@@ -25,8 +25,7 @@
 
 #include <cstring>
 
-#include "device_utils.h"
-#include "spec_internal.h"
+#include "lane_lists.h"
 
 namespace specdraft {
 
@@ -35,9 +34,6 @@ constexpr int kWM = 4;           // waves along the state rows; two along the we
 constexpr int kWaves = 2 * kWM;
 constexpr int kNB = 8;           // 16-row weight fragments per wave
 constexpr int kWF = 2 * kNB;     // weight fragments of a tile
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef const __attribute__((address_space(3))) u32x4 lds_word;
 
 struct TileArgs {
   const u32x4* w;    // packed head weights
@@ -48,18 +44,6 @@ struct TileArgs {
   Partials part;
 };
 
-// ---- top-k lists: one float64 per entry, as in the wide kernel (high word = the logit, low word breaks ties) ----
-__device__ __forceinline__ double tile_key(float x, int32_t not_index) {
-  const int32_t b = __float_as_int(x);
-  return __hiloint2double(b, not_index ^ (b >> 31));
-}
-__device__ __forceinline__ float tile_logit(double key) { return __int_as_float(__double2hiint(key)); }
-__device__ __forceinline__ int32_t tile_index(double key) {
-  return ~(__double2loint(key) ^ (__double2hiint(key) >> 31));
-}
-// What a row's exponentials are relative to: its best logit so far, or where it has none (-inf and NaN only; weight rows past
-// the vocabulary) a number below every logit whose product with log2(e) is still finite, so that exp(-inf) is 0 there too.
-__device__ __forceinline__ float row_reference(double best) { return fmaxf(-2e38f, tile_logit(best)); }
 // The accumulators stay where they are across the K loop: left to itself the register allocator lets them change places
 // there for the sake of the epilogue (230 moves in a loop of 160 matrix instructions).
 template <int MB>
@@ -82,22 +66,13 @@ struct TileGeo {
 
 constexpr bool tile_parks(int mb, int kt) { return mb == 4 && kt == 3; }
 
-// N = copies of this wave that may still be in flight; all LDS reads have returned.  Then the barrier.
-template <int N, bool LDS>
-__device__ __forceinline__ void copies_landed_barrier() {
-  static_assert(N >= 0 && N < 64, "the counter has six bits");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (LDS ? 0 : 15 << 8));
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // The four buffers are distinct objects to the compiler (restrict): a read of one then waits only for the copies into that
-// one, which the counted wait in front of the barrier has already seen land, and not for every copy in flight.
+// one, which the counted wait in front of the barrier has already seen land, and not for every copy in flight.  Nothing else is
+// kept in that memory before this returns.
 template <int MB, int KT>
-__device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, int mtile, int range,
+__device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, int mtile, int wave,
                                            lds_byte* __restrict b0, lds_byte* __restrict b1, lds_byte* __restrict b2,
-                                           lds_byte* __restrict b3, lds_byte* park, unsigned char* smem) {
+                                           lds_byte* __restrict b3, lds_byte* park, float (&sum)[MB], double (&lk)[MB][KT]) {
   using G = TileGeo<MB>;
   static_assert(kSteps == 4, "four buffers");
   lds_byte* const bufs[kSteps] = {b0, b1, b2, b3};
@@ -107,7 +82,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     asm volatile("" : "+s"(none));   // (or the first answer is kept)
     return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
   };
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = wave / kWM, wm = wave % kWM;
+  const int wn = wave / kWM, wm = wave % kWM;
   const int kt = p.kt;
 
   // ---- copies: 1 KiB = one fragment of the packed layout per instruction; wave w takes fragments w, w + 8, ...
@@ -177,8 +152,6 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
 
   // running state of this lane, per state row 16 * (wm * MB + m) + col of the block: its best logits so far, and the sum of
   // exponentials relative to the first of them
-  float sum[MB];
-  double lk[MB][KT];
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
     sum[m] = 0.f;
@@ -262,7 +235,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     asm volatile("" : "+v"(lowest), "+v"(highest));
     float ml[MB];
 #pragma unroll
-    for (int m = 0; m < MB; ++m) ml[m] = row_reference(lk[m][0]);
+    for (int m = 0; m < MB; ++m) ml[m] = list_reference(lk[m][0]);
 #pragma unroll
     for (int n = 0; n < kNB; ++n)
 #pragma unroll
@@ -275,7 +248,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
         for (int m = 0; m < MB; ++m) x[m] = __builtin_amdgcn_fmed3f(acc[m][n][i], lowest, highest);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < MB; ++m) key[m] = tile_key(x[m], not_index);
+        for (int m = 0; m < MB; ++m) key[m] = list_key(x[m], not_index);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < KT; ++q) {   // down the lists, the smaller of each pair moves on
@@ -291,7 +264,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int m = 0; m < MB; ++m) {
-      const float mx = row_reference(lk[m][0]);
+      const float mx = list_reference(lk[m][0]);
       sum[m] *= __builtin_amdgcn_exp2f((ml[m] - mx) * kLog2e);
       ml[m] = -mx * kLog2e;
     }
@@ -304,72 +277,7 @@ __device__ __forceinline__ void tile_range(const TileArgs& p, int t0, int t1, in
     if (PARK && t + 1 < t1) put();
   }
 
-  // ---- merge the 8 lane lists of every row (4 lane groups x 2 waves) into the workgroup's partial, as the wide
-  // kernel does.  LDS aliases the copies' buffers: all copies land first, for all waves.
-  copies_landed_barrier<0, true>();
-  constexpr int ROWS = 16 * kWM * MB;
-  constexpr int RS = 8 * KT + 1;
-  uint64_t* sk = reinterpret_cast<uint64_t*>(smem);            // [ROWS][RS]
-  float* sm = reinterpret_cast<float*>(sk + ROWS * RS);        // [ROWS][8]
-  float* ss = sm + ROWS * 8;
-  const int lane = lane_id(), tid = wave * 64 + lane, col = lane & 15, grp = lane >> 4;
-  {
-    const int src = wn * 4 + grp;   // this lane's place among the 8 that hold a row
-#pragma unroll
-    for (int m = 0; m < MB; ++m) {
-      const int rl = (wm * MB + m) * 16 + col;
-#pragma unroll
-      for (int q = 0; q < KT; ++q) sk[rl * RS + src * KT + q] = best_key(tile_logit(lk[m][q]), tile_index(lk[m][q]));
-      sm[rl * 8 + src] = row_reference(lk[m][0]);
-      ss[rl * 8 + src] = sum[m];
-    }
-  }
-  __syncthreads();
-  const uint64_t kEmpty = best_key(SPEC_NEG_INF, kIdxNone);
-#pragma unroll 1
-  for (int r0 = 0; r0 < ROWS; r0 += kWaves * 8) {
-    const int rl = min(r0 + (tid >> 3), ROWS - 1), s8 = tid & 7;
-    const int r = mtile * ROWS + rl;
-    const bool live = r0 + (tid >> 3) < ROWS && r < p.R;
-    uint64_t hk[KT];
-#pragma unroll
-    for (int q = 0; q < KT; ++q) hk[q] = sk[rl * RS + s8 * KT + q];
-    const float m = sm[rl * 8 + s8], s = ss[rl * 8 + s8];
-    float mx = fmaxf(m, dpp_f<kDppXor1>(m));
-    mx = fmaxf(mx, dpp_f<kDppXor2>(mx));
-    mx = fmaxf(mx, dpp_f<kDppHalfMirror>(mx));
-    float tot = s * __expf(m - mx);
-    tot += dpp_f<kDppXor1>(tot);
-    tot += dpp_f<kDppXor2>(tot);
-    tot += dpp_f<kDppHalfMirror>(tot);
-    const int64_t slot = (int64_t)r * p.nparts + range;
-    if (live && s8 == 0) {
-      p.part.m[slot] = mx;
-      p.part.s[slot] = tot;
-    }
-#pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      if (j < p.k_top) {
-        uint64_t best = key_step<kDppXor1>(hk[0]);
-        best = key_step<kDppXor2>(best);
-        best = key_step<kDppHalfMirror>(best);
-        const bool won = hk[0] == best;   // the owner of the winner pops it
-#pragma unroll
-        for (int q = 0; q + 1 < KT; ++q) {
-          const uint64_t up = opaque_key(hk[q + 1]);
-          hk[q] = won ? up : hk[q];
-        }
-        hk[KT - 1] = won ? kEmpty : hk[KT - 1];
-        if (live && s8 == j) {
-          float bv;
-          int32_t bi;
-          best_unkey(best, bv, bi);
-          p.part.val[slot * p.k_top + j] = bv;
-          p.part.idx[slot * p.k_top + j] = bi;
-        }
-      }
-    }
-  }
+  copies_landed_barrier<0, true>();   // nothing is on its way into LDS any more, for all waves
 }
 
 template <int MB, int KT>
@@ -385,7 +293,15 @@ __global__ __launch_bounds__(kWaves * 64) void head_tile_kernel(TileArgs p) {
   const int t0 = (int)((int64_t)range * p.n_tiles / p.n_ranges);
   const int t1 = (int)((int64_t)(range + 1) * p.n_tiles / p.n_ranges);
   lds_byte* l = (lds_byte*)smem;
-  tile_range<MB, KT>(p, t0, t1, mtile, range, l, l + G::STEP, l + 2 * G::STEP, l + 3 * G::STEP, l + 4 * G::STEP, smem);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float sum[MB];
+  double lk[MB][KT];
+  tile_range<MB, KT>(p, t0, t1, mtile, wave, l, l + G::STEP, l + 2 * G::STEP, l + 3 * G::STEP, l + 4 * G::STEP, sum, lk);
+  // (the lane is asked for anew here too: see tile_range)
+  uint32_t none = 0;
+  asm volatile("" : "+s"(none));
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
+  merge_lane_lists<MB, KT>(smem, lk, sum, wave, lane, mtile * 64 * MB, p.R, p.part, p.k_top, p.nparts, range);
 }
 
 template <int MB, int KT>
@@ -443,7 +359,7 @@ TilePlan plan_tile(int R, int k_top, int n_head, int kt, int n_cu) {
 size_t tile_lds_bytes(const TilePlan& pl) {
   const size_t steps = (size_t)kSteps * (kWF + 2 * pl.block) * 1024 +
                        (tile_parks(pl.block / 2, pl.kcap) ? (size_t)kWaves * 64 * (pl.block / 2) * 8 : 0);
-  const size_t merge = (size_t)32 * pl.block * ((8 * pl.kcap + 1) * 8 + 8 * 8);
+  const size_t merge = list_merge_bytes(pl.block / 2, pl.kcap);
   return steps > merge ? steps : merge;
 }
 

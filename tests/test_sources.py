@@ -36,3 +36,15 @@ def test_loads_that_rely_on_a_buffers_end_are_checked_whole():
     assert calls
     for name, args in calls:
         assert re.fullmatch(r"\w+, \w+, 0, 2", args), (name, args)
+
+
+def test_what_lies_in_restricted_buffers_is_reached_through_them_only():
+    """Copies into LDS go through restricted pointers, so that a read waits for those into its own buffer alone.  While they are in
+    scope nothing may reach that memory by another name; the merges that use it again stand behind."""
+    found = 0
+    for name, text in _sources():
+        for head, body in re.findall(r"\n(__device__[^\n{]*\((?:[^{}]*?)__restrict[^{}]*\) \{)(.*?)\n\}\n", text, re.S):
+            if "lds_byte* __restrict" in head:
+                found += 1
+                assert "smem" not in head + body, name
+    assert found == 2
