@@ -212,8 +212,9 @@ spec_status_t spec_verify_dynamic(const void* base_logits, int32_t logits_dtype,
                                   int32_t* greedy, int32_t* accept_len, int32_t* best_cand, int32_t* out_tokens,
                                   int32_t* n_out, int32_t* accept_all, void* hip_stream);
 
-/* Parity aid: full log-softmax rows of stage `stage`'s head for given states,
- * computed by the same contraction kernels as spec_draft with a store epilogue.
+/* Parity aid: full log-softmax rows of stage `stage`'s head for given states, from the streaming and dense
+ * contraction kernels (spec_plan_contraction's) with a store epilogue.  The kernels that keep only a row's top-k
+ * (panel, one-round and tile kernel, 17 rows and more) have none: a draft that takes them is not checked by this.
  *   states dev [rows, D] weight_dtype, 16-byte aligned;  logp dev [rows, V] float32;  rows <= max rows of the model. */
 spec_status_t spec_head_logp(spec_model_t* m, int32_t stage, const void* states, int32_t rows,
                              float* logp, void* hip_stream);
@@ -286,9 +287,10 @@ spec_status_t spec_advance(const void* hidden, int32_t hidden_dtype, int32_t bat
  * SPEC_EINVAL on bad arguments (nothing is launched). */
 spec_status_t spec_copy_probe(const void* src, void* dst, int64_t bytes, void* hip_stream);
 
-/* Host-only query (no device, no model, no HIP call): the launch plan the library uses for ONE
- * contraction of the draft (Sec. 3.1: a stage's vocabulary head, with the next stage's state
- * projection riding in the same launch) in the bf16 configuration:
+/* Host-only query (no device, no model, no HIP call): the launch plan of the streaming and dense kernels for ONE
+ * contraction (Sec. 3.1: a stage's vocabulary head, with the next stage's state projection riding in the same
+ * launch) in the bf16 configuration.  A projection alone and spec_head_logp's heads are launched like this; a draft's head is
+ * where neither spec_plan_panel nor (a head alone) spec_plan_head names another kernel:
  *   rows    state rows (>= 1);  k  their width (multiple of 64)
  *   n_head  head rows (vocabulary), 0 = no head;  k_top  entries kept per row (1..8; ignored without a head)
  *   n_proj  projection rows, 0 = none (n_head + n_proj >= 1)
@@ -305,19 +307,21 @@ typedef struct {
   int32_t k_split;      /* workgroups per tile along k (a projection alone), 1 otherwise */
   int32_t workgroups;   /* row_blocks * ranges * k_split */
   int32_t lds_bytes;    /* dynamic LDS per workgroup */
-  int32_t proj_apart;   /* 1: spec_draft does not launch this pair as one contraction (its tile list would make
-                           the launch one tile longer for a few ranges) but as two, whose plans are those of
-                           (n_head, 0) and (0, n_proj); the other fields describe the single launch anyway */
+  int32_t proj_apart;   /* 1: on these kernels spec_draft does not launch this pair as one contraction (its tile list would
+                           make the launch one tile longer for a few ranges) but as two, whose plans are those of
+                           (n_head, 0) and (0, n_proj); the other fields describe the single launch anyway.
+                           (0 where spec_plan_panel takes the pair: that is one launch) */
 } spec_plan_t;
 /* SPEC_EINVAL: arguments out of range; SPEC_ESHAPE: no kernel instance serves the plan (a library bug). */
 spec_status_t spec_plan_contraction(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_proj,
                                     int32_t n_cu, spec_plan_t* out);
-/* The same for a head that is launched alone (the last stage's, or with proj_apart) for its top-k: of more than 64 rows the
- * tile kernel takes what its own estimate finds cheaper there, and the plan is then that kernel's; else it is
- * spec_plan_contraction's, which describes the other kernels only. */
+/* The same for a head that is launched alone (the last stage's, or with proj_apart) for its top-k and that spec_plan_panel
+ * leaves: of more than 64 rows the tile kernel takes what its own estimate finds cheaper than the dense ones, and the plan is then
+ * that kernel's; else it is spec_plan_contraction's. */
 spec_status_t spec_plan_head(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_cu, spec_plan_t* out);
-/* The same for a head with (or, n_proj = 0, without) the next projection as a draft launches it for its top-k: where the panel
- * kernel or head_once_kernel takes it, that kernel's plan, ahead of both above; else spec_plan_contraction's. */
+/* The query a draft asks first, for a head with (or, n_proj = 0, without) the next projection and its top-k: where the panel
+ * kernel or head_once_kernel takes it, that kernel's plan, and the two above do not count; else spec_plan_contraction's, and a
+ * head alone is spec_plan_head's. */
 spec_status_t spec_plan_panel(int32_t rows, int32_t k, int32_t n_head, int32_t k_top, int32_t n_proj, int32_t n_cu,
                               spec_plan_t* out);
 

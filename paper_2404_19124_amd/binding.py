@@ -509,21 +509,21 @@ def spec_advance(hidden: torch.Tensor, best_cand: torch.Tensor, accept_len: torc
 
 
 def spec_plan_contraction(rows: int, k: int, n_head: int, k_top: int, n_proj: int, n_cu: int = 256) -> dict:
-    """The launch plan of one contraction (host-only: needs no GPU)."""
+    """The launch plan of one contraction on the streaming and dense kernels (host-only: needs no GPU)."""
     out = spec_plan_t()
     _check(lib().spec_plan_contraction(int(rows), int(k), int(n_head), int(k_top), int(n_proj), int(n_cu), C.byref(out)))
     return {name: int(getattr(out, name)) for name, _ in spec_plan_t._fields_}
 
 
 def spec_plan_head(rows: int, k: int, n_head: int, k_top: int, n_cu: int = 256) -> dict:
-    """The launch plan of a head that is launched alone for its top-k (host-only: needs no GPU)."""
+    """The launch plan of a head that is launched alone for its top-k and that spec_plan_panel leaves (host-only: needs no GPU)."""
     out = spec_plan_t()
     _check(lib().spec_plan_head(int(rows), int(k), int(n_head), int(k_top), int(n_cu), C.byref(out)))
     return {name: int(getattr(out, name)) for name, _ in spec_plan_t._fields_}
 
 
 def spec_plan_panel(rows: int, k: int, n_head: int, k_top: int, n_proj: int, n_cu: int = 256) -> dict:
-    """The launch plan of a draft's head and the projection that rides with it (host-only: needs no GPU)."""
+    """The launch plan of a draft's head and the projection that rides with it, asked before the others (host-only: needs no GPU)."""
     out = spec_plan_t()
     _check(lib().spec_plan_panel(int(rows), int(k), int(n_head), int(k_top), int(n_proj), int(n_cu), C.byref(out)))
     return {name: int(getattr(out, name)) for name, _ in spec_plan_t._fields_}
