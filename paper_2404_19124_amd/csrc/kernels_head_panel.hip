@@ -46,7 +46,9 @@ struct PanelArgs {
   Partials part;
 };
 
-// MF = 16-row state fragments.
+// MF = 16-row state fragments.  (MF = 8 keeps 19 to 59 scalar registers, what the closing rows need of them, in lanes of a vector
+// register: written once in front of the tiles, read back 2 to 6 at a time in the closing blocks of 350 to 750 instructions, none in a
+// block that multiplies.  No more than some forty instructions of a wave's life, so nothing was given up for them.)
 template <int MF>
 struct PanelGeo {
   static constexpr int D = 8;                     // K-steps (of 32) of weights that a wave has on their way

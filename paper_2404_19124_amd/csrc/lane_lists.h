@@ -54,8 +54,9 @@ __device__ __forceinline__ uint64_t row8_best_key(uint64_t key) {
 constexpr size_t list_merge_bytes(int mb, int kt) { return (size_t)64 * mb * ((8 * kt + 1) * 8 + 8 * 8); }
 
 template <int MB, int KT>
-__device__ __forceinline__ void merge_lane_lists(unsigned char* smem, const double (&lk)[MB][KT], const float (&sum)[MB], int wave, int lane,
-                                                 int row0, int R, const Partials& part, int k_top, int nparts, int range) {
+__device__ __forceinline__ void merge_lane_lists(unsigned char* smem, const double (&lk)[MB][KT], const float (&sum)[MB],
+                                                 int wave, int lane, int row0, int R, const Partials& part, int k_top,
+                                                 int nparts, int range) {
   constexpr int ROWS = 64 * MB, RS = 8 * KT + 1;
   uint64_t* sk = reinterpret_cast<uint64_t*>(smem);            // [ROWS][RS]
   float* sm = reinterpret_cast<float*>(sk + ROWS * RS);        // [ROWS][8]
